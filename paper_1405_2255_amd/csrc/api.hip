@@ -135,7 +135,7 @@ struct fmm_ctx {
     // walk
     DevBuf fa, fb, m2l, m2l2, p2p, p2p2, p2pe, p2pe2, m2l_off, p2p_off, chunks, ccnt, coff, Fpart;
     DevBuf rflag, ranges, rkey, wcode, rup;
-    DevBuf pt_n, pt_m, pt_s, pt_off, pt_moff, ptasks, pchain, ppart;
+    DevBuf pt_n, pt_m, pt_s, pt_off, pt_moff, ptasks, pentry, pchain, ppart;
     DevBuf counters, nonfinite, walktmp, coffsets, ckey, ckey2, order, order2;
     DevBuf actflag, actf, actinv, actpre, cellact, actbad;   // forces for a listed subset
     DevBuf epsmin;                                           // smallest individual eps
@@ -240,7 +240,7 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
                        c->tree_off == std::vector<int64_t>(off, off + K + 1);
     double *x = ensure<double>(c->x, n), *y = ensure<double>(c->y, n), *z = ensure<double>(c->z, n),
            *m = ensure<double>(c->m, n);
-    double4 *xyzm = ensure<double4>(c->xyzm, n);
+    double4 *xyzm = ensure<double4>(c->xyzm, n + NEAR_PAD);
     c->refitted = reuse;
     if (reuse) {
         CK(launch_gather(pos, mass, c->perm, n, x, y, z, m, xyzm, s));
@@ -539,78 +539,91 @@ void prepare_p2p(fmm_ctx *c, int64_t nlist, bool by_source, bool side = false) {
     CK(launch_list_offsets(rk, runs, c->ncells, c->pb, off, s));
 }
 
-// direct sums of every leaf (prepared ranges), added into out4; with v4 (sorted
-// velocities) the FP64 kernel that also adds each pair's jerk into jo4
 // Direct-sum tasks of the prepared lists: per leaf the task counts, the
 // ancestor chains and the task list (active: leaves without listed sinks get
 // none).  side: on the side stream with its own scratch, counters and host
 // slots (the caller joins the side stream before the tasks run).
 struct P2PPlan {
-    int ntasks = 0, prows = 0;
-    int2 *tasks = nullptr;
-    int *nts = nullptr, *moff = nullptr, *chain = nullptr, *up = nullptr;
+    int width = 0;                 // sinks per task and entries of a partial row
+    int ntasks = 0, prows = 0;     // (FP64: a row per task)
+    int4 *near = nullptr;          // FP64 tasks, list entries and slices per leaf
+    int2 *entry = nullptr;
+    int2 *tasks = nullptr;         // mixed-precision tasks and their partial rows
+    int *nts = nullptr, *toff = nullptr, *moff = nullptr, *chain = nullptr;
 };
 
-P2PPlan plan_p2p(fmm_ctx *c, const uint8_t *active, bool side = false) {
+P2PPlan plan_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false) {
     const hipStream_t s = side ? c->side : c->stream;
     const int nl = c->nleaves;
     TreeArrays t = tree_arrays(c);
     P2PPlan pl;
+    pl.width = width;
     int *ntask = ensure<int>(c->pt_n, (size_t)nl + 1), *mtask = ensure<int>(c->pt_m, (size_t)nl + 1);
     pl.nts = ensure<int>(c->pt_s, (size_t)nl + 1);
-    int *toff = ensure<int>(c->pt_off, (size_t)nl + 1);
+    pl.toff = ensure<int>(c->pt_off, (size_t)nl + 1);
     pl.moff = ensure<int>(c->pt_moff, (size_t)nl + 1);
     int *tmp = side ? ensure<int>(c->tmp_side, scan_tmp_ints(nl + 1)) : tmp_ints(c, scan_tmp_ints(nl + 1));
     int *totals = ptr<int>(c->nonfinite) + (side ? 6 : 1);
     int *host = c->hint + (side ? 4 : 0);
+    const int *leaf_cell = ptr<int>(c->leaf_cell);
     const int64_t *off = ptr<int64_t>(c->p2p_off);
     const int2 *rg = ptr<int2>(c->ranges);
-    pl.up = ensure<int>(c->rup, (size_t)std::max(c->ncells, 1));
-    CK(launch_range_up(c->ncells, t.parent, off, pl.up, s));
-    pl.chain = ensure<int>(c->pchain, (size_t)std::max(nl, 1) * P2P_CHAIN);
-    CK(launch_p2p_plan(nl, ptr<int>(c->leaf_cell), off, rg, pl.up, t, active, ntask, mtask, pl.nts,
-                       toff, pl.moff, pl.chain, tmp, totals, s));
+    int *up = ensure<int>(c->rup, (size_t)std::max(c->ncells, 1));
+    CK(launch_range_up(c->ncells, t.parent, off, up, s));
+    if (width == 64) {
+        pl.chain = ensure<int>(c->pchain, (size_t)std::max(nl, 1) * P2P_CHAIN);
+        CK(launch_p2p_plan(nl, leaf_cell, off, rg, up, t, active, ntask, mtask, pl.nts, pl.toff,
+                           pl.moff, pl.chain, tmp, totals, s));
+    } else {
+        CK(launch_near_count(nl, width, leaf_cell, off, rg, up, t, active, ntask, pl.nts, mtask,
+                             pl.toff, pl.moff, tmp, totals, s));
+    }
     CK(hipMemcpyAsync(host, totals, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
     pl.ntasks = host[0];
-    pl.prows = host[1];
-    pl.tasks = ensure<int2>(c->ptasks, std::max(pl.ntasks, 1));
-    CK(launch_p2p_tasks(nl, toff, pl.tasks, s));
+    if (width == 64) {
+        pl.prows = host[1];
+        pl.tasks = ensure<int2>(c->ptasks, std::max(pl.ntasks, 1));
+        CK(launch_p2p_tasks(nl, pl.toff, pl.tasks, s));
+    } else {
+        pl.prows = pl.ntasks;
+        pl.near = ensure<int4>(c->ptasks, std::max(pl.ntasks, 1));
+        pl.entry = ensure<int2>(c->pentry, (size_t)host[1] + 64);
+        CK(launch_near_fill(nl, width, leaf_cell, off, rg, up, t, pl.nts, pl.toff, pl.moff,
+                            pl.near, pl.entry, s));
+    }
     return pl;
 }
 
 // the direct sums of a plan, added into out4 (and the jerk into jo4)
-void exec_p2p(fmm_ctx *c, const P2PPlan &pl, int want_f, int with_pot, int mixed, double4 *out4,
-              bool timed, const double4 *v4 = nullptr, double4 *jo4 = nullptr) {
+void exec_p2p(fmm_ctx *c, const P2PPlan &pl, int want_f, int with_pot, double4 *out4, bool timed,
+              const double4 *v4 = nullptr, double4 *jo4 = nullptr) {
     hipStream_t s = c->stream;
     TreeArrays t = tree_arrays(c);
-    const int64_t *off = ptr<int64_t>(c->p2p_off);
-    const int2 *rg = ptr<int2>(c->ranges);
-    double4 *part = ensure<double4>(c->ppart, (size_t)std::max(pl.prows, 1) * 64);
+    const int *leaf_cell = ptr<int>(c->leaf_cell), *leaf_of = ptr<int>(c->leaf_of);
+    const double4 *xyzm = ptr<double4>(c->xyzm);
+    const size_t rows = (size_t)std::max(pl.prows, 1) * pl.width;
+    double4 *part = ensure<double4>(c->ppart, rows);
+    double4 *jpart = v4 ? ensure<double4>(c->jpart, rows) : nullptr;
     if (timed && c->opts.timing) CK(hipEventRecord(c->ev_p2p[0], s));
-    double4 *jpart = nullptr;
-    if (v4) {
-        jpart = ensure<double4>(c->jpart, (size_t)std::max(pl.prows, 1) * 64);
-        CK(launch_p2p_jerk(pl.ntasks, pl.tasks, ptr<int>(c->leaf_cell), pl.nts, pl.moff, off, rg,
-                           pl.up, t, ptr<double4>(c->xyzm), v4, out4, jo4, part, jpart, s));
-    } else {
-        CK(launch_p2p(want_f, with_pot, mixed, pl.ntasks, pl.tasks, ptr<int>(c->leaf_cell), pl.nts,
-                      pl.moff, off, rg, pl.chain, t, ptr<double4>(c->xyzm), out4, part, s));
-    }
+    if (pl.width == 64)
+        CK(launch_p2p_mixed(pl.ntasks, pl.tasks, leaf_cell, pl.nts, pl.moff,
+                            ptr<int64_t>(c->p2p_off), ptr<int2>(c->ranges), pl.chain, t, xyzm,
+                            out4, part, s));
+    else if (v4)
+        CK(launch_p2p_jerk(pl.ntasks, pl.near, pl.entry, xyzm, v4, out4, jo4, part, jpart, s));
+    else
+        CK(launch_near(want_f, with_pot, pl.ntasks, pl.near, pl.entry, xyzm, out4, part, s));
     if (timed && c->opts.timing) CK(hipEventRecord(c->ev_p2p[1], s));
-    if (pl.prows > 0) {
-        CK(launch_p2p_reduce(c->n, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), pl.nts, pl.moff,
-                             t, part, out4, s));
-        if (v4)
-            CK(launch_p2p_reduce(c->n, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), pl.nts,
-                                 pl.moff, t, jpart, jo4, s));
+    if (pl.prows == 0) return;
+    if (pl.width == 64) {
+        CK(launch_p2p_reduce(c->n, leaf_of, leaf_cell, pl.nts, pl.moff, t, part, out4, s));
+        return;
     }
-}
-
-void run_p2p(fmm_ctx *c, int want_f, int with_pot, int mixed, double4 *out4, bool timed,
-             const uint8_t *active = nullptr, const double4 *v4 = nullptr,
-             double4 *jo4 = nullptr) {
-    exec_p2p(c, plan_p2p(c, active), want_f, with_pot, mixed, out4, timed, v4, jo4);
+    CK(launch_near_reduce(c->n, pl.width, leaf_of, leaf_cell, pl.nts, pl.toff, t, part, out4, s));
+    if (v4)
+        CK(launch_near_reduce(c->n, pl.width, leaf_of, leaf_cell, pl.nts, pl.toff, t, jpart, jo4,
+                              s));
 }
 
 // ------------------------------------------------------------ sink scale
@@ -643,7 +656,7 @@ void sink_scale(fmm_ctx *c, bool want_f, const double *eps_b) {
             CK(launch_est_l2l_level(want_f, t, c->ls[Lv], c->ls[Lv + 1], Fe, s));
         double4 *e4 = ensure<double4>(c->est4, n);
         CK(launch_est_l2p(want_f, t, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), n, Fe, e4, s));
-        run_p2p(c, want_f, 0, 0, e4, false);
+        exec_p2p(c, plan_p2p(c, nullptr, NEAR_R), want_f, 0, e4, false);
         CK(launch_scale(want_f, n, e4, scale, s));
     }
     if (eps_b) CK(launch_scale_eps(n, c->perm, eps_b, scale, s));
@@ -704,7 +717,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     double *P = ensure<double>(c->P, (size_t)(p + 1) * c->ncells);
     short *plans = ensure<short>(c->plans, 2 * XP_SIZE);
     double *Tsh = ensure<double>(c->Tsh, 2 * (size_t)nc * c->ncells);
-    double4 *v4 = vel ? ensure<double4>(c->vel4, n) : nullptr;
+    double4 *v4 = vel ? ensure<double4>(c->vel4, n + NEAR_PAD) : nullptr;
     double *Md = vel ? ensure<double>(c->Md, 2 * (size_t)nc * c->ncells) : nullptr;
     const hipStream_t us = c->side;
     CK(hipEventRecord(c->ev_fork, s));
@@ -824,7 +837,8 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     // the direct-sum lists, on the side stream (overlapping M2L, queued above)
     CK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
     prepare_p2p(c, L.n_p2p, true, true);
-    const P2PPlan near = plan_p2p(c, cell_active, true);
+    const bool near32 = c->opts.precision == FMM_PREC_MIXED && !vel;
+    const P2PPlan near = plan_p2p(c, cell_active, near32 ? 64 : vel ? NEAR_JERK_R : NEAR_R, true);
     CK(hipEventRecord(c->ev_join, c->side));
     c->join_pending = true;
     mark(c, PH_M2L);
@@ -850,7 +864,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     join_side(c);   // the direct-sum lists and tasks from the side stream
     // near field (with the jerk: FP64, potential and acceleration as the force-only
     // FP64 kernel sums them)
-    exec_p2p(c, near, 0, 1, c->opts.precision == FMM_PREC_MIXED && !vel, o4, true, v4, jo4);
+    exec_p2p(c, near, 0, 1, o4, true, v4, jo4);
     mark(c, PH_P2P);
     int *nonfinite = ptr<int>(c->nonfinite);
     CK(hipMemsetAsync(nonfinite, 0, sizeof(int), s));
@@ -1046,7 +1060,7 @@ void fmm_destroy(fmm_ctx *c) {
                       &c->rho2, &c->bsph, &c->smin, &c->leaf_cell, &c->M, &c->F, &c->P, &c->U, &c->Fe,
                       &c->fa, &c->fb, &c->m2l, &c->m2l2, &c->p2p, &c->p2p2, &c->p2pe,
                       &c->p2pe2, &c->rflag, &c->ranges, &c->rkey, &c->pt_n, &c->pt_m,
-                      &c->pt_s, &c->pt_off, &c->pt_moff, &c->ptasks, &c->pchain, &c->ppart, &c->m2l_off,
+                      &c->pt_s, &c->pt_off, &c->pt_moff, &c->ptasks, &c->pentry, &c->pchain, &c->ppart, &c->m2l_off,
                       &c->p2p_off, &c->chunks, &c->ccnt, &c->coff, &c->Fpart, &c->counters,
                       &c->nonfinite, &c->prev_scale, &c->walktmp, &c->coffsets,
                       &c->ckey, &c->ckey2, &c->order, &c->order2, &c->wcode, &c->rup, &c->tmp_side,

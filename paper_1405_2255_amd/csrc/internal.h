@@ -262,14 +262,40 @@ hipError_t launch_m2l_rot(int p, int64_t nlist, const uint64_t *list, int sh, co
                           hipStream_t s);
 
 // ---- p2p.hip ------------------------------------------------------------
-// near field of each sink leaf over its list, added to out4 (sorted order)
-// off: ncells + 1 offsets into range (per sink cell).  Planning: per leaf
-// the task counts (ntask, mtask, nsrc_tasks: nleaves + 1 ints each) and their
-// scans task_off, moff; totals[0] = tasks, totals[1] = partial rows.
-#define P2P_TASK 2048
+// Near field of each sink leaf over its list, added to out4 (sorted order).
+// off: ncells + 1 offsets into range (per sink cell).
 // up[c]: nearest proper ancestor of c with direct-sum ranges (or -1)
 hipError_t launch_range_up(int ncells, const int *parent, const int64_t *off, int *up,
                            hipStream_t s);
+// FP64 sums: tasks of up to `width` sinks (NEAR_R; NEAR_JERK_R with the jerk,
+// jerk.h) x NEAR_TASK sources (near.h).  Count and scan: tasks and list entries
+// per leaf (ntask, nentry and their scans task_off, entry_off: nleaves + 1 ints
+// each), nslice (nleaves); totals[0] = tasks, totals[1] = entries.  Fill: tasks
+// and entry (entry padded by 64).  Every task has a partial row of `width`
+// entries, used by leaves with more than one slice; the reduction adds those.
+#define NEAR_R 8
+#define NEAR_JERK_R 6
+#define NEAR_TASK 4096
+#define NEAR_PAD 128    // particles past n that the sums may load (and drop)
+hipError_t launch_near_count(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                             const int2 *range, const int *up, const TreeArrays &t,
+                             const uint8_t *active, int *ntask, int *nslice, int *nentry,
+                             int *task_off, int *entry_off, int *tmp, int *totals, hipStream_t s);
+hipError_t launch_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                            const int2 *range, const int *up, const TreeArrays &t,
+                            const int *nslice, const int *task_off, const int *entry_off,
+                            int4 *tasks, int2 *entry, hipStream_t s);
+hipError_t launch_near(int want_f, int with_pot, int ntasks, const int4 *tasks, const int2 *entry,
+                       const double4 *xyzm, double4 *out4, double4 *partial, hipStream_t s);
+hipError_t launch_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
+                              const int *nslice, const int *task_off, const TreeArrays &t,
+                              const double4 *partial, double4 *out4, hipStream_t s);
+// Mixed precision (FP32 pair arithmetic, separations in FP64, sums flushed to
+// FP64; potential and acceleration): tasks of up to 64 sinks x P2P_TASK sources.
+// Planning: per leaf the task counts (ntask, mtask, nsrc_tasks: nleaves + 1
+// ints each) and their scans task_off, moff; totals[0] = tasks, totals[1] =
+// partial rows (64 entries each).
+#define P2P_TASK 2048
 // chain: P2P_CHAIN ints per leaf, [0] = the number of cells on the leaf's
 // chain of ancestors that hold direct-sum ranges (the leaf first), then their
 // indices; written by the plan, read by the direct-sum kernel
@@ -280,12 +306,10 @@ hipError_t launch_p2p_plan(int nleaves, const int *leaf_cell, const int64_t *off
                            int *task_off, int *moff, int *chain, int *tmp, int *totals,
                            hipStream_t s);
 hipError_t launch_p2p_tasks(int nleaves, const int *task_off, int2 *tasks, hipStream_t s);
-// mixed != 0: FP32 pair arithmetic (separations in FP64, sums flushed to FP64)
-hipError_t launch_p2p(int want_f, int with_pot, int mixed, int ntasks, const int2 *tasks,
-                      const int *leaf_cell, const int *nsrc_tasks, const int *moff,
-                      const int64_t *off, const int2 *range, const int *chain,
-                      const TreeArrays &t, const double4 *xyzm, double4 *out4, double4 *partial,
-                      hipStream_t s);
+hipError_t launch_p2p_mixed(int ntasks, const int2 *tasks, const int *leaf_cell,
+                            const int *nsrc_tasks, const int *moff, const int64_t *off,
+                            const int2 *range, const int *chain, const TreeArrays &t,
+                            const double4 *xyzm, double4 *out4, double4 *partial, hipStream_t s);
 hipError_t launch_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell,
                              const int *nsrc_tasks, const int *moff, const TreeArrays &t,
                              const double4 *partial, double4 *out4, hipStream_t s);

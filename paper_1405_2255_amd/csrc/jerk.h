@@ -24,14 +24,12 @@ hipError_t launch_l2p_dot(int p, const TreeArrays &t, const int *leaf_of, const 
                           int64_t n, const double *x, const double *y, const double *z,
                           const double4 *v4, const double *F, const double *Fd, double4 *jo4,
                           hipStream_t s, const uint8_t *active = nullptr);
-// near field with jerk, FP64, in place of launch_p2p (same prepared tasks,
-// ranges and partial-row layout, same summation order, so out4 receives the
-// same values launch_p2p would add): (pot, a) added into out4, the jerk into
-// jo4; rows of multi-task leaves go to partial / jpartial and
-// launch_p2p_reduce adds each into its output
-hipError_t launch_p2p_jerk(int ntasks, const int2 *tasks, const int *leaf_cell,
-                           const int *nsrc_tasks, const int *moff, const int64_t *off,
-                           const int2 *range, const int *up, const TreeArrays &t,
+// near field with jerk, FP64, in place of launch_near (a plan of width
+// NEAR_JERK_R, the same summation order, so out4 receives the same values
+// launch_near would add): (pot, a) added into out4, the jerk into jo4; leaves
+// of more than one slice get partial / jpartial rows and launch_near_reduce
+// adds each into its output
+hipError_t launch_p2p_jerk(int ntasks, const int4 *tasks, const int2 *entry,
                            const double4 *xyzm, const double4 *v4, double4 *out4, double4 *jo4,
                            double4 *partial, double4 *jpartial, hipStream_t s);
 // exact jerk of listed sinks (input indices) against all n sources, written in

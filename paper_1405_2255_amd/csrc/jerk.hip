@@ -12,7 +12,7 @@
 // the rates from the row or column they already generate.
 #include "jerk.h"
 #include "harmonics.h"
-#include "range_loads.h"
+#include "near.h"
 
 namespace fmm {
 
@@ -192,42 +192,37 @@ k_l2p_dot(TreeArrays t, const int *leaf_of, const int *leaf_cell, int64_t n, con
 
 // ---- near field: potential, acceleration and jerk in one pass ---------------
 // d/dt [mu (x_a - x_b)/r^3] = mu [v_ab/r^3 - 3 (r . v_ab) r/r^5],
-// r = x_a - x_b, v_ab = v_a - v_b.  Same tasks, lane layout and summation
-// order as the force-only direct-sum kernel (a task is up to 64 sinks of a
-// leaf against one slice of P2P_TASK sources of the leaf's list; two sinks per
-// lane, lanes are (sink group, phase) pairs, phases added through LDS), so
-// the potential and acceleration are bit for bit those of the force-only
-// call; the jerk reuses each pair's separation and 1/r^3.
-constexpr int JR = 2;   // sinks per lane
-
-__device__ __forceinline__ int first_ranges(int c, const int *up, const int64_t *off) {
-    return off[c + 1] > off[c] ? c : up[c];
-}
-
-struct Sink {
-    double4 x, v;            // position (w: mass, unused), velocity
-    double4 f;               // (pot, ax, ay, az)
-    double jx, jy, jz;
-};
-
-// Summed with 2/|r| in place of 1/|r|, as the force-only direct sums are
-// (the same operations, so potential and acceleration equal theirs bit for
-// bit): potential times 2, acceleration and jerk times 8, scaled back once per
-// sink.
+// r = x_a - x_b, v_ab = v_a - v_b.  Same slices, lanes and summation order as
+// the force-only FP64 direct sums (near.h), so the potential and acceleration
+// are bit for bit those of the force-only call; the jerk reuses each pair's
+// separation and 1/r^3.
+//
+// Summed with 2/|r| in place of 1/|r|, as the force-only direct sums are:
+// potential times 2, acceleration and jerk times 8, scaled back once per sink.
 constexpr double JERK_POT_BACK = 0.5, JERK_ACC_BACK = 0.125;
 
-__device__ __forceinline__ void pair_jerk(const double4 s, const double4 va, bool skip, Sink &k) {
-    const double dx = s.x - k.x.x, dy = s.y - k.x.y, dz = s.z - k.x.z;
+struct Moving {
+    double4 x, v;            // position and mass, velocity
+};
+
+struct SinkSum {
+    double pot, ax, ay, az, jx, jy, jz;
+};
+
+__device__ __forceinline__ void pair_jerk(const Moving &s, double xb, double yb, double zb,
+                                          double ub, double vb, double wb, bool skip,
+                                          SinkSum &k) {
+    const double dx = s.x.x - xb, dy = s.x.y - yb, dz = s.x.z - zb;
     const double r2 = skip ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
-    const double mu = skip ? 0.0 : s.w;
+    const double mu = skip ? 0.0 : s.x.w;
     const double ri = rsqrt2_nr(r2);            // 2/|r|
     const double q = mu * ri;
     const double q3 = q * ri * ri;
-    k.f.x += q;
-    k.f.y = fma(q3, dx, k.f.y);
-    k.f.z = fma(q3, dy, k.f.z);
-    k.f.w = fma(q3, dz, k.f.w);
-    const double ux = va.x - k.v.x, uy = va.y - k.v.y, uz = va.z - k.v.z;
+    k.pot += q;
+    k.ax = fma(q3, dx, k.ax);
+    k.ay = fma(q3, dy, k.ay);
+    k.az = fma(q3, dz, k.az);
+    const double ux = s.v.x - ub, uy = s.v.y - vb, uz = s.v.z - wb;
     // 3 (r.u)/r^2 = 0.75 (r.u) (2/|r|)^2
     const double rv = 0.75 * fma(dx, ux, fma(dy, uy, dz * uz)) * (ri * ri);
     k.jx = fma(q3, fma(-rv, dx, ux), k.jx);
@@ -235,137 +230,79 @@ __device__ __forceinline__ void pair_jerk(const double4 s, const double4 va, boo
     k.jz = fma(q3, fma(-rv, dz, uz), k.jz);
 }
 
-// one lane's share of a source range that overlaps its sinks' own leaf:
-// sources a, a + stride, ... below e (the sinks themselves skipped by index),
-// the next source loaded before the current one is summed
-__device__ __forceinline__ void sum_own_jerk(const double4 *xyzm, const double4 *v4, int a,
-                                             int e, int stride, const int (&self)[JR],
-                                             Sink (&k)[JR]) {
-    if (a >= e) return;
-    double4 s = xyzm[a], va = v4[a];
-    for (;;) {
-        const int b = a + stride;
-        const bool more = b < e;
-        const double4 s2 = xyzm[more ? b : a], vb = v4[more ? b : a];
+template <int R>
+__device__ __forceinline__ void near_jerk(const NearTask &q, const int2 *entry,
+                                          const double4 *xyzm, const double4 *v4, double4 *out4,
+                                          double4 *jo4, double4 *row, double4 *jrow) {
+    const int lane = lane_id();
+    const double4 mx = xyzm[q.sb + (lane < R ? lane : 0)];
+    const double4 mv = v4[q.sb + (lane < R ? lane : 0)];
+    double sx[R], sy[R], sz[R], su[R], sv[R], sw[R];
+    SinkSum f[R];
 #pragma unroll
-        for (int r = 0; r < JR; ++r) pair_jerk(s, va, a == self[r], k[r]);
-        if (!more) break;
-        a = b;
-        s = s2;
-        va = vb;
+    for (int k = 0; k < R; ++k) {
+        sx[k] = readlane_f64(mx.x, k);
+        sy[k] = readlane_f64(mx.y, k);
+        sz[k] = readlane_f64(mx.z, k);
+        su[k] = readlane_f64(mv.x, k);
+        sv[k] = readlane_f64(mv.y, k);
+        sw[k] = readlane_f64(mv.z, k);
+        f[k] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     }
-}
-
-// The same for a range that holds none of the sinks, read from its start in
-// scalar registers: sources xs[i], xs[i + stride], ... below xs[n] with their
-// velocities vs[...] (n <= P2P_TASK).
-__device__ __forceinline__ void sum_far_jerk(const double4 *xs, const double4 *vs, uint32_t i,
-                                             uint32_t n, uint32_t stride, Sink (&k)[JR]) {
-    gchar *bx = uniform_base(xs), *bv = uniform_base(vs);
-    const uint32_t oe = n * 32u, st = stride * 32u;
-    for (uint32_t o = i * 32u; o < oe; o += st) {
-        const double4 s = load_source(bx + o), va = load_source(bv + o);
+    near_sources(
+        entry, q, [&](uint32_t i) { return Moving{load32(xyzm, i), load32(v4, i)}; },
+        [&](const Moving &a) {
 #pragma unroll
-        for (int r = 0; r < JR; ++r) pair_jerk(s, va, false, k[r]);
-    }
-}
-
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k_p2p_jerk(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks,
-           const int *moff, const int64_t *off, const int2 *range, const int *up, TreeArrays t,
-           const double4 *xyzm, const double4 *v4, double4 *out4, double4 *jo4,
-           double4 *partial, double4 *jpartial) {
-    __shared__ double4 red[4][JR * FMM_WAVE];
-    __shared__ double4 jred[4][JR * FMM_WAVE];
-    const int task = xcd_block(blockIdx.x, gridDim.x) * 4 + threadIdx.x / FMM_WAVE;
-    if (task >= ntasks) return;                // whole wavefronts leave together
-    const int lane = lane_id(), w = threadIdx.x / FMM_WAVE;
-    const int2 tk = tasks[task];
-    const int leaf = tk.x;
-    const int c = leaf_cell[leaf];
-    const int nts = nsrc_tasks[leaf];
-    const int sc = tk.y / nts, ts = tk.y % nts;
-    const int sb = t.beg[c] + sc * FMM_WAVE;
-    const int nb = min(t.end[c] - sb, FMM_WAVE);
-    const int ng = (nb + JR - 1) / JR;
-    const int S = FMM_WAVE / ng;               // phases per lane group
-    const int g = lane % ng, phase = lane / ng;
-    const bool active = phase < S;
-    Sink k[JR];
-    int self[JR];
-#pragma unroll
-    for (int r = 0; r < JR; ++r) {
-        const int slot = g + r * ng < nb ? g + r * ng : g;
-        self[r] = sb + slot;
-        k[r].x = xyzm[self[r]];
-        k[r].v = v4[self[r]];
-        k[r].f = make_double4(0.0, 0.0, 0.0, 0.0);
-        k[r].jx = k[r].jy = k[r].jz = 0.0;
-    }
-    int64_t skip = (int64_t)ts * P2P_TASK, left = P2P_TASK;
-    for (int anc = first_ranges(c, up, off); anc >= 0 && left > 0; anc = up[anc]) {
-        const int64_t r1 = off[anc + 1];
-        for (int64_t rb = off[anc]; rb < r1 && left > 0; rb += FMM_WAVE) {
-            const int2 mine = rb + lane < r1 ? range[rb + lane] : make_int2(0, 0);
-            const int nbat = (int)min((int64_t)FMM_WAVE, r1 - rb);
-            for (int j = 0; j < nbat && left > 0; ++j) {
-                int2 rg = make_int2(__builtin_amdgcn_readlane(mine.x, j),
-                                    __builtin_amdgcn_readlane(mine.y, j));
-                const int len = rg.y - rg.x;
-                if (skip >= len) {
-                    skip -= len;
-                    continue;
-                }
-                rg.x += (int)skip;
-                skip = 0;
-                if (rg.y - rg.x > left) rg.y = rg.x + (int)left;
-                left -= rg.y - rg.x;
-                if (!active) continue;
-                const bool own = rg.x < sb + nb && rg.y > sb;   // overlaps the task's sinks
-                if (own) sum_own_jerk(xyzm, v4, rg.x + phase, rg.y, S, self, k);
-                else sum_far_jerk(xyzm + rg.x, v4 + rg.x, phase, (uint32_t)(rg.y - rg.x), S, k);
+            for (int k = 0; k < R; ++k) {
+                pair_jerk(a, sx[k], sy[k], sz[k], su[k], sv[k], sw[k], false, f[k]);
+                if (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);
             }
-        }
-    }
-    // phases of slot q sit at red[w][q + phase * JR * ng]; active lanes cover
-    // every index below JR * ng * S <= JR * 64 exactly once
-    if (active) {
+        },
+        [&](Moving a, uint32_t i, bool on) {
+            if (!on) a.x = a.v = make_double4(0.0, 0.0, 0.0, 0.0);
 #pragma unroll
-        for (int r = 0; r < JR; ++r) {
-            red[w][g + r * ng + phase * JR * ng] = k[r].f;
-            jred[w][g + r * ng + phase * JR * ng] = make_double4(0.0, k[r].jx, k[r].jy, k[r].jz);
-        }
+            for (int k = 0; k < R; ++k) {
+                pair_jerk(a, sx[k], sy[k], sz[k], su[k], sv[k], sw[k],
+                          !on || i == (uint32_t)(q.sb + k), f[k]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    // lane i of each row of 16 lanes takes one component of sink i
+    double v = 0.0, vj = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const double w = wave_sum4(f[k].pot, f[k].ax, f[k].ay, f[k].az);
+        const double wj = wave_sum4(0.0, f[k].jx, f[k].jy, f[k].jz);
+        v = (lane & 15) == k ? w : v;
+        vj = (lane & 15) == k ? wj : vj;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane >= nb) return;
-    double4 v = red[w][lane], jv = jred[w][lane];
-    for (int ph = 1; ph < S; ++ph) {
-        const double4 q = red[w][lane + ph * JR * ng], qj = jred[w][lane + ph * JR * ng];
-        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
-        jv.y += qj.y; jv.z += qj.z; jv.w += qj.w;
-    }
-    v.x *= JERK_POT_BACK;
-    v.y *= JERK_ACC_BACK;
-    v.z *= JERK_ACC_BACK;
-    v.w *= JERK_ACC_BACK;
-    jv.y *= JERK_ACC_BACK;
-    jv.z *= JERK_ACC_BACK;
-    jv.w *= JERK_ACC_BACK;
-    const int bo = sb + lane;
-    if (moff[leaf + 1] == moff[leaf]) {        // the leaf's only task
-        double4 o = out4[bo];
-        o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
-        out4[bo] = o;
-        double4 oj = jo4[bo];
-        oj.y += jv.y; oj.z += jv.z; oj.w += jv.w;
-        jo4[bo] = oj;
+    const int comp = wave_sum4_component(), s = lane & 15;
+    v *= comp == 0 ? JERK_POT_BACK : JERK_ACC_BACK;
+    vj *= JERK_ACC_BACK;
+    if (s >= R) return;
+    if (q.single) {
+        reinterpret_cast<double *>(out4 + q.sb + s)[comp] += v;
+        reinterpret_cast<double *>(jo4 + q.sb + s)[comp] += vj;
     } else {
-        const int64_t row = ((int64_t)moff[leaf] + tk.y) * FMM_WAVE + lane;
-        partial[row] = v;
-        jpartial[row] = jv;
+        reinterpret_cast<double *>(row + s)[comp] = v;
+        reinterpret_cast<double *>(jrow + s)[comp] = vj;
     }
+}
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_p2p_jerk(int ntasks, const int4 *tasks, const int2 *entry, const double4 *xyzm,
+           const double4 *v4, double4 *out4, double4 *jo4, double4 *partial, double4 *jpartial) {
+    const int task = blockIdx.x * 4 + threadIdx.x / FMM_WAVE;
+    if (task >= ntasks) return;                // whole wavefronts leave together
+    const NearTask q = unpack_task(tasks[task]);
+    double4 *row = partial + (size_t)task * NEAR_JERK_R;
+    double4 *jrow = jpartial + (size_t)task * NEAR_JERK_R;
+    static_assert(NEAR_JERK_R == 6, "the cases below");
+#define FMM_NEAR(R) case R: near_jerk<R>(q, entry, xyzm, v4, out4, jo4, row, jrow); break
+    switch (q.r) {
+        FMM_NEAR(1); FMM_NEAR(2); FMM_NEAR(3); FMM_NEAR(4); FMM_NEAR(5); FMM_NEAR(6);
+    }
+#undef FMM_NEAR
 }
 
 // listed sinks: jerk[3 j + d] = G jo4[inv[act[j]]].(y, z, w) (indices out of
@@ -474,15 +411,12 @@ hipError_t launch_l2p_dot(int p, const TreeArrays &t, const int *leaf_of, const 
     return hipGetLastError();
 }
 
-hipError_t launch_p2p_jerk(int ntasks, const int2 *tasks, const int *leaf_cell,
-                           const int *nsrc_tasks, const int *moff, const int64_t *off,
-                           const int2 *range, const int *up, const TreeArrays &t,
+hipError_t launch_p2p_jerk(int ntasks, const int4 *tasks, const int2 *entry,
                            const double4 *xyzm, const double4 *v4, double4 *out4, double4 *jo4,
                            double4 *partial, double4 *jpartial, hipStream_t s) {
     if (ntasks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_p2p_jerk, dim3(blocks(ntasks, 4)), dim3(256), 0, s, ntasks, tasks,
-                       leaf_cell, nsrc_tasks, moff, off, range, up, t, xyzm, v4, out4, jo4,
-                       partial, jpartial);
+    hipLaunchKernelGGL(k_p2p_jerk, dim3(blocks(ntasks, 4)), dim3(256), 0, s, ntasks, tasks, entry,
+                       xyzm, v4, out4, jo4, partial, jpartial);
     return hipGetLastError();
 }
 

@@ -4,29 +4,31 @@
 //
 // P2P: the sources of a sink leaf are the merged particle ranges listed for
 // the leaf and for each of its ancestors (a direct sum accepted for a cell
-// applies to all particles below it).  A leaf's work is cut into tasks of at
-// most 64 sinks x P2P_TASK sources - a sparse leaf far out in an untruncated
-// halo can be summed against every particle, and as one wavefront's serial
-// loop it would set the kernel time; short tasks also even out the load of
-// the compute units at the end of a launch.  One wavefront per task: every lane holds
-// two sinks, lanes are (sink group, phase) pairs, the phases stride through
-// each range and are summed through LDS at the end, so small leaves still fill
-// the wavefront and every source load serves two pairs.  A leaf with one task
-// adds into the output directly; otherwise each task writes a row of partial
-// sums that a second kernel adds in task order (deterministic).
+// applies to all particles below it).  A leaf's work is cut into tasks of a few
+// sinks x P2P_TASK sources - a sparse leaf far out in an untruncated halo can
+// be summed against every particle, and as one wavefront's serial loop it
+// would set the kernel time; short tasks also even out the load of the compute
+// units at the end of a launch.  One wavefront per task.  FP64 sums hold up to
+// NEAR_R sinks in scalar registers and one source per lane (near.h).
+// Mixed-precision sums hold up to 64 sinks of a leaf, two per lane, lanes being
+// (sink group, phase) pairs that stride through each range; the phases are
+// summed through LDS at the end.  A leaf with one task adds into the output
+// directly; otherwise each task writes a row of partial sums that a second
+// kernel adds in task order (deterministic).
 // Source particles are read as (x, y, z, m) double4 from the key-sorted copy.
 #include <algorithm>
 
 #include "internal.h"
 #include "dev.h"
+#include "near.h"
 #include "range_loads.h"
 
 namespace fmm {
 
 namespace {
 
-// sinks per lane of the P2P kernel (two halves the source loads per pair;
-// more costs occupancy)
+// sinks per lane of the mixed-precision kernel (two halves the source loads
+// per pair; more costs occupancy)
 constexpr int P2P_R = 2;
 
 // up[c] = the nearest proper ancestor of c that has direct-sum ranges (or -1),
@@ -64,8 +66,8 @@ __device__ __forceinline__ int64_t leaf_sources(int c, const int *up, const int6
     return s;
 }
 
-// per leaf (one wavefront each): tasks = sink chunks of 64 x source chunks of
-// P2P_TASK sources; mtask = tasks that need a partial-sum row (leaves with
+// plan of the mixed-precision sums, per leaf (one wavefront each): tasks = sink
+// chunks of 64 x source chunks of P2P_TASK sources; mtask = tasks that need a partial-sum row (leaves with
 // more than one task) (active: when not null, leaves whose cell holds no
 // listed sink get no task); entry nleaves is zeroed for the scans.  Also the
 // leaf's chain of ancestors with ranges, so that the direct-sum tasks load it
@@ -123,9 +125,9 @@ __global__ void k_p2p_tasks(int nleaves, const int *task_off, int2 *tasks) {
 constexpr double P2P_POT_BACK = 0.5, P2P_ACC_BACK = 0.125;
 
 template <int WANT_F, int WITH_POT>
-__device__ __forceinline__ void pair(const double4 s, const double4 xb, bool skip, double &pot,
-                                     double &ax, double &ay, double &az) {
-    const double dx = s.x - xb.x, dy = s.y - xb.y, dz = s.z - xb.z;
+__device__ __forceinline__ void pair(const double4 s, double xb, double yb, double zb, bool skip,
+                                     double &pot, double &ax, double &ay, double &az) {
+    const double dx = s.x - xb, dy = s.y - yb, dz = s.z - zb;
     const double r2 = skip ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
     const double mu = skip ? 0.0 : s.w;
     if (WANT_F) {
@@ -146,23 +148,18 @@ __device__ __forceinline__ void pair(const double4 s, const double4 xb, bool ski
 // are FP32 (every pair's contribution carries a relative error of a few
 // FP32 units).  Only ranges without the sinks themselves come here: no
 // self-pair test.
-template <int WANT_F, int WITH_POT>
 __device__ __forceinline__ void pair32(const double4 s, const double4 xb, float &pot, float &ax,
                                        float &ay, float &az) {
     const float dx = (float)(s.x - xb.x), dy = (float)(s.y - xb.y), dz = (float)(s.z - xb.z);
     const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
     const float mu = (float)s.w;
-    if (WANT_F) {
-        pot += mu * __builtin_amdgcn_rcpf(r2);
-    } else {
-        const float ri = __builtin_amdgcn_rsqf(r2);
-        const float q = mu * ri;
-        const float q3 = q * ri * ri;
-        if (WITH_POT) pot += q;
-        ax = fmaf(q3, dx, ax);
-        ay = fmaf(q3, dy, ay);
-        az = fmaf(q3, dz, az);
-    }
+    const float ri = __builtin_amdgcn_rsqf(r2);
+    const float q = mu * ri;
+    const float q3 = q * ri * ri;
+    pot += q;
+    ax = fmaf(q3, dx, ax);
+    ay = fmaf(q3, dy, ay);
+    az = fmaf(q3, dz, az);
 }
 
 // FP32 partial sums run over at most this many sources per lane before they
@@ -173,7 +170,7 @@ constexpr int P2P_CHUNK32 = 32;
 // sources p[0], p[stride], ... below pe (the sinks themselves skipped by
 // address), the next source loaded before the current one is summed.  Always
 // FP64.
-template <int R, int WANT_F, int WITH_POT>
+template <int R>
 __device__ __forceinline__ void sum_own(const double4 *p, const double4 *pe, int stride,
                                         const double4 (&xb)[R], const double4 *const (&self)[R],
                                         double4 (&f)[R]) {
@@ -185,7 +182,7 @@ __device__ __forceinline__ void sum_own(const double4 *p, const double4 *pe, int
         const double4 b = (more ? q : p)[0];
 #pragma unroll
         for (int k = 0; k < R; ++k)
-            pair<WANT_F, WITH_POT>(a, xb[k], p == self[k], f[k].x, f[k].y, f[k].z, f[k].w);
+            pair<0, 1>(a, xb[k].x, xb[k].y, xb[k].z, p == self[k], f[k].x, f[k].y, f[k].z, f[k].w);
         if (!more) break;
         p = q;
         a = b;
@@ -196,24 +193,9 @@ static_assert((int64_t)P2P_TASK * sizeof(double4) < (int64_t(1) << 32),
               "byte offsets within a task's source range fit 32 bits");
 
 // One lane's share of a source range that holds none of its sinks: sources
-// base[i], base[i + stride], ... below base[n] (n <= P2P_TASK).
-template <int R, int WANT_F, int WITH_POT>
-__device__ __forceinline__ void sum_far(const double4 *base, uint32_t i, uint32_t n,
-                                        uint32_t stride, const double4 (&xb)[R],
-                                        double4 (&f)[R]) {
-    gchar *b = uniform_base(base);
-    const uint32_t oe = n * 32u, st = stride * 32u;
-    for (uint32_t o = i * 32u; o < oe; o += st) {
-        const double4 a = load_source(b + o);
-#pragma unroll
-        for (int k = 0; k < R; ++k)
-            pair<WANT_F, WITH_POT>(a, xb[k], false, f[k].x, f[k].y, f[k].z, f[k].w);
-    }
-}
-
-// The same in mixed precision: FP32 partial sums over at most P2P_CHUNK32
-// sources per lane, then added into the FP64 sums.
-template <int R, int WANT_F, int WITH_POT>
+// base[i], base[i + stride], ... below base[n] (n <= P2P_TASK), FP32 partial
+// sums over at most P2P_CHUNK32 sources per lane, then added into the FP64 sums.
+template <int R>
 __device__ __forceinline__ void sum_far32(const double4 *base, uint32_t i, uint32_t n,
                                           uint32_t stride, const double4 (&xb)[R],
                                           double4 (&f)[R]) {
@@ -228,10 +210,9 @@ __device__ __forceinline__ void sum_far32(const double4 *base, uint32_t i, uint3
             const double4 a = load_source(b + o);
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                pair32<WANT_F, WITH_POT>(a, xb[k], g[k].x, g[k].y, g[k].z, g[k].w);
+                pair32(a, xb[k], g[k].x, g[k].y, g[k].z, g[k].w);
         }
-        constexpr double sp = WANT_F ? 1.0 : 1.0 / P2P_POT_BACK;
-        constexpr double sa = WANT_F ? 1.0 : 1.0 / P2P_ACC_BACK;
+        constexpr double sp = 1.0 / P2P_POT_BACK, sa = 1.0 / P2P_ACC_BACK;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             f[k].x = fma((double)g[k].x, sp, f[k].x);
@@ -245,9 +226,9 @@ __device__ __forceinline__ void sum_far32(const double4 *base, uint32_t i, uint3
 // R sinks per lane: ng = ceil(nb / R) lane groups, group g holds sink slots
 // g, g + ng, g + 2 ng, ... (a slot past the leaf repeats slot g and is
 // discarded); lanes [0, ng * S) are (group, phase) with S = floor(64 / ng).
-template <int R, int WANT_F, int WITH_POT, int MIXED>
+template <int R>
 __global__ void __launch_bounds__(256)
-k_p2p(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks,
+k_p2p_mixed(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks,
       const int *moff, const int64_t *off, const int2 *range, const int *chain, TreeArrays t,
       const double4 *xyzm, double4 *out4, double4 *partial) {
     __shared__ double4 red[4][R * FMM_WAVE];
@@ -309,9 +290,9 @@ k_p2p(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks
             // terms: summed in FP64 also in mixed precision
             const uint32_t nr = (uint32_t)(rg.y - rg.x);
             if (own)
-                sum_own<R, WANT_F, WITH_POT>(xyzm + rg.x + phase, xyzm + rg.y, S, xb, self, f);
-            else if (MIXED) sum_far32<R, WANT_F, WITH_POT>(xyzm + rg.x, phase, nr, S, xb, f);
-            else sum_far<R, WANT_F, WITH_POT>(xyzm + rg.x, phase, nr, S, xb, f);
+                sum_own<R>(xyzm + rg.x + phase, xyzm + rg.y, S, xb, self, f);
+            else
+                sum_far32<R>(xyzm + rg.x, phase, nr, S, xb, f);
           }
         }
     }
@@ -330,12 +311,10 @@ k_p2p(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks
         const double4 q = red[w][lane + ph * R * ng];
         v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
     }
-    if (!WANT_F) {
-        v.x *= P2P_POT_BACK;
-        v.y *= P2P_ACC_BACK;
-        v.z *= P2P_ACC_BACK;
-        v.w *= P2P_ACC_BACK;
-    }
+    v.x *= P2P_POT_BACK;
+    v.y *= P2P_ACC_BACK;
+    v.z *= P2P_ACC_BACK;
+    v.w *= P2P_ACC_BACK;
     const int bi = sb + lane;
     if (moff[leaf + 1] == moff[leaf]) {          // the leaf's only task
         double4 o = out4[bi];
@@ -346,7 +325,190 @@ k_p2p(int ntasks, const int2 *tasks, const int *leaf_cell, const int *nsrc_tasks
     }
 }
 
-// add the partial sums of multi-task leaves, in task order
+// *out += row[0] + row[stride] + ... (n rows): eight rows' loads in flight at a
+// time, added in order
+__device__ __forceinline__ void add_rows(double4 *out, const double4 *row, int64_t stride, int n) {
+    double4 v = *out;
+    for (int t0 = 0; t0 < n; t0 += 8) {
+        double4 q[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) q[j] = row[min(t0 + j, n - 1) * stride];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (t0 + j < n) {
+                v.x += q[j].x; v.y += q[j].y; v.z += q[j].z; v.w += q[j].w;
+            }
+        }
+    }
+    *out = v;
+}
+
+// FP64 sums of one task: R sinks in scalar registers, a source per lane.  The
+// pairs of a step are scheduled four at a time, which is enough to cover the
+// latency of a dependent operation and keeps the kernel within 128 registers
+// (four wavefronts per SIMD).
+template <int R, int WANT_F, int WITH_POT>
+__device__ __forceinline__ void near_sum(const NearTask &q, const int2 *entry,
+                                         const double4 *xyzm, double4 *out4, double4 *row) {
+    const int lane = lane_id();
+    const double4 mine = xyzm[q.sb + (lane < R ? lane : 0)];
+    double sx[R], sy[R], sz[R], f[R][4];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        sx[k] = readlane_f64(mine.x, k);
+        sy[k] = readlane_f64(mine.y, k);
+        sz[k] = readlane_f64(mine.z, k);
+        f[k][0] = f[k][1] = f[k][2] = f[k][3] = 0.0;
+    }
+    near_sources(
+        entry, q, [&](uint32_t i) { return load32(xyzm, i); },
+        [&](const double4 &a) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                pair<WANT_F, WITH_POT>(a, sx[k], sy[k], sz[k], false, f[k][0], f[k][1], f[k][2],
+                                       f[k][3]);
+                if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        },
+        [&](double4 a, uint32_t i, bool on) {
+            if (!on) a = make_double4(0.0, 0.0, 0.0, 0.0);
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                pair<WANT_F, WITH_POT>(a, sx[k], sy[k], sz[k], !on || i == (uint32_t)(q.sb + k),
+                                       f[k][0], f[k][1], f[k][2], f[k][3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    // lane i of each row of 16 lanes takes one component of sink i
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const double w = wave_sum4(f[k][0], f[k][1], f[k][2], f[k][3]);
+        v = (lane & 15) == k ? w : v;
+    }
+    const int comp = wave_sum4_component(), s = lane & 15;
+    if (!WANT_F) v *= comp == 0 ? P2P_POT_BACK : P2P_ACC_BACK;
+    if (s >= R) return;
+    if (q.single) reinterpret_cast<double *>(out4 + q.sb + s)[comp] += v;
+    else reinterpret_cast<double *>(row + s)[comp] = v;
+}
+
+template <int WANT_F, int WITH_POT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_p2p(int ntasks, const int4 *tasks, const int2 *entry, const double4 *xyzm, double4 *out4,
+      double4 *partial) {
+    const int task = blockIdx.x * 4 + threadIdx.x / FMM_WAVE;
+    if (task >= ntasks) return;                  // whole wavefronts leave together
+    const NearTask q = unpack_task(tasks[task]);
+    double4 *row = partial + (size_t)task * NEAR_R;
+    static_assert(NEAR_R == 8, "the cases below");
+#define FMM_NEAR(R) case R: near_sum<R, WANT_F, WITH_POT>(q, entry, xyzm, out4, row); break
+    switch (q.r) {
+        FMM_NEAR(1); FMM_NEAR(2); FMM_NEAR(3); FMM_NEAR(4);
+        FMM_NEAR(5); FMM_NEAR(6); FMM_NEAR(7); FMM_NEAR(8);
+    }
+#undef FMM_NEAR
+}
+
+// Plan of the FP64 direct sums, one wavefront per leaf.  Count: the leaf's
+// tasks (groups of at most `width` sinks x slices of NEAR_TASK sources), its
+// slices and its list entries (its and its ancestors' ranges, and the closing
+// entry); active: when not null, leaves whose cell holds no listed sink get
+// none.  Entry nleaves is zeroed for the scans.
+__global__ void k_near_count(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                             const int2 *range, const int *up, TreeArrays t,
+                             const uint8_t *active, int *ntask, int *nslice, int *nentry) {
+    const int leaf = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FMM_WAVE);
+    if (leaf > nleaves) return;
+    int tasks = 0, slices = 0;
+    int64_t entries = 0;
+    const int c = leaf < nleaves ? leaf_cell[leaf] : -1;
+    if (c >= 0 && (!active || active[c])) {
+        for (int a = first_with_ranges(c, up, off); a >= 0; a = up[a])
+            entries += off[a + 1] - off[a];
+        const int64_t S = leaf_sources(c, up, off, range);
+        slices = (int)max((int64_t)1, (S + NEAR_TASK - 1) / NEAR_TASK);
+        tasks = slices * ((t.end[c] - t.beg[c] + width - 1) / width);
+        ++entries;
+    }
+    if (lane_id() != 0) return;
+    ntask[leaf] = tasks;
+    nentry[leaf] = (int)entries;
+    if (leaf < nleaves) nslice[leaf] = slices;
+}
+
+// Fill: the list entries (shift, end) of every leaf and its tasks, slice by
+// slice (the groups of a slice next to each other, so that the wavefronts of a
+// block read the same sources).
+__global__ void k_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                            const int2 *range, const int *up, TreeArrays t, const int *nslice,
+                            const int *task_off, const int *entry_off, int4 *tasks,
+                            int2 *entry) {
+    const int leaf = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FMM_WAVE);
+    if (leaf >= nleaves) return;
+    const int e0 = entry_off[leaf], k0 = task_off[leaf];
+    if (task_off[leaf + 1] == k0) return;
+    const int lane = lane_id(), c = leaf_cell[leaf], nts = nslice[leaf];
+    const int beg = t.beg[c], nb = t.end[c] - beg, ng = (nb + width - 1) / width;
+    // the leaf's position count is known only at the end; a slice is full
+    // unless it is the last one, which is written then
+    int pos = 0, d = 0, last_first = e0;
+    for (int a = first_with_ranges(c, up, off); a >= 0; a = up[a]) {
+        const int64_t r1 = off[a + 1];
+        for (int64_t rb = off[a]; rb < r1; rb += FMM_WAVE) {
+            const int2 rg = rb + lane < r1 ? range[rb + lane] : make_int2(0, 0);
+            const int len = rg.y - rg.x;
+            const int end = pos + wave_incl_scan(len), begin = end - len;
+            if (rb + lane < r1) entry[e0 + d + lane] = make_int2(rg.x - begin, end);
+            // slices that begin in this lane's range
+            const int s0 = (begin + NEAR_TASK - 1) / NEAR_TASK;
+            const int s1 = len > 0 ? (end - 1) / NEAR_TASK : s0 - 1;
+            unsigned long long who = __ballot(s1 >= s0);
+            while (who) {
+                const int l = __ffsll((long long)who) - 1;
+                who &= who - 1;
+                const int t0 = __builtin_amdgcn_readlane(s0, l);
+                const int t1 = __builtin_amdgcn_readlane(s1, l);
+                const int first = e0 + d + l;
+                const int m = (min(t1, nts - 2) - t0 + 1) * ng;
+                for (int k = lane; k < m; k += FMM_WAVE) {
+                    const int ts = t0 + k / ng, g = k % ng;
+                    const int b0 = group_begin(nb, ng, g), b1 = group_begin(nb, ng, g + 1);
+                    tasks[k0 + ts * ng + g] =
+                        pack_task(beg + b0, first, ts * NEAR_TASK, b1 - b0, NEAR_TASK, false);
+                }
+                if (t1 == nts - 1) last_first = first;
+            }
+            d += (int)min((int64_t)FMM_WAVE, r1 - rb);
+            pos = __builtin_amdgcn_readlane(end, FMM_WAVE - 1);
+        }
+    }
+    const int ts = nts - 1;
+    for (int g = lane; g < ng; g += FMM_WAVE) {
+        const int b0 = group_begin(nb, ng, g), b1 = group_begin(nb, ng, g + 1);
+        tasks[k0 + ts * ng + g] = pack_task(beg + b0, last_first, ts * NEAR_TASK, b1 - b0,
+                                            pos - ts * NEAR_TASK, nts == 1);
+    }
+    if (lane == 0) entry[e0 + d] = make_int2(-pos, INT_MAX);
+}
+
+// add the slices' sums of leaves with more than one, in slice order
+__global__ void k_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
+                              const int *nslice, const int *task_off, TreeArrays t,
+                              const double4 *partial, double4 *out4) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int leaf = leaf_of[i], nts = nslice[leaf];
+    if (nts <= 1) return;
+    const int c = leaf_cell[leaf];
+    const int k = (int)(i - t.beg[c]), nb = t.end[c] - t.beg[c], ng = (nb + width - 1) / width;
+    const int g = group_of(nb, ng, k);
+    add_rows(out4 + i, partial + ((int64_t)task_off[leaf] + g) * width + (k - group_begin(nb, ng, g)),
+             (int64_t)ng * width, nts);
+}
+
+// the same for the mixed-precision sums, whose groups are consecutive runs of
+// 64 sinks, numbered before the slices
 __global__ void k_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell,
                              const int *nsrc_tasks, const int *moff, TreeArrays t,
                              const double4 *partial, double4 *out4) {
@@ -354,24 +516,10 @@ __global__ void k_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell
     if (i >= n) return;
     const int leaf = leaf_of[i];
     if (moff[leaf + 1] == moff[leaf]) return;
-    const int c = leaf_cell[leaf];
-    const int k = (int)(i - t.beg[c]);
-    const int sc = k / FMM_WAVE, slot = k % FMM_WAVE, nts = nsrc_tasks[leaf];
-    double4 v = out4[i];
-    const double4 *row = partial + ((int64_t)moff[leaf] + sc * nts) * FMM_WAVE + slot;
-    // eight rows' loads in flight at a time, added in task order
-    for (int t0 = 0; t0 < nts; t0 += 8) {
-        double4 q[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) q[j] = row[(int64_t)min(t0 + j, nts - 1) * FMM_WAVE];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (t0 + j < nts) {
-                v.x += q[j].x; v.y += q[j].y; v.z += q[j].z; v.w += q[j].w;
-            }
-        }
-    }
-    out4[i] = v;
+    const int k = (int)(i - t.beg[leaf_cell[leaf]]), nts = nsrc_tasks[leaf];
+    add_rows(out4 + i,
+             partial + ((int64_t)moff[leaf] + k / FMM_WAVE * nts) * FMM_WAVE + k % FMM_WAVE,
+             FMM_WAVE, nts);
 }
 
 // all-pairs direct sum: one sink per thread, sources in order, read as
@@ -608,26 +756,13 @@ hipError_t launch_p2p_tasks(int nleaves, const int *task_off, int2 *tasks, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_p2p(int want_f, int with_pot, int mixed, int ntasks, const int2 *tasks,
-                      const int *leaf_cell, const int *nsrc_tasks, const int *moff,
-                      const int64_t *off, const int2 *range, const int *chain,
-                      const TreeArrays &t, const double4 *xyzm, double4 *out4, double4 *partial,
-                      hipStream_t s) {
+hipError_t launch_p2p_mixed(int ntasks, const int2 *tasks, const int *leaf_cell,
+                            const int *nsrc_tasks, const int *moff, const int64_t *off,
+                            const int2 *range, const int *chain, const TreeArrays &t,
+                            const double4 *xyzm, double4 *out4, double4 *partial, hipStream_t s) {
     if (ntasks <= 0) return hipSuccess;
-    const dim3 g(blocks(ntasks, 4)), b(256);
-#define FMM_P2P_LAUNCH(F, P, X)                                                                  \
-    hipLaunchKernelGGL((k_p2p<P2P_R, F, P, X>), g, b, 0, s, ntasks, tasks, leaf_cell, nsrc_tasks, \
-                       moff, off, range, chain, t, xyzm, out4, partial)
-    if (mixed) {
-        if (want_f) FMM_P2P_LAUNCH(1, 0, 1);
-        else if (with_pot) FMM_P2P_LAUNCH(0, 1, 1);
-        else FMM_P2P_LAUNCH(0, 0, 1);
-    } else {
-        if (want_f) FMM_P2P_LAUNCH(1, 0, 0);
-        else if (with_pot) FMM_P2P_LAUNCH(0, 1, 0);
-        else FMM_P2P_LAUNCH(0, 0, 0);
-    }
-#undef FMM_P2P_LAUNCH
+    hipLaunchKernelGGL(k_p2p_mixed<P2P_R>, dim3(blocks(ntasks, 4)), dim3(256), 0, s, ntasks, tasks,
+                       leaf_cell, nsrc_tasks, moff, off, range, chain, t, xyzm, out4, partial);
     return hipGetLastError();
 }
 
@@ -636,6 +771,52 @@ hipError_t launch_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell
                              const double4 *partial, double4 *out4, hipStream_t s) {
     hipLaunchKernelGGL(k_p2p_reduce, dim3(blocks(n, 256)), dim3(256), 0, s, n, leaf_of, leaf_cell,
                        nsrc_tasks, moff, t, partial, out4);
+    return hipGetLastError();
+}
+
+hipError_t launch_near_count(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                             const int2 *range, const int *up, const TreeArrays &t,
+                             const uint8_t *active, int *ntask, int *nslice, int *nentry,
+                             int *task_off, int *entry_off, int *tmp, int *totals,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_near_count, dim3(blocks((int64_t)(nleaves + 1) * FMM_WAVE, 256)),
+                       dim3(256), 0, s, nleaves, width, leaf_cell, off, range, up, t, active,
+                       ntask, nslice, nentry);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = exclusive_scan(ntask, task_off, nleaves + 1, tmp, totals, s);
+    if (e != hipSuccess) return e;
+    return exclusive_scan(nentry, entry_off, nleaves + 1, tmp, totals + 1, s);
+}
+
+hipError_t launch_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                            const int2 *range, const int *up, const TreeArrays &t,
+                            const int *nslice, const int *task_off, const int *entry_off,
+                            int4 *tasks, int2 *entry, hipStream_t s) {
+    hipLaunchKernelGGL(k_near_fill, dim3(blocks((int64_t)nleaves * FMM_WAVE, 256)), dim3(256), 0,
+                       s, nleaves, width, leaf_cell, off, range, up, t, nslice, task_off,
+                       entry_off, tasks, entry);
+    return hipGetLastError();
+}
+
+hipError_t launch_near(int want_f, int with_pot, int ntasks, const int4 *tasks, const int2 *entry,
+                       const double4 *xyzm, double4 *out4, double4 *partial, hipStream_t s) {
+    if (ntasks <= 0) return hipSuccess;
+#define FMM_P2P_LAUNCH(F, P)                                                                  \
+    hipLaunchKernelGGL((k_p2p<F, P>), dim3(blocks(ntasks, 4)), dim3(256), 0, s, ntasks, tasks, \
+                       entry, xyzm, out4, partial)
+    if (want_f) FMM_P2P_LAUNCH(1, 0);
+    else if (with_pot) FMM_P2P_LAUNCH(0, 1);
+    else FMM_P2P_LAUNCH(0, 0);
+#undef FMM_P2P_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
+                              const int *nslice, const int *task_off, const TreeArrays &t,
+                              const double4 *partial, double4 *out4, hipStream_t s) {
+    hipLaunchKernelGGL(k_near_reduce, dim3(blocks(n, 256)), dim3(256), 0, s, n, width, leaf_of,
+                       leaf_cell, nslice, task_off, t, partial, out4);
     return hipGetLastError();
 }
 

@@ -730,16 +730,6 @@ constexpr int DPP_HALF_MIRROR = 0x141;
 constexpr int DPP_MIRROR = 0x140;
 
 template <int CTRL>
-__device__ __forceinline__ int dpp_int(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_double(double v) {
-    return __hiloint2double(dpp_int<CTRL>(__double2hiint(v)), dpp_int<CTRL>(__double2loint(v)));
-}
-
-template <int CTRL>
 __device__ __forceinline__ void argmax_step(double &e, int &j) {
     const double oe = dpp_double<CTRL>(e);
     const int oj = dpp_int<CTRL>(j);
