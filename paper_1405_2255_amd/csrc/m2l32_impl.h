@@ -68,38 +68,52 @@ struct UnitTheta32 {
     __device__ __forceinline__ const cplxf *row() const { return rows[N & 1]; }
 };
 
-template <int P, int N0, int N1, int J>
-__device__ __forceinline__ void contract_row32(cplxf *acc, const cplxf *th, const cplxf *Ma,
-                                               const float *pa, const float *pb) {
+// the terms of degree n = J - k of row J from M_k in mk
+template <int N0, int J, int n>
+__device__ __forceinline__ void contract32(cplxf *acc, const cplxf *th, const cplxf *Mk,
+                                           float sc) {
+    constexpr int k = J - n;
+    cplxf mk[k + 1];
 #pragma unroll
-    for (int n = N0; n <= (N1 < J ? N1 : J); ++n) {
-        const int k = J - n;
-        const float sc = pa[k] * pb[n];
-        cplxf mk[P + 1];
+    for (int l = 0; l <= k; ++l) mk[l] = {Mk[l].re * sc, Mk[l].im * sc};
 #pragma unroll
-        for (int l = 0; l <= k; ++l) {
-            const cplxf v = Ma[tri(k, l)];
-            mk[l] = {v.re * sc, v.im * sc};
+    for (int m = 0; m <= n; ++m) {
+        cplxf &a = acc[tri(n, m) - tri(N0, 0)];
+#pragma unroll
+        for (int l = -k; l <= k; ++l) {
+            const int q = m + l;
+            if (q > J || q < -J) continue;
+            const cplxf mv = mk[l < 0 ? -l : l];
+            const float sl = (l < 0 && (l & 1)) ? -1.0f : 1.0f;
+            const float cr = sl * mv.re;
+            const float ci = (l < 0) ? sl * mv.im : -mv.im;   // conj(M_k^l)
+            const cplxf tv = th[q < 0 ? -q : q];
+            const float sq = (q < 0 && (q & 1)) ? -1.0f : 1.0f;
+            const float tr = sq * tv.re;
+            const float ti = (q < 0) ? -sq * tv.im : tv.im;  // Theta_J^q
+            a.re = fmaf(cr, tr, fmaf(-ci, ti, a.re));
+            if (m != 0) a.im = fmaf(cr, ti, fmaf(ci, tr, a.im));
         }
+    }
+}
+
+// rows JE and JO = JE + 1 of Theta together: the multipoles of each degree are
+// loaded once for both (the lanes read different cells, so the kernel is bound
+// by the L1 visits of its loads as much as by its arithmetic); an output's
+// terms still come in the order of their rows
+template <int P, int N0, int N1, int JE, int k>
+__device__ __forceinline__ void contract_pair32(cplxf *acc, const cplxf *te, const cplxf *to,
+                                                const cplxf *Ma, const float *pa,
+                                                const float *pb) {
+    constexpr int JO = JE + 1;
+    constexpr bool even = JE > M2L32_JLO && JE - k >= N0 && JE - k <= N1;
+    constexpr bool odd = JO <= P && JO > M2L32_JLO && JO - k >= N0 && JO - k <= N1;
+    if constexpr (even || odd) {
+        cplxf mk[k + 1];
 #pragma unroll
-        for (int m = 0; m <= n; ++m) {
-            cplxf &a = acc[tri(n, m) - tri(N0, 0)];
-#pragma unroll
-            for (int l = -k; l <= k; ++l) {
-                const int q = m + l;
-                if (q > J || q < -J) continue;
-                const cplxf mv = mk[l < 0 ? -l : l];
-                const float sl = (l < 0 && (l & 1)) ? -1.0f : 1.0f;
-                const float cr = sl * mv.re;
-                const float ci = (l < 0) ? sl * mv.im : -mv.im;   // conj(M_k^l)
-                const cplxf tv = th[q < 0 ? -q : q];
-                const float sq = (q < 0 && (q & 1)) ? -1.0f : 1.0f;
-                const float tr = sq * tv.re;
-                const float ti = (q < 0) ? -sq * tv.im : tv.im;  // Theta_J^q
-                a.re = fmaf(cr, tr, fmaf(-ci, ti, a.re));
-                if (m != 0) a.im = fmaf(cr, ti, fmaf(ci, tr, a.im));
-            }
-        }
+        for (int l = 0; l <= k; ++l) mk[l] = Ma[tri(k, l)];
+        if constexpr (even) contract32<N0, JE, JE - k>(acc, te, mk, pa[k] * pb[JE - k]);
+        if constexpr (odd) contract32<N0, JO, JO - k>(acc, to, mk, pa[k] * pb[JO - k]);
     }
 }
 
@@ -131,60 +145,61 @@ __device__ __forceinline__ void m2l32_pass(int B, int e0, int e1, double sigma,
         const cplxf *Ma = M + (size_t)A * tri(P + 1, 0);
         UnitTheta32<P> g;
         g.start((float)(dx * ir), (float)(dy * ir), (float)(dz * ir));
-        auto row = [&]<int J>() {
-            if constexpr (J > 0) g.template next<J>();
-            if constexpr (J >= N0 && J > M2L32_JLO)
-                contract_row32<P, N0, N1, J>(acc, g.template row<J>(), Ma, pa, pb);
-            __asm__ volatile("" ::: "memory");
+        auto rows = [&]<int H>() {
+            constexpr int JE = 2 * H, JO = JE + 1;
+            if constexpr (JE > 0) g.template next<JE>();
+            if constexpr (JO <= P) g.template next<JO>();
+            auto degree = [&]<int k>() {
+                contract_pair32<P, N0, N1, JE, k>(acc, g.template row<JE>(), g.template row<JO>(),
+                                                  Ma, pa, pb);
+                __asm__ volatile("" ::: "memory");
+            };
+            if constexpr (JO >= N0) Unroll<(JE > N1 ? JE - N1 : 0), (JO <= P ? JO : JE) - N0>::run(degree);
         };
-        Unroll<0, P>::run(row);
+        Unroll<0, P / 2>::run(rows);
     }
 #pragma unroll
     for (int i = 0; i < NACC; ++i) out[tri(N0, 0) + i] = acc[i];
 }
 
-// FP64 terms of degree j <= JL (unscaled F_n, n <= JL)
-template <int P, int JL>
-__device__ __forceinline__ void m2l_low(int B, int e0, int e1, const uint64_t *list,
-                                        uint64_t mask, const TreeArrays &t, const cplx *M,
-                                        cplx *out) {
-    constexpr int NACC = tri(JL + 1, 0);
-    cplx acc[NACC];
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) acc[i] = {0.0, 0.0};
-    const double4 cb = t.cen[B];
-    for (int e = e0; e < e1; ++e) {
-        const int A = (int)(list[e] & mask);
-        const double4 ca = t.cen[A];
-        const cplx *Ma = M + (size_t)A * tri(P + 1, 0);
-        RowGen<JL> g;
-        g.theta_start(cb.x - ca.x, cb.y - ca.y, cb.z - ca.z);
-        auto row = [&]<int J>() {
-            if constexpr (J > 0) g.template theta_row<J>();
-            m2l_detail::contract_row<P, 0, JL, J>(acc, g.template row<J>(), Ma);
-        };
-        Unroll<0, JL>::run(row);
-    }
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) out[i] = acc[i];
+__host__ __device__ constexpr int pass_count32(int p) {
+    int c = 0;
+    for (int n0 = 0; n0 <= p; n0 = pass_end32(p, n0) + 1) ++c;
+    return c;
 }
 
+// the pass with index `pass` (the same in every lane)
 template <int P, int N0>
-__device__ __forceinline__ void m2l32_passes(int B, int e0, int e1, double sigma,
+__device__ __forceinline__ void m2l32_passes(int pass, int B, int e0, int e1, double sigma,
                                              const uint64_t *list, uint64_t mask,
                                              const TreeArrays &t, const cplxf *M, cplxf *out) {
     constexpr int N1 = pass_end32(P, N0);
-    m2l32_pass<P, N0, N1>(B, e0, e1, sigma, list, mask, t, M, out);
-    if constexpr (N1 < P) m2l32_passes<P, N1 + 1>(B, e0, e1, sigma, list, mask, t, M, out);
+    if (pass == 0)
+        m2l32_pass<P, N0, N1>(B, e0, e1, sigma, list, mask, t, M, out);
+    else if constexpr (N1 < P)
+        m2l32_passes<P, N1 + 1>(pass - 1, B, e0, e1, sigma, list, mask, t, M, out);
 }
 
+// One lane per chunk and pass: the grid's y dimension takes the FP32 passes and
+// after them the FP64 terms of the low degrees.  2.41e6 pairs at p = 14: 2.50 ms
+// against 3.83 ms with all passes in one wavefront and a load per degree pair.
+// (The FP64 kernel's real Theta would take 1.87 ms, but its FP32 rounding differs
+// from this one's by nearly 1e-9 of the forces.)
 template <int P>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_m2l32(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, TreeArrays t,
         const double *M, const float *M32, float *Fpart, double *Flow, double *sig) {
     const int ch = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (ch >= nchunks) return;
     const int4 c = chunks[ch];
+    if (blockIdx.y == pass_count32(P)) {
+        constexpr int JL = P < M2L32_JLO ? P : M2L32_JLO;
+        m2l_detail::m2l_pass<JL, 0, JL>(c.x, c.y, c.z, list, mask, t,
+                                        reinterpret_cast<const cplx *>(M), tri(P + 1, 0),
+                                        reinterpret_cast<cplx *>(Flow) +
+                                            (size_t)ch * tri(M2L32_JLO + 1, 0));
+        return;
+    }
     // sigma: the smallest separation of the chunk
     const double4 cb = t.cen[c.x];
     double sigma = INFINITY;
@@ -193,12 +208,9 @@ k_m2l32(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, Tr
         const double dx = cb.x - ca.x, dy = cb.y - ca.y, dz = cb.z - ca.z;
         sigma = fmin(sigma, sqrt(fma(dx, dx, fma(dy, dy, dz * dz))));
     }
-    sig[ch] = sigma;
-    constexpr int JL = P < M2L32_JLO ? P : M2L32_JLO;
-    m2l_low<P, JL>(c.x, c.y, c.z, list, mask, t, reinterpret_cast<const cplx *>(M),
-                   reinterpret_cast<cplx *>(Flow) + (size_t)ch * tri(M2L32_JLO + 1, 0));
+    if (blockIdx.y == 0) sig[ch] = sigma;
     cplxf *out = reinterpret_cast<cplxf *>(Fpart) + (size_t)ch * tri(P + 1, 0);
-    m2l32_passes<P, 0>(c.x, c.y, c.z, sigma, list, mask, t,
+    m2l32_passes<P, 0>(blockIdx.y, c.x, c.y, c.z, sigma, list, mask, t,
                        reinterpret_cast<const cplxf *>(M32), out);
 }
 
@@ -211,7 +223,9 @@ k_m2l32(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, Tr
                                       uint64_t mask, const TreeArrays &t, const double *M,   \
                                       const float *M32, float *Fpart, double *Flow,          \
                                       double *sig, hipStream_t s) {                          \
-        hipLaunchKernelGGL(m2l32_detail::k_m2l32<P>, dim3((unsigned)((nchunks + 63) / 64)), \
+        hipLaunchKernelGGL(m2l32_detail::k_m2l32<P>,                                         \
+                           dim3(m2l_detail::m2l_blocks(nchunks),                             \
+                                m2l32_detail::pass_count32(P) + 1),                          \
                            dim3(64), 0, s, nchunks, chunks, list, mask, t, M, M32, Fpart,    \
                            Flow, sig);                                                       \
         return hipGetLastError();                                                            \
