@@ -1318,7 +1318,10 @@ fmm_status fmm_direct(fmm_ctx *c, int64_t n, const double *pos, const double *ma
         return fmm::fail(c, FMM_E_INVAL, "bad argument");
     if (n == 0) return FMM_OK;
     return fmm::guarded(c, [&]() -> fmm_status {
-        CK(fmm::launch_direct(n, pos, mass, G, pot, acc, c->stream));
+        const int nchunk = fmm::direct_sinks_chunks(n, n);
+        double4 *part = nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * n) : nullptr;
+        CK(fmm::launch_direct_sinks(n, pos, mass, G, n, nullptr, nchunk, pot, acc, part, nullptr,
+                                    c->stream));
         fmm::sync(c);
         return FMM_OK;
     });
@@ -1445,8 +1448,11 @@ fmm_status fmm_direct_jerk_sinks(fmm_ctx *c, int64_t n, const double *pos, const
     return fmm::guarded(c, [&]() -> fmm_status {
         int *bad = fmm::ensure<int>(c->nonfinite, 8) + 5;
         CK(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
-        CK(fmm::launch_direct_jerk_sinks(n, pos, vel, mass, G, nsinks, sinks, jerk, bad,
-                                         c->stream));
+        const int nchunk = fmm::direct_sinks_chunks(n, nsinks);
+        double4 *part =
+            nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * nsinks) : nullptr;
+        CK(fmm::launch_direct_jerk_sinks(n, pos, vel, mass, G, nsinks, sinks, nchunk, jerk, part,
+                                         bad, c->stream));
         CK(hipMemcpyAsync(c->hint, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
         fmm::sync(c);
         if (c->hint[0]) return fmm::fail(c, FMM_E_INVAL, "sink index out of range");

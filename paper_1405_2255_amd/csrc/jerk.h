@@ -33,10 +33,12 @@ hipError_t launch_p2p_jerk(int ntasks, const int4 *tasks, const int2 *entry,
                            const double4 *xyzm, const double4 *v4, double4 *out4, double4 *jo4,
                            double4 *partial, double4 *jpartial, hipStream_t s);
 // exact jerk of listed sinks (input indices) against all n sources, written in
-// list order; *bad (zeroed by the caller) = 1 for an index outside [0, n)
+// list order; nchunk and part as for launch_direct_sinks; *bad (zeroed by the
+// caller) = 1 for an index outside [0, n)
 hipError_t launch_direct_jerk_sinks(int64_t n, const double *pos, const double *vel,
                                    const double *mass, double G, int64_t nsinks,
-                                   const int64_t *sinks, double *jerk, int *bad, hipStream_t s);
+                                   const int64_t *sinks, int nchunk, double *jerk, double4 *part,
+                                   int *bad, hipStream_t s);
 // listed sinks (input indices act[j], inverse permutation inv): jerk in list order
 hipError_t launch_output_jerk_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
                                      const double4 *jo4, double G, double *jerk, int *nonfinite,

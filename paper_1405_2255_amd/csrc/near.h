@@ -180,4 +180,63 @@ __device__ __forceinline__ int wave_sum4_component() {
     return ((row & 1) << 1) | (row >> 1);
 }
 
+// ---- exact sums over all sources (a slice [j0, j1) per wavefront) -------------
+// Sinks of one wavefront: DIRECT_R of them, entries t0.. of the sink list (or
+// particles t0.. where the list is null), repeated past the end.  pos[k]: their
+// particle indices (scalar registers); *bad is set for an index outside [0, n),
+// whose sums are not written.
+struct DirectSinks {
+    int64_t t0;
+    int64_t idx[DIRECT_R];
+    unsigned valid;          // bit k: entry t0 + k exists and is in range
+};
+__device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
+    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, l);
+    const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
+}
+__device__ __forceinline__ DirectSinks direct_sinks(int64_t wave, int64_t n, int64_t nsinks,
+                                                    const int64_t *sinks, int *bad) {
+    DirectSinks d;
+    d.t0 = wave * DIRECT_R;
+    const int k = lane_id() & (DIRECT_R - 1);
+    const int64_t t = d.t0 + k;
+    int64_t i = t < nsinks ? (sinks ? sinks[t] : t) : 0;
+    const bool ok = t < nsinks && i >= 0 && i < n;
+    if (bad && t < nsinks && !ok) atomicOr(bad, 1);
+    if (!ok) i = 0;
+    d.valid = (unsigned)(__ballot(ok) & ((1u << DIRECT_R) - 1u));
+#pragma unroll
+    for (int q = 0; q < DIRECT_R; ++q) d.idx[q] = readlane64(i, q);
+    return d;
+}
+
+// The sources [j0, j1), 64 per step: fast(o) where no sink is among them,
+// checked(o, on) elsewhere; o = source - j0 of this lane, on: it exists.
+template <class Fast, class Checked>
+__device__ __forceinline__ void direct_steps(const DirectSinks &d, int64_t j0, int64_t j1,
+                                             Fast &&fast, Checked &&checked) {
+    const uint32_t lane = lane_id();
+    const uint32_t len = (uint32_t)(j1 - j0);        // chunks hold at most 2^31 sources
+    uint32_t o = 0;
+    while (o < len) {
+        // the first sink from here on, if any
+        uint32_t next = UINT_MAX;
+#pragma unroll
+        for (int q = 0; q < DIRECT_R; ++q) {
+            const int64_t r = d.idx[q] - j0;
+            if (r >= (int64_t)o && r < (int64_t)len) next = min(next, (uint32_t)r);
+        }
+        const uint32_t stop = min(len, next);
+        while (o + FMM_WAVE <= stop) {
+            fast(o + lane);
+            o += FMM_WAVE;
+        }
+        if (o < len) {
+            checked(o + lane, o + lane < len);
+            o += FMM_WAVE;
+        }
+    }
+}
+
 }  // namespace fmm

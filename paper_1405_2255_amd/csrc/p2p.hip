@@ -46,12 +46,6 @@ __device__ __forceinline__ int first_with_ranges(int c, const int *up, const int
     return off[c + 1] > off[c] ? c : up[c];
 }
 
-__device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
-    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, l);
-    const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-}
-
 // Work of one sink leaf: the number of source particles in its direct-sum
 // ranges and those of its ancestors (one concatenated list); every lane of
 // the wavefront ends with it.  Lanes take the range entries in turn.
@@ -522,84 +516,81 @@ __global__ void k_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell
              FMM_WAVE, nts);
 }
 
-// all-pairs direct sum: one sink per thread, sources in order, read as
-// wavefront-uniform values
-__global__ void __launch_bounds__(256)
-k_direct(int64_t n, const double *pos, const double *mass, double G, double *pot, double *acc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool active = i < n;
-    const int64_t ii = active ? i : 0;
-    const double xb = pos[3 * ii], yb = pos[3 * ii + 1], zb = pos[3 * ii + 2];
-    double p = 0.0, ax = 0.0, ay = 0.0, az = 0.0;
-    for (int64_t j = 0; j < n; ++j) {
-        const double dx = pos[3 * j] - xb, dy = pos[3 * j + 1] - yb, dz = pos[3 * j + 2] - zb;
-        const bool self = j == ii;
-        const double r2 = self ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
-        const double mu = self ? 0.0 : mass[j];
-        const double ri = rsqrt_nr(r2);
-        const double q = mu * ri, q3 = q * ri * ri;
-        p += q;
-        ax = fma(q3, dx, ax);
-        ay = fma(q3, dy, ay);
-        az = fma(q3, dz, az);
-    }
-    if (!active) return;
-    pot[i] = -G * p;
-    acc[3 * i] = G * ax;
-    acc[3 * i + 1] = G * ay;
-    acc[3 * i + 2] = G * az;
-}
-
-// The same sum for listed sinks, with the sources split over the grid's y
-// dimension: block (x, k) takes sinks [256 x, 256 x + 256) against sources
-// [k chunk, min(n, (k + 1) chunk)), one sink per thread, the sources read as
-// wavefront-uniform values.  A few thousand sinks thus still fill the chip.
-// With one chunk the block writes the results; otherwise it writes row k of
-// part (nsinks double4 per row: Psi, a without G) and k_direct_sinks_reduce
-// adds the rows of each sink in chunk order, so the result does not depend on
-// the order in which blocks run.  An index outside [0, n) sets *bad (by the
-// blocks of chunk 0) and its outputs are not written.
-__global__ void __launch_bounds__(256)
+// Exact sums of listed sinks (sinks null: of every particle).  A wavefront
+// takes DIRECT_R sinks in scalar registers against the sources of its grid row,
+// [k chunk, min(n, (k + 1) chunk)), one per lane (near.h), so that a few
+// thousand sinks still fill the chip.  With one chunk it writes the results;
+// otherwise it writes row k of part (nsinks double4 per row: Psi, a without G)
+// and k_direct_sinks_reduce adds the rows of each sink in chunk order, so the
+// result does not depend on the order in which blocks run.  An index outside
+// [0, n) sets *bad (by the blocks of chunk 0) and its outputs are not written.
+// Bound by VALU issue like the near field: 4096 sinks of 10^6 in 2.4 ms (1.7e12
+// pairs/s), all of 30,000 in 0.57 ms.  A sink per lane, with the sources read as
+// scalars and a self test per pair (25 issue slots), took 5.5 ms and, on 118 of
+// the 256 compute units, 5.3 ms.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_direct_sinks(int64_t n, const double *pos, const double *mass, double G, int64_t nsinks,
                const int64_t *sinks, int64_t chunk, double *pot, double *acc, double4 *part,
                int *bad) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
-    int64_t ii = t < nsinks ? sinks[t] : 0;
-    const bool valid = t < nsinks && ii >= 0 && ii < n;
-    if (k == 0 && t < nsinks && !valid) atomicOr(bad, 1);
-    if (!valid) ii = 0;
-    const double xb = pos[3 * ii], yb = pos[3 * ii + 1], zb = pos[3 * ii + 2];
+    const int64_t wave = (int64_t)blockIdx.x * 4 + threadIdx.x / FMM_WAVE;
+    if (wave * DIRECT_R >= nsinks) return;       // whole wavefronts leave together
+    const int k = blockIdx.y, lane = lane_id();
+    const DirectSinks d = direct_sinks(wave, n, nsinks, sinks, k == 0 ? bad : nullptr);
+    double sx[DIRECT_R], sy[DIRECT_R], sz[DIRECT_R], f[DIRECT_R][4];
+#pragma unroll
+    for (int q = 0; q < DIRECT_R; ++q) {
+        const double *x = pos + 3 * d.idx[q];
+        sx[q] = readlane_f64(x[0], 0);
+        sy[q] = readlane_f64(x[1], 0);
+        sz[q] = readlane_f64(x[2], 0);
+        f[q][0] = f[q][1] = f[q][2] = f[q][3] = 0.0;
+    }
     const int64_t j0 = (int64_t)k * chunk, j1 = min(n, j0 + chunk);
-    double p = 0.0, ax = 0.0, ay = 0.0, az = 0.0;
-    for (int64_t j = j0; j < j1; ++j) {
-        const double dx = pos[3 * j] - xb, dy = pos[3 * j + 1] - yb, dz = pos[3 * j + 2] - zb;
-        const bool self = j == ii;
-        const double r2 = self ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
-        const double mu = self ? 0.0 : mass[j];
-        const double ri = rsqrt_nr(r2);
-        const double q = mu * ri, q3 = q * ri * ri;
-        p += q;
-        ax = fma(q3, dx, ax);
-        ay = fma(q3, dy, ay);
-        az = fma(q3, dz, az);
+    const double *px = pos + 3 * j0, *pm = mass + j0;
+    auto source = [&](uint32_t o) {
+        const size_t i = 3 * (size_t)o;
+        return make_double4(px[i], px[i + 1], px[i + 2], pm[o]);
+    };
+    direct_steps(
+        d, j0, j1,
+        [&](uint32_t o) {
+            const double4 a = source(o);
+#pragma unroll
+            for (int q = 0; q < DIRECT_R; ++q) {
+                pair<0, 1>(a, sx[q], sy[q], sz[q], false, f[q][0], f[q][1], f[q][2], f[q][3]);
+                if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        },
+        [&](uint32_t o, bool on) {
+            double4 a = make_double4(0.0, 0.0, 0.0, 0.0);
+            if (on) a = source(o);
+#pragma unroll
+            for (int q = 0; q < DIRECT_R; ++q) {
+                pair<0, 1>(a, sx[q], sy[q], sz[q], !on || j0 + o == d.idx[q], f[q][0], f[q][1],
+                           f[q][2], f[q][3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < DIRECT_R; ++q) {
+        const double w = wave_sum4(f[q][0], f[q][1], f[q][2], f[q][3]);
+        v = (lane & 15) == q ? w : v;
     }
-    if (!valid) return;
-    if (part) {
-        part[(int64_t)k * nsinks + t] = make_double4(p, ax, ay, az);
-        return;
-    }
-    pot[t] = -G * p;
-    acc[3 * t] = G * ax;
-    acc[3 * t + 1] = G * ay;
-    acc[3 * t + 2] = G * az;
+    const int comp = wave_sum4_component(), s = lane & 15;
+    if (s >= DIRECT_R || !((d.valid >> s) & 1u)) return;
+    v *= comp == 0 ? P2P_POT_BACK : P2P_ACC_BACK;
+    const int64_t t = d.t0 + s;
+    if (part) reinterpret_cast<double *>(part + (int64_t)k * nsinks + t)[comp] = v;
+    else if (comp == 0) pot[t] = -G * v;
+    else acc[3 * t + comp - 1] = G * v;
 }
 
 __global__ void k_direct_sinks_reduce(int64_t n, double G, int64_t nsinks, const int64_t *sinks,
                                       int nchunk, const double4 *part, double *pot, double *acc) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nsinks) return;
-    const int64_t ii = sinks[t];
+    const int64_t ii = sinks ? sinks[t] : t;
     if (ii < 0 || ii >= n) return;
     double4 v = part[t];
     for (int k = 1; k < nchunk; ++k) {
@@ -879,10 +870,9 @@ hipError_t launch_scale(int want_f, int64_t n, const double4 *est4, double *scal
 }
 
 int direct_sinks_chunks(int64_t n, int64_t nsinks) {
-    // about DIRECT_SINKS_BLOCKS blocks, at least 2048 sources per chunk
-    const int64_t sb = (nsinks + 255) / 256;
-    const int64_t want = (DIRECT_SINKS_BLOCKS + sb - 1) / sb;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(want, n / 2048));
+    const int64_t waves = (nsinks + DIRECT_R - 1) / DIRECT_R;
+    const int64_t want = (DIRECT_WAVES + waves - 1) / waves;
+    return (int)std::max<int64_t>(n / (1ll << 31) + 1, std::min<int64_t>(want, n / DIRECT_SOURCES));
 }
 
 hipError_t launch_direct_sinks(int64_t n, const double *pos, const double *mass, double G,
@@ -891,8 +881,8 @@ hipError_t launch_direct_sinks(int64_t n, const double *pos, const double *mass,
     if (nsinks <= 0) return hipSuccess;
     if (nchunk < 1 || (nchunk > 1 && !part)) return hipErrorInvalidValue;
     const int64_t chunk = (n + nchunk - 1) / nchunk;
-    hipLaunchKernelGGL(k_direct_sinks, dim3(blocks(nsinks, 256), (unsigned)nchunk), dim3(256), 0,
-                       s, n, pos, mass, G, nsinks, sinks, chunk, pot, acc,
+    hipLaunchKernelGGL(k_direct_sinks, dim3(blocks(nsinks, 4 * DIRECT_R), (unsigned)nchunk),
+                       dim3(256), 0, s, n, pos, mass, G, nsinks, sinks, chunk, pot, acc,
                        nchunk > 1 ? part : nullptr, bad);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nchunk == 1) return e;
@@ -904,12 +894,6 @@ hipError_t launch_direct_sinks(int64_t n, const double *pos, const double *mass,
 hipError_t launch_fill_int(int *p, int64_t count, int v, hipStream_t s) {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_int, dim3(blocks(count, 256)), dim3(256), 0, s, p, count, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_direct(int64_t n, const double *pos, const double *mass, double G,
-                         double *pot, double *acc, hipStream_t s) {
-    hipLaunchKernelGGL(k_direct, dim3(blocks(n, 256)), dim3(256), 0, s, n, pos, mass, G, pot, acc);
     return hipGetLastError();
 }
 

@@ -64,3 +64,26 @@ def test_lists_of_many_short_ranges(gpu_lib, n, leaf):
     assert np.max(np.linalg.norm(acc.cpu().numpy() - ref["acc"], axis=1) /
                   np.linalg.norm(ref["acc"], axis=1)) < 1e-10
     assert np.max(np.abs(pot.cpu().numpy() - ref["pot"]) / np.abs(ref["pot"])) < 1e-10
+
+
+@pytest.mark.parametrize("n", [2, 7, 8, 9, 63, 64, 65, 513, 1023, 1024, 1025, 2049, 5000])
+def test_exact_sums(gpu_lib, n):
+    # 8 sinks per wavefront, 64 sources per step, chunks of at least 512 sources;
+    # the list unsorted and with repeats, its ends at the ends of chunks
+    pos, m = workloads.cluster("uniform", n, 400 + n, masses="salpeter")
+    vel = np.random.default_rng(n).standard_normal(pos.shape)
+    P, V, M = _dev(pos), _dev(vel), _dev(m)
+    ctx = gpu_lib.Context()
+    p0, a0, f0 = oracle.direct(pos, m)
+    pot, acc = ctx.direct(P, M, 1.0)
+    assert np.max(np.abs(pot.cpu().numpy() - p0) / np.abs(p0)) < 1e-12
+    assert np.max(np.linalg.norm(acc.cpu().numpy() - a0, axis=1) / f0) < 1e-12
+    rng = np.random.default_rng(n + 1)
+    for k in (1, 5, 11):
+        s = np.concatenate([rng.integers(0, n, k), [n - 1, 0, n // 2, n - 1]]).astype(np.int64)
+        pot, acc = ctx.direct_sinks(P, M, _dev(s), 1.0)
+        assert np.max(np.abs(pot.cpu().numpy() - p0[s]) / np.abs(p0[s])) < 1e-12
+        assert np.max(np.linalg.norm(acc.cpu().numpy() - a0[s], axis=1) / f0[s]) < 1e-12
+        jerk = ctx.direct_jerk_sinks(P, V, M, _dev(s), 1.0).cpu().numpy()
+        j0 = oracle.direct_jerk(pos, vel, m, sinks=s)
+        assert np.max(np.linalg.norm(jerk - j0, axis=1) / np.linalg.norm(j0, axis=1)) < 1e-10
