@@ -108,9 +108,8 @@ hipError_t launch_norm3(const double *acc, int64_t n, double G, double *out, hip
 
 using namespace fmm;
 
-// entries of the pinned host mirror of the walk counters: 4 totals plus one
-// frontier size per sweep (at most 2 * FMM_MAXLEVEL + 4 sweeps)
-constexpr int HCNT = 128;
+// entries of the pinned host mirror of the walk counters
+constexpr int HCNT = WALK_COUNTERS;
 
 struct fmm_ctx {
     fmm_opts opts{};
@@ -165,7 +164,7 @@ struct fmm_ctx {
     int64_t n = 0;
     int ncells = 0, nleaves = 0, depth = 0, sh = 0, pb = 0, p = 0;
     int pack = 0;   // direct-sum keys carry the range end (sh + 2 pb <= 64)
-    int walk_used[3] = {0, 0, 0};   // sweeps the last walk of each mode needed
+    std::vector<int64_t> walk_front[3];   // frontier sizes of the last walk of each mode
     int64_t n_m2l = 0, n_p2p = 0, n_ranges = 0;
     uint64_t *m2l_sorted = nullptr, *p2p_sorted = nullptr;
     uint32_t *p2pe_sorted = nullptr;
@@ -367,8 +366,9 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
     const int *leaf_of = ptr<int>(c->leaf_of), *leaf_cell = ptr<int>(c->leaf_cell);
     // geometry bottom up, then the radii about the midpoints and the centres
     // of mass of every cell in one pass
-    for (int L = c->depth; L >= 0; --L)
-        CK(launch_geometry_level(t, c->ls[L], c->ls[L + 1], x, y, z, m, s));
+    LevelStart levels{};
+    for (int L = 0; L <= c->depth + 1; ++L) levels.first[L] = c->ls[L];
+    CK(launch_geometry(t, levels, c->depth, c->nleaves, leaf_cell, x, y, z, m, s));
     CK(launch_radii(t, n, leaf_of, leaf_cell, c->depth, x, y, z, false, s));
     CK(launch_radii_finish(t, ncells, s));
     if (c->opts.centre != FMM_CENTRE_MIDPOINT) {
@@ -379,8 +379,7 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
         // before anything reads an expansion centre.
         CK(hipEventRecord(c->ev_fork, s));
         CK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        for (int L = c->depth; L >= 0; --L)
-            CK(launch_enclosing_level(t, c->ls[L], c->ls[L + 1], x, y, z, c->side));
+        CK(launch_enclosing(t, levels, c->depth, c->nleaves, leaf_cell, x, y, z, c->side));
         CK(launch_radii(t, n, leaf_of, leaf_cell, c->depth, x, y, z, true, c->side));
         CK(launch_centre_select(t, ncells, c->side));
         CK(hipEventRecord(c->ev_join, c->side));
@@ -408,7 +407,6 @@ struct Lists {
 };
 
 Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
-    static_assert(4 + 2 * FMM_MAXLEVEL + 4 <= HCNT, "counter mirror too small for the deepest tree");
     hipStream_t s = c->stream;
     WalkParams wp = wp0;
     wp.nroots = c->nroots;
@@ -424,7 +422,7 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
     int64_t cap_f = std::max<int64_t>({1024, 2 * n, (int64_t)c->nroots, (int64_t)(c->fa.cap / 8)});
     int64_t cap_m = std::max<int64_t>(1024, c->m2l.cap ? (int64_t)(c->m2l.cap / 8) : 8 * n);
     int64_t cap_p = std::max<int64_t>(1024, c->p2p.cap ? (int64_t)(c->p2p.cap / 8) : 4 * n);
-    unsigned long long *cnt = ensure<unsigned long long>(c->counters, WALK_CUM + 3 * (sweeps + 1));
+    unsigned long long *cnt = ensure<unsigned long long>(c->counters, WALK_COUNTERS);
     unsigned long long *btmp = ensure<unsigned long long>(c->walktmp, walk_tmp_u64());
     const TreeArrays t = tree_arrays(c);
     for (;;) {
@@ -432,32 +430,41 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
         uint64_t *ml = ensure<uint64_t>(c->m2l, cap_m), *pl = ensure<uint64_t>(c->p2p, cap_p);
         uint32_t *pe = ensure<uint32_t>(c->p2pe, cap_p);
         uint16_t *code = ensure<uint16_t>(c->wcode, cap_f);
-        CK(hipMemsetAsync(cnt, 0, (WALK_CUM + 3 * (sweeps + 1)) * sizeof(unsigned long long), s));
+        CK(hipMemsetAsync(cnt, 0, WALK_COUNTERS * sizeof(unsigned long long), s));
         CK(launch_root_pairs(fa, c->nroots, s));           // (r, r) for every root
         if (c->opts.timing) CK(hipEventRecord(c->ev_walk[0], s));
-        // as many sweeps as the last walk of this kind needed (plus one), more
-        // only while the frontier is not empty; at most `sweeps`
-        int target = c->walk_used[wp.mode] > 0 ? std::min(sweeps, c->walk_used[wp.mode] + 1)
-                                               : sweeps;
-        int launched = 0;
+        const WalkBuffers wb{{fa, fb}, cap_f, ml, cap_m, pl, pe, cap_p, cnt, code};
+        // Launches for the frontier sizes of the last walk of this kind: a run of
+        // small frontiers is one launch, and one more ends the list, for the
+        // sweeps that come out differently.  Without a last walk, or while pairs
+        // are left, a few sweeps at a time.
+        std::vector<char> plan;
+        const std::vector<int64_t> &last = c->walk_front[wp.mode];
+        for (size_t i = 0; i < last.size(); ++i) {
+            const bool small = last[i] <= WALK_SMALL - WALK_SMALL / 8;
+            if (!small || plan.empty() || !plan.back()) plan.push_back(small);
+        }
+        if (last.empty()) plan.assign({1, 0, 0, 0, 0, 0, 0, 0, 0});
+        if (!plan.back()) plan.push_back(1);
+        int launched = 0, cur = 0;
         for (;;) {
-            for (int i = launched; i < target; ++i) {
-                WalkBuffers wb{(i & 1) ? fb : fa, (i & 1) ? fa : fb, cap_f, ml, cap_m, pl, pe,
-                               cap_p, cnt, code};
-                CK(launch_walk(wp, t, P, wb, i, btmp, s));
-            }
-            launched = target;
+            if (launched + (int)plan.size() > WALK_LAUNCHES)
+                throw HipFail{hipErrorUnknown, "walk did not terminate"};
+            for (char small : plan) CK(launch_walk(wp, t, P, wb, launched++, small != 0, btmp, s));
             if (c->opts.timing) CK(hipEventRecord(c->ev_walk[1], s));
-            CK(hipMemcpyAsync(c->hcnt, cnt, (4 + sweeps) * sizeof(unsigned long long),
+            CK(hipMemcpyAsync(c->hcnt, cnt, (WALK_CUR + launched + 1) * sizeof(unsigned long long),
                               hipMemcpyDeviceToHost, s));
             sync(c);
-            if (c->hcnt[4 + launched - 1] == 0 || launched >= sweeps) break;
-            target = std::min(sweeps, launched + 4);
+            cur = (int)c->hcnt[WALK_CUR + launched];
+            if (c->hcnt[3] || cur >= sweeps || (cur > 0 && c->hcnt[4 + cur - 1] == 0)) break;
+            // a frontier past its buffer: nothing more can run
+            if (cur > 0 && (int64_t)c->hcnt[4 + cur - 1] > cap_f) break;
+            plan.assign({0, 0, 0, 0, 0, 0, 1});
         }
         const unsigned long long *h = c->hcnt;
         int64_t maxf = 0, visited = 1;
         int used = 0;
-        for (int i = 0; i < sweeps; ++i) {
+        for (int i = 0; i < std::min(sweeps, WALK_SWEEPS); ++i) {
             maxf = std::max<int64_t>(maxf, (int64_t)h[4 + i]);
             visited += (int64_t)h[4 + i];
             if (h[4 + i]) used = i + 1;
@@ -475,8 +482,10 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
             if ((int64_t)h[1] > cap_p) cap_p = (int64_t)h[1] + (int64_t)h[1] / 2;
             continue;
         }
-        if (h[4 + launched - 1] != 0) throw HipFail{hipErrorUnknown, "walk did not terminate"};
-        c->walk_used[wp.mode] = used + 1;
+        if (cur > 0 && h[4 + cur - 1] != 0) throw HipFail{hipErrorUnknown, "walk did not terminate"};
+        std::vector<int64_t> &front = c->walk_front[wp.mode];
+        front.assign(1, c->nroots);
+        for (int i = 0; i < used; ++i) front.push_back((int64_t)h[4 + i]);
         return Lists{ml, (int64_t)h[0], pl, pe, (int64_t)h[1], (int64_t)h[2], used + 1};
     }
 }
@@ -652,16 +661,13 @@ void sink_scale(fmm_ctx *c, bool want_f, const double *eps_b) {
         prepare_p2p(c, L.n_p2p, false);
         double4 *Fe = ensure<double4>(c->Fe, c->ncells);
         CK(launch_est_m2l(want_f, t, c->ncells, ptr<int64_t>(c->m2l_off), ml, c->sh, Fe, s));
-        for (int Lv = 1; Lv <= c->depth; ++Lv)
-            CK(launch_est_l2l_level(want_f, t, c->ls[Lv], c->ls[Lv + 1], Fe, s));
         double4 *e4 = ensure<double4>(c->est4, n);
-        CK(launch_est_l2p(want_f, t, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), n, Fe, e4, s));
+        CK(launch_est_down(want_f, t, ptr<int>(c->leaf_cell), c->nleaves, Fe, e4, s));
         exec_p2p(c, plan_p2p(c, nullptr, NEAR_R), want_f, 0, e4, false);
         CK(launch_scale(want_f, n, e4, scale, s));
     }
     if (eps_b) CK(launch_scale_eps(n, c->perm, eps_b, scale, s));
-    for (int Lv = c->depth; Lv >= 0; --Lv)
-        CK(launch_smin_level(t, c->ls[Lv], c->ls[Lv + 1], scale, s));
+    CK(launch_smin(t, c->nleaves, ptr<int>(c->leaf_cell), scale, s));
 }
 
 // ------------------------------------------------------------ the call

@@ -436,30 +436,26 @@ k_est_m2l(int want_f, TreeArrays t, int nsinks, const int64_t *off, const uint64
     if (lane == 0) Fe[b] = make_double4(f0, f10, f11r, f11i);
 }
 
-// p = 1 shift: F_1^m is unchanged and F_0^0 is not needed for |a|; so the
-// children inherit the parent's coefficients.
-__global__ void k_est_l2l_level(int want_f, TreeArrays t, int c0, int c1, double4 *Fe) {
-    const int c = c0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= c1) return;
-    const int pc = t.parent[c];
-    if (pc < 0) return;
-    const double4 a = Fe[pc];
-    double4 v = Fe[c];
-    v.x += a.x;
-    if (!want_f) {
-        v.y += a.y;
-        v.z += a.z;
-        v.w += a.w;
+// p = 1 shift: F_1^m is unchanged and F_0^0 is not needed for |a|, so a leaf's
+// far field is the sum over its chain of ancestors, the same at every particle.
+// EST_G lanes per leaf follow the chain together (one launch where a level by
+// level pass takes one per level) and write its particles.
+constexpr int EST_G = 16;
+__global__ void __launch_bounds__(256)
+k_est_down(int want_f, TreeArrays t, const int *leaf_cell, int nleaves, const double4 *Fe,
+           double4 *out4) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gt / EST_G >= nleaves) return;
+    const int c = leaf_cell[gt / EST_G];
+    double4 f = Fe[c];
+    for (int a = t.parent[c]; a >= 0; a = t.parent[a]) {
+        const double4 v = Fe[a];
+        f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
     }
-    Fe[c] = v;
-}
-
-__global__ void k_est_l2p(int want_f, TreeArrays t, const int *leaf_of, const int *leaf_cell,
-                          int64_t n, const double4 *Fe, double4 *out4) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double4 f = Fe[leaf_cell[leaf_of[i]]];
-    out4[i] = want_f ? make_double4(f.x, 0.0, 0.0, 0.0) : make_double4(0.0, -f.z, -f.w, -f.y);
+    const double4 o = want_f ? make_double4(f.x, 0.0, 0.0, 0.0)
+                             : make_double4(0.0, -f.z, -f.w, -f.y);
+    const int e = t.end[c];
+    for (int i = t.beg[c] + (int)(gt % EST_G); i < e; i += EST_G) out4[i] = o;
 }
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -647,19 +643,10 @@ hipError_t launch_est_m2l(int want_f, const TreeArrays &t, int nsinks, const int
     return hipGetLastError();
 }
 
-hipError_t launch_est_l2l_level(int want_f, const TreeArrays &t, int c0, int c1, double4 *Fe,
-                                hipStream_t s) {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_est_l2l_level, dim3(blocks(c1 - c0, 128)), dim3(128), 0, s, want_f, t,
-                       c0, c1, Fe);
-    return hipGetLastError();
-}
-
-hipError_t launch_est_l2p(int want_f, const TreeArrays &t, const int *leaf_of,
-                          const int *leaf_cell, int64_t n, const double4 *Fe, double4 *out4,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_est_l2p, dim3(blocks(n, 256)), dim3(256), 0, s, want_f, t, leaf_of,
-                       leaf_cell, n, Fe, out4);
+hipError_t launch_est_down(int want_f, const TreeArrays &t, const int *leaf_cell, int nleaves,
+                           const double4 *Fe, double4 *out4, hipStream_t s) {
+    hipLaunchKernelGGL(k_est_down, dim3(blocks((int64_t)nleaves * EST_G, 256)), dim3(256), 0, s,
+                       want_f, t, leaf_cell, nleaves, Fe, out4);
     return hipGetLastError();
 }
 

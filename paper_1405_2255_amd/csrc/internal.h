@@ -94,24 +94,31 @@ hipError_t launch_tree_cells(const uint64_t *key, const uint64_t *key2, int64_t 
 hipError_t launch_leaf_flags(const TreeArrays &t, int ncells, int *flags, hipStream_t s);
 hipError_t launch_leaf_ranges(const TreeArrays &t, int ncells, const int *leafscan,
                               int *leaf_cell, int *leaf_of, int64_t n, hipStream_t s);
-hipError_t launch_geometry_level(const TreeArrays &t, int c0, int c1, const double *x,
-                                 const double *y, const double *z, const double *m,
-                                 hipStream_t s);
-// enclosing-sphere candidates of the cells [c0, c1) of one level (children done)
-hipError_t launch_enclosing_level(const TreeArrays &t, int c0, int c1, const double *x,
-                                  const double *y, const double *z, hipStream_t s);
+// first cell of each level; levels without cells start where the next one does
+struct LevelStart {
+    int first[FMM_MAXLEVEL + 3];
+};
+#define LEVEL_SMALL 256   // cells of a level that one block can take
+hipError_t launch_geometry(const TreeArrays &t, const LevelStart &ls, int depth, int nleaves,
+                           const int *leaf_cell, const double *x, const double *y,
+                           const double *z, const double *m, hipStream_t s);
+// enclosing-sphere candidates of every cell
+hipError_t launch_enclosing(const TreeArrays &t, const LevelStart &ls, int depth, int nleaves,
+                            const int *leaf_cell, const double *x, const double *y,
+                            const double *z, hipStream_t s);
 // squared radii of every cell: candidate = false about the box midpoint and
 // the centre of mass (rho2 slots 0, 1), true about the enclosing-sphere
 // candidate (slot 2)
 hipError_t launch_radii(const TreeArrays &t, int64_t n, const int *leaf_of,
                         const int *leaf_cell, int maxlevel, const double *x, const double *y,
                         const double *z, bool candidate, hipStream_t s);
-// cen.w and com.w from slots 0, 1
+// cen.w and com.w from slots 0, 1; smin = infinity
 hipError_t launch_radii_finish(const TreeArrays &t, int ncells, hipStream_t s);
 // the candidate replaces the midpoint where its radius (slot 2) is smaller
 hipError_t launch_centre_select(const TreeArrays &t, int ncells, hipStream_t s);
-hipError_t launch_smin_level(const TreeArrays &t, int c0, int c1, const double *scale,
-                             hipStream_t s);
+// minimum sink scale of every cell (smin infinite before)
+hipError_t launch_smin(const TreeArrays &t, int nleaves, const int *leaf_cell,
+                       const double *scale, hipStream_t s);
 
 // ---- expansions.hip ---------------------------------------------------
 // Internal expansion layout: for each cell, the complex coefficients X_n^m,
@@ -163,11 +170,8 @@ hipError_t launch_l2p(int p, const TreeArrays &t, const int *leaf_of, const int 
 // or the 1/r^2 sum (f); L2L of the same; evaluation at particles.
 hipError_t launch_est_m2l(int want_f, const TreeArrays &t, int nsinks, const int64_t *off,
                           const uint64_t *list, int sh, double4 *Fe, hipStream_t s);
-hipError_t launch_est_l2l_level(int want_f, const TreeArrays &t, int c0, int c1, double4 *Fe,
-                                hipStream_t s);
-hipError_t launch_est_l2p(int want_f, const TreeArrays &t, const int *leaf_of,
-                          const int *leaf_cell, int64_t n, const double4 *Fe, double4 *out4,
-                          hipStream_t s);
+hipError_t launch_est_down(int want_f, const TreeArrays &t, const int *leaf_cell, int nleaves,
+                           const double4 *Fe, double4 *out4, hipStream_t s);
 
 // ---- walk.hip -----------------------------------------------------------
 struct WalkParams {
@@ -186,24 +190,33 @@ struct WalkParams {
                              // particle are dropped (forces for a subset, Sec. 7.1)
 };
 struct WalkBuffers {
-    const uint2 *in;
-    uint2 *out; int64_t cap_out;     // both frontier buffers hold cap_out pairs
+    uint2 *front[2]; int64_t cap_out;   // sweep i reads front[i & 1] and writes the other
+                                        // (both hold cap_out pairs)
     uint64_t *m2l; int64_t cap_m2l;
     uint64_t *p2p; uint32_t *p2p_end; int64_t cap_p2p;   // key, end of the source range
     unsigned long long *counters;   // [0] m2l, [1] direct entries, [2] direct particle
                                     // pairs, [3] overflow, [4 + i] frontier after sweep i,
-                                    // [WALK_CUM + 3 i + k] those three totals before sweep i
+                                    // [WALK_CUM + 3 i + k] those three totals before sweep i,
+                                    // [WALK_CUR + j] the sweep that launch j begins with
     uint16_t *code;                 // cap_out: each input pair's decision (count -> write)
 };
-// sweep i reads the frontier size from counters[4 + i - 1] (1 for sweep 0);
-// btmp holds walk_tmp_u64() entries of per-block scratch
+// Launch j takes the sweep in counters[WALK_CUR + j] (launch 0: sweep 0) and
+// leaves the next one in counters[WALK_CUR + j + 1]; sweep i reads its frontier
+// size from counters[4 + i - 1] (sweep 0: the roots) and does nothing if it is 0.
+// small: one block takes sweeps as long as their frontiers hold at most
+// WALK_SMALL pairs (none if the first is larger); else one sweep over the
+// whole chip.  btmp holds walk_tmp_u64() entries of per-block scratch.
+constexpr int WALK_SMALL = 4096;
+constexpr int WALK_SWEEPS = 2 * FMM_MAXLEVEL + 4;           // most sweeps of a walk
+constexpr int WALK_CUM = 4 + WALK_SWEEPS;
+constexpr int WALK_CUR = WALK_CUM + 3 * (WALK_SWEEPS + 1);
+constexpr int WALK_LAUNCHES = 4 * WALK_SWEEPS;              // most launches of a walk
+constexpr int WALK_COUNTERS = WALK_CUR + WALK_LAUNCHES + 1;
 size_t walk_tmp_u64();
-// first of the per-sweep running totals in WalkBuffers::counters, which hold
-// WALK_CUM + 3 (sweeps + 1) entries
-constexpr int WALK_CUM = 4 + 2 * FMM_MAXLEVEL + 4;
 hipError_t launch_root_pairs(uint2 *f, int nroots, hipStream_t s);
 hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *P,
-                       const WalkBuffers &wb, int sweep, unsigned long long *btmp, hipStream_t s);
+                       const WalkBuffers &wb, int launch, bool small, unsigned long long *btmp,
+                       hipStream_t s);
 // offsets of the sorted (sink << sh | source) list per sink: off[c] for c in [0, nsinks]
 hipError_t launch_list_offsets(const uint64_t *list, int64_t nlist, int nsinks, int sh,
                                int64_t *off, hipStream_t s);

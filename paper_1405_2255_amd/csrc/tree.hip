@@ -470,53 +470,10 @@ __global__ void k_leaf_of(const int *scan, int64_t n, int *leaf_of) {
     if (i < n) leaf_of[i] = scan[i + 1] - 1;
 }
 
-__global__ void k_geometry_level(TreeArrays t, int c0, int c1, const double *x, const double *y,
-                                 const double *z, const double *m) {
-    const int c = c0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= c1) return;
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-    const int nch = t.nchild[c];
-    if (nch == 0) {
-        const int e = t.end[c];
-#pragma unroll 8
-        for (int i = t.beg[c]; i < e; ++i) {
-            const double a = x[i], b = y[i], d = z[i], w = m[i];
-            lo[0] = fmin(lo[0], a); hi[0] = fmax(hi[0], a);
-            lo[1] = fmin(lo[1], b); hi[1] = fmax(hi[1], b);
-            lo[2] = fmin(lo[2], d); hi[2] = fmax(hi[2], d);
-            M += w; sx = fma(w, a, sx); sy = fma(w, b, sy); sz = fma(w, d, sz);
-        }
-    } else {
-        // the loads of all (at most 8) children first, so that they are in
-        // flight together; a missing child reads the first one and is skipped
-        const int k0 = t.child0[c];
-        double clo[8][3], chi[8][3], cw[8];
-        double4 cq[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = k0 + (j < nch ? j : 0);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                clo[j][d] = t.lo[3 * k + d];
-                chi[j][d] = t.hi[3 * k + d];
-            }
-            cw[j] = t.mass[k];
-            cq[j] = t.com[k];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (j < nch) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    lo[d] = fmin(lo[d], clo[j][d]);
-                    hi[d] = fmax(hi[d], chi[j][d]);
-                }
-                const double w = cw[j];
-                M += w; sx = fma(w, cq[j].x, sx); sy = fma(w, cq[j].y, sy); sz = fma(w, cq[j].z, sz);
-            }
-        }
-    }
+// ---- geometry: bounding box, mass, centre of mass, box midpoint ------------
+__device__ __forceinline__ void put_geometry(const TreeArrays &t, int c, const double (&lo)[3],
+                                             const double (&hi)[3], double M, double sx, double sy,
+                                             double sz) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         t.lo[3 * c + d] = lo[d];
@@ -528,6 +485,90 @@ __global__ void k_geometry_level(TreeArrays t, int c0, int c1, const double *x, 
     t.rho2[3 * c] = 0ull;
     t.rho2[3 * c + 1] = 0ull;
     t.rho2[3 * c + 2] = 0ull;
+}
+
+// every leaf, LEAF_G lanes each (a lane per leaf left a chain of one load per
+// particle: 14 us for each level of 10^6 particles, where all leaves together
+// now take 12); the lanes' sums are added in a fixed butterfly
+constexpr int LEAF_G = 16;
+
+__global__ void __launch_bounds__(256)
+k_geometry_leaves(TreeArrays t, int nleaves, const int *leaf_cell, const double *x,
+                  const double *y, const double *z, const double *m) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gt / LEAF_G >= nleaves) return;      // whole lane groups leave together
+    const int c = leaf_cell[gt / LEAF_G], sub = (int)(gt % LEAF_G);
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    const int e = t.end[c];
+    for (int i = t.beg[c] + sub; i < e; i += LEAF_G) {
+        const double a = x[i], b = y[i], d = z[i], w = m[i];
+        lo[0] = fmin(lo[0], a); hi[0] = fmax(hi[0], a);
+        lo[1] = fmin(lo[1], b); hi[1] = fmax(hi[1], b);
+        lo[2] = fmin(lo[2], d); hi[2] = fmax(hi[2], d);
+        M += w; sx = fma(w, a, sx); sy = fma(w, b, sy); sz = fma(w, d, sz);
+    }
+#pragma unroll
+    for (int o = LEAF_G / 2; o > 0; o >>= 1) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = fmin(lo[d], __shfl_xor(lo[d], o, LEAF_G));
+            hi[d] = fmax(hi[d], __shfl_xor(hi[d], o, LEAF_G));
+        }
+        M += __shfl_xor(M, o, LEAF_G);
+        sx += __shfl_xor(sx, o, LEAF_G);
+        sy += __shfl_xor(sy, o, LEAF_G);
+        sz += __shfl_xor(sz, o, LEAF_G);
+    }
+    if (sub == 0) put_geometry(t, c, lo, hi, M, sx, sy, sz);
+}
+
+__device__ __forceinline__ void geometry_cell(const TreeArrays &t, int c) {
+    const int nch = t.nchild[c];
+    if (nch == 0) return;
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    // the loads of all (at most 8) children first, so that they are in
+    // flight together; a missing child reads the first one and is skipped
+    const int k0 = t.child0[c];
+    double clo[8][3], chi[8][3], cw[8];
+    double4 cq[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = k0 + (j < nch ? j : 0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            clo[j][d] = t.lo[3 * k + d];
+            chi[j][d] = t.hi[3 * k + d];
+        }
+        cw[j] = t.mass[k];
+        cq[j] = t.com[k];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (j < nch) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = fmin(lo[d], clo[j][d]);
+                hi[d] = fmax(hi[d], chi[j][d]);
+            }
+            const double w = cw[j];
+            M += w; sx = fma(w, cq[j].x, sx); sy = fma(w, cq[j].y, sy); sz = fma(w, cq[j].z, sz);
+        }
+    }
+    put_geometry(t, c, lo, hi, M, sx, sy, sz);
+}
+
+// the internal cells of levels Lhi .. Llo, bottom up.  One level: the whole
+// grid; a run of levels of at most LEVEL_SMALL cells each: one block, so that
+// the many sparse levels of a deep tree cost one launch.
+__global__ void __launch_bounds__(LEVEL_SMALL)
+k_geometry_levels(TreeArrays t, LevelStart ls, int Lhi, int Llo) {
+    for (int L = Lhi; L >= Llo; --L) {
+        const int c = ls.first[L] + blockIdx.x * blockDim.x + threadIdx.x;
+        if (c < ls.first[L + 1]) geometry_cell(t, c);
+        if (L > Llo) __syncthreads();     // (one block)
+    }
 }
 
 // Squared distance without fused multiply-adds, so that the radius of a cell
@@ -668,10 +709,12 @@ k_radii(TreeArrays t, int64_t n, const int *leaf_of, const int *leaf_cell, int m
     }
 }
 
-// Radii about the midpoint and the centre of mass from the squared maxima.
+// Radii about the midpoint and the centre of mass from the squared maxima; the
+// minimum sink scales start at infinity.
 __global__ void k_radii_finish(TreeArrays t, int ncells) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
+    t.smin[c] = INFINITY;
     t.cen[c].w = __dsqrt_rn(bitsd(t.rho2[3 * c]));
     t.com[c].w = __dsqrt_rn(bitsd(t.rho2[3 * c + 1]));
 }
@@ -866,14 +909,11 @@ __device__ __forceinline__ double enc_farthest(bool points, bool regs, int n, in
     return best * best;
 }
 
-__global__ void __launch_bounds__(256)
-k_enclosing_level(TreeArrays t, int c0, int c1, const double *x, const double *y,
-                  const double *z) {
+// the sphere of cell c, by the lane group's lane `sub`
+__device__ __forceinline__ void enclosing_cell(const TreeArrays &t, int c, int sub,
+                                               const double *x, const double *y,
+                                               const double *z) {
 #pragma clang fp contract(off)
-    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = c0 + (int)(gt / ENC_G);
-    if (c >= c1) return;   // whole lane groups leave together
-    const int sub = (int)(gt % ENC_G);
     const int nch = t.nchild[c];
     const bool points = nch == 0;
     const int b = t.beg[c];
@@ -940,26 +980,53 @@ k_enclosing_level(TreeArrays t, int c0, int c1, const double *x, const double *y
     if (sub == 0) t.bsph[c] = make_double4(cx, cy, cz, Rc);
 }
 
-__global__ void k_smin_level(TreeArrays t, int c0, int c1, const double *scale) {
-    const int c = c0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= c1) return;
-    double s = INFINITY;
-    const int nch = t.nchild[c];
-    if (nch == 0) {
-        const int e = t.end[c];
-#pragma unroll 8
-        for (int i = t.beg[c]; i < e; ++i) s = fmin(s, scale[i]);
-    } else {
-        // all children's loads in flight together (a missing child re-reads the first)
-        const int k0 = t.child0[c];
-        double v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = t.smin[k0 + (j < nch ? j : 0)];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s = fmin(s, v[j]);
-    }
-    t.smin[c] = s;
+// every leaf (lane groups of whole wavefronts), then the internal cells of
+// levels Lhi .. Llo as the geometry does (a run of levels: at most one block of
+// lane groups each)
+__global__ void __launch_bounds__(256)
+k_enclosing_leaves(TreeArrays t, int nleaves, const int *leaf_cell, const double *x,
+                   const double *y, const double *z) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gt / ENC_G >= nleaves) return;   // whole lane groups leave together
+    enclosing_cell(t, leaf_cell[gt / ENC_G], (int)(gt % ENC_G), x, y, z);
 }
+
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
+k_enclosing_levels(TreeArrays t, LevelStart ls, int Lhi, int Llo, const double *x,
+                   const double *y, const double *z) {
+    const int gt = blockIdx.x * THREADS + threadIdx.x;
+    for (int L = Lhi; L >= Llo; --L) {
+        const int c = ls.first[L] + gt / ENC_G;
+        if (c < ls.first[L + 1] && t.nchild[c] > 0) enclosing_cell(t, c, gt % ENC_G, x, y, z);
+        if (L > Llo) __syncthreads();     // (one block)
+    }
+}
+
+// Minimum sink scale of every cell: LEAF_G lanes take the minimum of a leaf,
+// then one of them goes up the tree with it until an ancestor already holds a
+// value at most as large (whoever put it there takes it further up).  Bit
+// patterns of values >= 0 order like the values.
+__global__ void __launch_bounds__(256)
+k_smin(TreeArrays t, int nleaves, const int *leaf_cell, const double *scale) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gt / LEAF_G >= nleaves) return;      // whole lane groups leave together
+    int c = leaf_cell[gt / LEAF_G];
+    const int sub = (int)(gt % LEAF_G), e = t.end[c];
+    double s = INFINITY;
+    for (int i = t.beg[c] + sub; i < e; i += LEAF_G) s = fmin(s, scale[i]);
+#pragma unroll
+    for (int o = LEAF_G / 2; o > 0; o >>= 1) s = fmin(s, __shfl_xor(s, o, LEAF_G));
+    if (sub != 0) return;
+    t.smin[c] = s;
+    const unsigned long long b = dbits(s);
+    for (c = t.parent[c]; c >= 0; c = t.parent[c]) {
+        unsigned long long *p = reinterpret_cast<unsigned long long *>(t.smin + c);
+        if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= b) break;
+        if (atomicMin(p, b) <= b) break;
+    }
+}
+
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
@@ -1097,21 +1164,51 @@ hipError_t launch_leaf_ranges(const TreeArrays &t, int ncells, const int *leafsc
     return hipGetLastError();
 }
 
-hipError_t launch_geometry_level(const TreeArrays &t, int c0, int c1, const double *x,
-                                 const double *y, const double *z, const double *m,
-                                 hipStream_t s) {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_geometry_level, dim3(blocks(c1 - c0, 128)), dim3(128), 0, s, t, c0, c1,
-                       x, y, z, m);
-    return hipGetLastError();
+// fn(Lhi, Llo): a run of consecutive levels of at most `small` cells each, or
+// one level, from the deepest up
+template <class F>
+static hipError_t up_levels(const LevelStart &ls, int depth, int small, F &&fn) {
+    for (int L = depth; L >= 0;) {
+        int lo = L;
+        auto few = [&](int l) { return ls.first[l + 1] - ls.first[l] <= small; };
+        if (few(L))
+            while (lo > 0 && few(lo - 1)) --lo;
+        const hipError_t e = fn(L, lo);
+        if (e != hipSuccess) return e;
+        L = lo - 1;
+    }
+    return hipSuccess;
 }
 
-hipError_t launch_enclosing_level(const TreeArrays &t, int c0, int c1, const double *x,
-                                  const double *y, const double *z, hipStream_t s) {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_enclosing_level, dim3(blocks((int64_t)(c1 - c0) * ENC_G, 256)),
-                       dim3(256), 0, s, t, c0, c1, x, y, z);
-    return hipGetLastError();
+hipError_t launch_geometry(const TreeArrays &t, const LevelStart &ls, int depth, int nleaves,
+                           const int *leaf_cell, const double *x, const double *y,
+                           const double *z, const double *m, hipStream_t s) {
+    hipLaunchKernelGGL(k_geometry_leaves, dim3(blocks((int64_t)nleaves * LEAF_G, 256)), dim3(256),
+                       0, s, t, nleaves, leaf_cell, x, y, z, m);
+    return up_levels(ls, depth, LEVEL_SMALL, [&](int Lhi, int Llo) {
+        const int nc = Lhi > Llo ? 1 : ls.first[Lhi + 1] - ls.first[Lhi];
+        hipLaunchKernelGGL(k_geometry_levels, dim3(blocks(nc, LEVEL_SMALL)), dim3(LEVEL_SMALL), 0,
+                           s, t, ls, Lhi, Llo);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_enclosing(const TreeArrays &t, const LevelStart &ls, int depth, int nleaves,
+                            const int *leaf_cell, const double *x, const double *y,
+                            const double *z, hipStream_t s) {
+    hipLaunchKernelGGL(k_enclosing_leaves, dim3(blocks((int64_t)nleaves * ENC_G, 256)), dim3(256),
+                       0, s, t, nleaves, leaf_cell, x, y, z);
+    return up_levels(ls, depth, 1024 / ENC_G, [&](int Lhi, int Llo) {
+        if (Lhi > Llo) {
+            hipLaunchKernelGGL(k_enclosing_levels<1024>, dim3(1), dim3(1024), 0, s, t, ls, Lhi,
+                               Llo, x, y, z);
+        } else {
+            const int64_t nc = ls.first[Lhi + 1] - ls.first[Lhi];
+            hipLaunchKernelGGL(k_enclosing_levels<256>, dim3(blocks(nc * ENC_G, 256)), dim3(256),
+                               0, s, t, ls, Lhi, Llo, x, y, z);
+        }
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_radii(const TreeArrays &t, int64_t n, const int *leaf_of, const int *leaf_cell,
@@ -1137,11 +1234,10 @@ hipError_t launch_centre_select(const TreeArrays &t, int ncells, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_smin_level(const TreeArrays &t, int c0, int c1, const double *scale,
-                             hipStream_t s) {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_smin_level, dim3(blocks(c1 - c0, 128)), dim3(128), 0, s, t, c0, c1,
-                       scale);
+hipError_t launch_smin(const TreeArrays &t, int nleaves, const int *leaf_cell,
+                       const double *scale, hipStream_t s) {
+    hipLaunchKernelGGL(k_smin, dim3(blocks((int64_t)nleaves * LEAF_G, 256)), dim3(256), 0, s, t,
+                       nleaves, leaf_cell, scale);
     return hipGetLastError();
 }
 

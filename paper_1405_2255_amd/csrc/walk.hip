@@ -93,12 +93,14 @@ __device__ __forceinline__ Decision decide(const WalkParams &wp, const TreeArray
 }
 
 // Sweeps run without host round trips: sweep i reads its frontier size from
-// counters[4 + i - 1].  Each sweep is two launches over a fixed grid of
+// counters[4 + i - 1].  A sweep with a large frontier is two launches over a fixed grid of
 // WALK_BLOCKS blocks, block b owning a contiguous chunk of the frontier:
 // count (per-block totals) and write (each block sums the totals of the
 // blocks before it for its offsets, block 0 the sweep's totals; then the
 // outputs at their offsets, in frontier order).  No atomics; the output order
-// is deterministic.
+// is deterministic.  Sweeps whose frontier holds at most WALK_SMALL pairs are
+// bound by launches and by the latency of a chain of dependent loads: one
+// block takes a run of them in a single launch, in the same order.
 constexpr int WALK_BLOCKS = 1024;
 constexpr int WALK_THREADS = 256;
 constexpr int WALK_WBATCH = 4;  // rounds whose loads the write kernel issues together
@@ -143,17 +145,20 @@ __device__ __forceinline__ void block_scan3(int &a, int &b, int &c, int *tot) {
 }
 
 __global__ void __launch_bounds__(WALK_THREADS)
-k_walk_count(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int sweep,
+k_walk_count(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch,
              unsigned long long *btot) {
     const unsigned long long *cnt = wb.counters;
+    const int sweep = (int)cnt[WALK_CUR + launch];
     const int64_t n_in = sweep_input(wp, cnt, sweep);
+    if (n_in == 0) return;
+    const uint2 *in = wb.front[sweep & 1];
     unsigned long long f = 0, m = 0, q = 0;
     double pairs = 0.0;
     if (n_in <= wb.cap_out) {
         const int64_t chunk = (n_in + WALK_BLOCKS - 1) / WALK_BLOCKS;
         const int64_t lo = (int64_t)blockIdx.x * chunk, hi = min(n_in, lo + chunk);
         for (int64_t i = lo + threadIdx.x; i < hi; i += WALK_THREADS) {
-            const uint2 pr = wb.in[i];
+            const uint2 pr = in[i];
             const Decision d = decide(wp, t, P, (int)pr.x, (int)pr.y);
             wb.code[i] = (uint16_t)(d.kind | (d.nf << 3));   // kind < 8, nf <= 64
             f += d.nf;
@@ -236,11 +241,55 @@ __device__ __forceinline__ void walk_offsets(const unsigned long long *btot, boo
     }
 }
 
+// the outputs of one pair (A, B): frontier pairs from pf on, or the M2L entry
+// pm, or the direct-sum entry pp (dropped past the buffers' ends)
+__device__ __forceinline__ void write_outputs(const WalkParams &wp, const WalkBuffers &wb,
+                                              uint2 *out, int kind, int n, int A, int B, int kA,
+                                              int kB, int nchA, int begA, int endA, int64_t pf,
+                                              int64_t pm, int64_t pp) {
+    switch (kind) {
+    case 1:     // all ordered daughter pairs of A
+        if (pf + n <= wb.cap_out)
+            for (int a = 0; a < nchA; ++a)
+                for (int b = 0; b < nchA; ++b) out[pf + a * nchA + b] = make_uint2(kA + a, kA + b);
+        break;
+    case 2:
+        if (pf + n <= wb.cap_out)
+            for (int a = 0; a < n; ++a) out[pf + a] = make_uint2(kA + a, B);
+        break;
+    case 3:
+        if (pf + n <= wb.cap_out)
+            for (int b = 0; b < n; ++b) out[pf + b] = make_uint2(A, kB + b);
+        break;
+    case 4:     // direct sum of A's particles onto B's (B may be any cell)
+        if (pp + 1 <= wb.cap_p2p) {
+            if (wp.pack) {
+                wb.p2p[pp] = ((uint64_t)B << (2 * wp.pb)) | ((uint64_t)begA << wp.pb) |
+                             (uint64_t)endA;
+            } else {
+                wb.p2p[pp] = ((uint64_t)B << wp.pb) | (uint64_t)begA;
+                wb.p2p_end[pp] = (uint32_t)endA;
+            }
+        }
+        break;
+    case 5:
+        if (pm + 1 <= wb.cap_m2l) wb.m2l[pm] = ((uint64_t)B << wp.sh) | (uint64_t)A;
+        break;
+    default:
+        break;
+    }
+}
+
 __global__ void __launch_bounds__(WALK_THREADS)
-k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int sweep,
+k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch,
              const unsigned long long *btot) {
     unsigned long long *cnt = wb.counters;
+    const int sweep = (int)cnt[WALK_CUR + launch];
     const int64_t n_in = sweep_input(wp, cnt, sweep);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[WALK_CUR + launch + 1] = sweep + (n_in > 0);
+    if (n_in == 0) return;
+    const uint2 *in = wb.front[sweep & 1];
+    uint2 *out = wb.front[(sweep + 1) & 1];
     const int64_t chunk = (n_in + WALK_BLOCKS - 1) / WALK_BLOCKS;
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = min(n_in, lo + chunk);
     const bool fits = n_in <= wb.cap_out;
@@ -269,7 +318,7 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int s
         for (int r = 0; r < WALK_WBATCH; ++r) {
             const int64_t i = base0 + (int64_t)r * WALK_THREADS + threadIdx.x;
             const bool v = i < hi;    // the decision the count pass took for this pair
-            const uint2 pr = v ? wb.in[i] : make_uint2(0u, 0u);
+            const uint2 pr = v ? in[i] : make_uint2(0u, 0u);
             const unsigned code = v ? wb.code[i] : 0u;
             A[r] = (int)pr.x;
             B[r] = (int)pr.y;
@@ -295,49 +344,115 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int s
             block_scan3(sf, sm, sp, tot);
             const int64_t pf = of + sf - n, pm = om + sm - (k == 5), pp = op + sp - (k == 4);
             const int a0 = A[r], b0 = B[r];
-            switch (k) {
-            case 1: {   // all ordered daughter pairs of A
-                const int k0 = kA[r], nch = nchA[r];
-                if (pf + n <= wb.cap_out)
-                    for (int a = 0; a < nch; ++a)
-                        for (int b = 0; b < nch; ++b)
-                            wb.out[pf + a * nch + b] = make_uint2(k0 + a, k0 + b);
-                break;
-            }
-            case 2: {
-                const int k0 = kA[r];
-                if (pf + n <= wb.cap_out)
-                    for (int a = 0; a < n; ++a) wb.out[pf + a] = make_uint2(k0 + a, b0);
-                break;
-            }
-            case 3: {
-                const int k0 = kB[r];
-                if (pf + n <= wb.cap_out)
-                    for (int b = 0; b < n; ++b) wb.out[pf + b] = make_uint2(a0, k0 + b);
-                break;
-            }
-            case 4:     // direct sum of A's particles onto B's (B may be any cell)
-                if (pp + 1 <= wb.cap_p2p) {
-                    if (wp.pack) {
-                        wb.p2p[pp] = ((uint64_t)b0 << (2 * wp.pb)) |
-                                     ((uint64_t)begA[r] << wp.pb) | (uint64_t)endA[r];
-                    } else {
-                        wb.p2p[pp] = ((uint64_t)b0 << wp.pb) | (uint64_t)begA[r];
-                        wb.p2p_end[pp] = (uint32_t)endA[r];
-                    }
-                }
-                break;
-            case 5:
-                if (pm + 1 <= wb.cap_m2l) wb.m2l[pm] = ((uint64_t)b0 << wp.sh) | (uint64_t)a0;
-                break;
-            default:
-                break;
-            }
+            write_outputs(wp, wb, out, k, n, a0, b0, kA[r], kB[r], nchA[r], begA[r], endA[r], pf,
+                          pm, pp);
             of += tot[0];
             om += tot[1];
             op += tot[2];
         }
     }
+}
+
+// A run of sweeps with small frontiers, one block: each thread decides up to
+// SMALL_B pairs (pair r * SMALL_THREADS + thread), the counts of all pairs are
+// scanned in frontier order, and the outputs are written.  The three counts of
+// a pair share one 64-bit word: frontier pairs in bits 0..23 (at most 64 per
+// pair), M2L entries in 24..43, direct entries in 44..63.
+constexpr int SMALL_THREADS = 1024;
+constexpr int SMALL_B = WALK_SMALL / SMALL_THREADS;
+constexpr int SMALL_WAVES = SMALL_THREADS / FMM_WAVE;
+static_assert(SMALL_B * SMALL_WAVES == FMM_WAVE, "one wavefront scans the wavefronts' totals");
+static_assert(WALK_SMALL * 64 < (1 << 24), "frontier count field");
+
+__device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int off = 1; off < FMM_WAVE; off <<= 1) {
+        const unsigned long long o = __shfl_up(v, off, FMM_WAVE);
+        if (lane >= off) v += o;
+    }
+    return v;
+}
+
+__global__ void __launch_bounds__(SMALL_THREADS)
+k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch) {
+    __shared__ unsigned long long ws[FMM_WAVE + 1];
+    __shared__ double red[SMALL_WAVES];
+    unsigned long long *cnt = wb.counters;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / FMM_WAVE;
+    int sweep = (int)cnt[WALK_CUR + launch];
+    int64_t n_in = sweep_input(wp, cnt, sweep);
+    const unsigned long long *cum = cnt + WALK_CUM + 3 * sweep;
+    unsigned long long m0 = cum[0], p0 = cum[1];
+    const unsigned long long pairs0 = cum[2];
+    double pairs = 0.0;
+    const int first = sweep;
+    while (n_in > 0 && n_in <= WALK_SMALL && n_in <= wb.cap_out && sweep < WALK_SWEEPS) {
+        const uint2 *in = wb.front[sweep & 1];
+        uint2 *out = wb.front[(sweep + 1) & 1];
+        int A[SMALL_B], B[SMALL_B], kind[SMALL_B], nf[SMALL_B];
+        unsigned long long c[SMALL_B];
+#pragma unroll
+        for (int r = 0; r < SMALL_B; ++r) {
+            const int i = r * SMALL_THREADS + tid;
+            const uint2 pr = i < n_in ? in[i] : make_uint2(0u, 0u);
+            A[r] = (int)pr.x;
+            B[r] = (int)pr.y;
+        }
+#pragma unroll
+        for (int r = 0; r < SMALL_B; ++r) {
+            Decision d{0, 0, 0.0};
+            if (r * SMALL_THREADS + tid < n_in) d = decide(wp, t, P, A[r], B[r]);
+            kind[r] = d.kind;
+            nf[r] = d.nf;
+            pairs += d.pairs;
+            c[r] = (unsigned long long)d.nf | ((unsigned long long)(d.kind == 5) << 24) |
+                   ((unsigned long long)(d.kind == 4) << 44);
+        }
+        unsigned long long incl[SMALL_B];
+#pragma unroll
+        for (int r = 0; r < SMALL_B; ++r) {
+            incl[r] = wave_incl_scan64(c[r]);
+            if (lane == FMM_WAVE - 1) ws[r * SMALL_WAVES + w] = incl[r];
+        }
+        __syncthreads();
+        if (w == 0) {       // exclusive scan of the wavefronts' totals, and the total
+            const unsigned long long v = ws[lane], s = wave_incl_scan64(v);
+            ws[lane] = s - v;
+            if (lane == FMM_WAVE - 1) ws[FMM_WAVE] = s;
+        }
+        __syncthreads();
+        const unsigned long long total = ws[FMM_WAVE];
+#pragma unroll
+        for (int r = 0; r < SMALL_B; ++r) {
+            if (kind[r] == 0) continue;
+            const unsigned long long o = ws[r * SMALL_WAVES + w] + incl[r] - c[r];
+            const int a = A[r], b = B[r];
+            write_outputs(wp, wb, out, kind[r], nf[r], a, b, t.child0[a], t.child0[b],
+                          t.nchild[a], t.beg[a], t.end[a], (int64_t)(o & 0xffffffu),
+                          (int64_t)(m0 + ((o >> 24) & 0xfffffu)), (int64_t)(p0 + (o >> 44)));
+        }
+        n_in = (int64_t)(total & 0xffffffu);
+        m0 += (total >> 24) & 0xfffffu;
+        p0 += total >> 44;
+        if (tid == 0) {
+            cnt[4 + sweep] = (unsigned long long)n_in;
+            cnt[WALK_CUM + 3 * (sweep + 1)] = m0;
+            cnt[WALK_CUM + 3 * (sweep + 1) + 1] = p0;
+        }
+        ++sweep;
+        __syncthreads();    // the outputs are this block's next inputs
+    }
+    pairs = wave_sum(pairs);
+    if (lane == 0) red[w] = pairs;
+    __syncthreads();
+    if (tid != 0) return;
+    cnt[WALK_CUR + launch + 1] = sweep;
+    if (sweep == first) return;
+    for (int i = 1; i < SMALL_WAVES; ++i) pairs += red[i];
+    cnt[0] = m0;
+    cnt[1] = p0;
+    cnt[2] = cnt[WALK_CUM + 3 * sweep + 2] = pairs0 + (unsigned long long)pairs;
 }
 
 __global__ void k_list_offsets(const uint64_t *list, int64_t nlist, int nsinks, int sh,
@@ -436,13 +551,18 @@ hipError_t launch_root_pairs(uint2 *f, int nroots, hipStream_t s) {
 }
 
 hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *P,
-                       const WalkBuffers &wb, int sweep, unsigned long long *btmp, hipStream_t s) {
+                       const WalkBuffers &wb, int launch, bool small, unsigned long long *btmp,
+                       hipStream_t s) {
+    if (small) {
+        hipLaunchKernelGGL(k_walk_small, dim3(1), dim3(SMALL_THREADS), 0, s, wp, t, P, wb, launch);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_walk_count, dim3(WALK_BLOCKS), dim3(WALK_THREADS), 0, s, wp, t, P, wb,
-                       sweep, btmp);
+                       launch, btmp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_walk_write, dim3(WALK_BLOCKS), dim3(WALK_THREADS), 0, s, wp, t, P, wb,
-                       sweep, (const unsigned long long *)btmp);
+                       launch, (const unsigned long long *)btmp);
     return hipGetLastError();
 }
 
