@@ -165,7 +165,7 @@ struct fmm_ctx {
     int ncells = 0, nleaves = 0, depth = 0, sh = 0, pb = 0, p = 0;
     int pack = 0;   // direct-sum keys carry the range end (sh + 2 pb <= 64)
     std::vector<int64_t> walk_front[3];   // frontier sizes of the last walk of each mode
-    int64_t n_m2l = 0, n_p2p = 0, n_ranges = 0;
+    int64_t n_m2l = 0, n_p2p = 0;
     uint64_t *m2l_sorted = nullptr, *p2p_sorted = nullptr;
     uint32_t *p2pe_sorted = nullptr;
     std::vector<int> ls;  // first cell of each level
@@ -272,42 +272,55 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
         std::swap(i1, i2);
     }
     // level-21 cells with more than `leaf` particles get a second key word;
-    // each such run is re-sorted by (second word, position)
+    // each such run is re-sorted by (second word, position).  Few inputs need
+    // it: unless the context's last build did, the tree is counted without
+    // waiting to know, and again in the rare case
     uint64_t *kd = ensure<uint64_t>(c->dkey, n);
-    {
-        uint64_t *rs = ensure<uint64_t>(c->runstart, n);
-        uint64_t *sa = ensure<uint64_t>(c->dsort, n), *sb = ensure<uint64_t>(c->dsort2, n);
-        uint32_t *o1 = ensure<uint32_t>(c->order, n), *o2 = ensure<uint32_t>(c->order2, n);
-        int *any = ptr<int>(c->nonfinite) + 4;
-        CK(hipMemsetAsync(any, 0, sizeof(int), s));
-        CK(launch_deep_keys(pos, i1, k1, n, K, doff, bb, leaf, kd, rs, o1, any, s));
-        CK(hipMemcpyAsync(c->hint, any, sizeof(int), hipMemcpyDeviceToHost, s));
-        sync(c);
-        c->deep = c->hint[0] != 0;
-        if (c->deep) {
-            CK(hipMemcpyAsync(sa, kd, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
-            CK(radix_sort(&sa, &sb, &o1, &o2, n, 63, tmp, s));          // by (second word, position)
-            CK(launch_gather_u64(o1, rs, n, sb, s));                     // run of each
-            CK(radix_sort(&sb, &sa, &o1, &o2, n, std::max(1, bitlen((uint64_t)n)), tmp, s));
-            // sa is free now: it receives the second words in the final order
-            CK(launch_apply_order2(o1, k1, kd, i1, n, k2, sa, i2, s));
-            std::swap(k1, k2);
-            std::swap(i1, i2);
-            kd = sa;
-        }
-    }
-    c->kdeep = kd;
-    c->perm = i1;
-    CK(launch_gather(pos, mass, c->perm, n, x, y, z, m, xyzm, s));
-    // octree: every cell of every level from the run structure of the keys
+    uint64_t *rs = ensure<uint64_t>(c->runstart, n);
+    uint64_t *sa = ensure<uint64_t>(c->dsort, n), *sb = ensure<uint64_t>(c->dsort2, n);
+    uint32_t *o1 = ensure<uint32_t>(c->order, n), *o2 = ensure<uint32_t>(c->order2, n);
+    int *any = ptr<int>(c->nonfinite) + 4, *hany = c->hint + 8;
+    CK(hipMemsetAsync(any, 0, sizeof(int), s));
+    CK(launch_deep_keys(pos, i1, k1, n, K, doff, bb, leaf, kd, rs, o1, any, s));
+    CK(hipMemcpyAsync(hany, any, sizeof(int), hipMemcpyDeviceToHost, s));
+    auto refine = [&]() {
+        CK(hipMemcpyAsync(sa, kd, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
+        CK(radix_sort(&sa, &sb, &o1, &o2, n, 63, tmp, s));          // by (second word, position)
+        CK(launch_gather_u64(o1, rs, n, sb, s));                     // run of each
+        CK(radix_sort(&sb, &sa, &o1, &o2, n, std::max(1, bitlen((uint64_t)n)), tmp, s));
+        // sa is free now: it receives the second words in the final order
+        CK(launch_apply_order2(o1, k1, kd, i1, n, k2, sa, i2, s));
+        std::swap(k1, k2);
+        std::swap(i1, i2);
+        kd = sa;
+    };
     int *tg = ensure<int>(c->tg, n), *tpre = ensure<int>(c->tpre, n);
     int *tsuf = ensure<int>(c->tsuf, n);
     int *tcnt = ensure<int>(c->flags, n + 2);
     int *total = ptr<int>(c->nonfinite) + 1;
-    CK(launch_tree(k1, kd, n, K, doff, leaf, tg, tpre, tsuf, tcnt, s));
-    CK(exclusive_scan(tcnt, tcnt, n + 1, tmp, total, s));
-    CK(hipMemcpyAsync(c->hint, total, sizeof(int), hipMemcpyDeviceToHost, s));
-    sync(c);
+    // particles in key order, and the number of cells: every cell of every level
+    // from the run structure of the keys
+    auto count_cells = [&]() {
+        CK(launch_gather(pos, mass, i1, n, x, y, z, m, xyzm, s));
+        CK(launch_tree(k1, kd, n, K, doff, leaf, tg, tpre, tsuf, tcnt, s));
+        CK(exclusive_scan(tcnt, tcnt, n + 1, tmp, total, s));
+        CK(hipMemcpyAsync(c->hint, total, sizeof(int), hipMemcpyDeviceToHost, s));
+        sync(c);
+    };
+    const bool ask = c->deep;
+    if (ask) {
+        sync(c);
+        c->deep = *hany != 0;
+        if (c->deep) refine();
+    }
+    count_cells();
+    if (!ask && *hany) {
+        c->deep = true;
+        refine();
+        count_cells();
+    }
+    c->kdeep = kd;
+    c->perm = i1;
     const int nc_all = c->hint[0];
     uint64_t *cl1 = ensure<uint64_t>(c->tcell, nc_all), *cl2 = ensure<uint64_t>(c->tcell2, nc_all);
     CK(launch_tree_emit(k1, kd, n, K, doff, leaf, tpre, tsuf, tcnt, cl1, s));
@@ -319,26 +332,13 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
     grow_cells(c, nc_all, 0);
     TreeArrays t = tree_arrays(c);
     CK(launch_tree_cells(k1, kd, n, K, doff, cl1, nc_all, dls, t, s));
-    int hls[FMM_MAXLEVEL + 2];
-    static_assert(sizeof(hls) <= HCNT * sizeof(unsigned long long), "level table mirror");
-    CK(hipMemcpyAsync(c->hcnt, dls, sizeof(hls), hipMemcpyDeviceToHost, s));
-    sync(c);
-    std::memcpy(hls, c->hcnt, sizeof(hls));
-    tmp = tmp2;
-    // ls[L] = first cell of level L up to the deepest level, then ncells twice
-    c->ls.clear();
-    for (int L = 0; L <= FMM_MAXLEVEL + 1; ++L) {
-        c->ls.push_back(hls[L]);
-        if (hls[L] == nc_all) break;
-    }
-    c->ls.push_back(nc_all);
-    const int ncells = c->ls.back();
+    // per-cell arrays, then the leaves in key order; the level table and the
+    // number of leaves come to the host together
+    const int ncells = nc_all;
     c->ncells = ncells;
-    c->depth = (int)c->ls.size() - 3;   // ls ends with two equal entries
     c->sh = std::max(1, bitlen((uint64_t)ncells));
     c->pb = std::max(1, bitlen((uint64_t)n));
     c->pack = c->sh + 2 * c->pb <= 64;
-    // per-cell arrays sized now that the count is known
     ensure<int>(c->leaf_lo, ncells); ensure<int>(c->leaf_hi, ncells);
     ensure<double4>(c->cen, ncells); ensure<double4>(c->com, ncells);
     ensure<double>(c->mass, ncells); ensure<double>(c->lo, 3 * (size_t)ncells);
@@ -346,17 +346,29 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
     ensure<double4>(c->bsph, ncells);
     ensure<double>(c->smin, ncells);
     t = tree_arrays(c);
-    // leaves in key order
+    tmp = tmp2;
     int *flags = ensure<int>(c->flags, n + 2);
     CK(hipMemsetAsync(flags, 0, sizeof(int) * (n + 1), s));
     CK(launch_leaf_flags(t, ncells, flags, s));
     CK(exclusive_scan(flags, flags, n + 1, tmp, total, s));
+    int hls[FMM_MAXLEVEL + 2];
+    static_assert(sizeof(hls) <= HCNT * sizeof(unsigned long long), "level table mirror");
+    CK(hipMemcpyAsync(c->hcnt, dls, sizeof(hls), hipMemcpyDeviceToHost, s));
     CK(hipMemcpyAsync(c->hint, total, sizeof(int), hipMemcpyDeviceToHost, s));
     int *leaf_cell = ensure<int>(c->leaf_cell, ncells);
     int *leaf_of = ensure<int>(c->leaf_of, n);
     CK(launch_leaf_ranges(t, ncells, flags, leaf_cell, leaf_of, n, s));
     sync(c);
     c->nleaves = c->hint[0];
+    std::memcpy(hls, c->hcnt, sizeof(hls));
+    // ls[L] = first cell of level L up to the deepest level, then ncells twice
+    c->ls.clear();
+    for (int L = 0; L <= FMM_MAXLEVEL + 1; ++L) {
+        c->ls.push_back(hls[L]);
+        if (hls[L] == ncells) break;
+    }
+    c->ls.push_back(ncells);
+    c->depth = (int)c->ls.size() - 3;   // ls ends with two equal entries
     c->tree_valid = true;
     c->tree_n = n;
     c->tree_off.assign(off, off + K + 1);
@@ -510,9 +522,10 @@ uint64_t *sort_list(fmm_ctx *c, DevBuf &a, DevBuf &b, int64_t nlist, int nsinks,
 // order), merging the ranges that the walk emitted next to each other - two
 // radix passes fewer; used for the estimate's short lists, where the longer
 // range lists cost the direct-sum kernel nothing measurable
-// side: on the side stream, with its own scratch, device counter and host
-// slot, so that it can run while the main stream does M2L (the caller joins
-// the side stream before the lists are used)
+// side: on the side stream, with its own scratch and device counter, so that it
+// can run while the main stream does M2L (the caller joins the side stream
+// before the lists are used).  Nothing here waits for the device: the number of
+// ranges stays there.
 void prepare_p2p(fmm_ctx *c, int64_t nlist, bool by_source, bool side = false) {
     const hipStream_t s = side ? c->side : c->stream;
     uint64_t *k1 = ptr<uint64_t>(c->p2p);
@@ -534,25 +547,24 @@ void prepare_p2p(fmm_ctx *c, int64_t nlist, bool by_source, bool side = false) {
     int2 *rg = ensure<int2>(c->ranges, std::max<int64_t>(nlist, 1));
     uint64_t *rk = ensure<uint64_t>(c->rkey, std::max<int64_t>(nlist, 1));
     int *total = ptr<int>(c->nonfinite) + (side ? 3 : 1);
-    int *host = c->hint + (side ? 3 : 0);
-    int64_t runs = 0;
     if (nlist > 0) {
         CK(launch_range_merge(k1, v1, nlist, c->pb, c->pack, flag, tmp, total, rg, rk, false, s));
-        CK(hipMemcpyAsync(host, total, sizeof(int), hipMemcpyDeviceToHost, s));
         CK(launch_range_merge(k1, v1, nlist, c->pb, c->pack, flag, tmp, total, rg, rk, true, s));
-        CK(hipStreamSynchronize(s));
-        runs = *host;
     }
-    c->n_ranges = runs;
     int64_t *off = ensure<int64_t>(c->p2p_off, (size_t)c->ncells + 1);
-    CK(launch_list_offsets(rk, runs, c->ncells, c->pb, off, s));
+    CK(launch_list_offsets(rk, 0, c->ncells, c->pb, off, s, nlist > 0 ? total : nullptr));
 }
 
 // Direct-sum tasks of the prepared lists: per leaf the task counts, the
 // ancestor chains and the task list (active: leaves without listed sinks get
 // none).  side: on the side stream with its own scratch, counters and host
-// slots (the caller joins the side stream before the tasks run).
+// slots (the caller joins the side stream before the tasks run).  begin_p2p
+// queues the counts and their copy to the host, finish_p2p waits for them,
+// sizes the buffers and queues the rest.
 struct P2PPlan {
+    bool side = false;
+    const uint8_t *active = nullptr;
+    int *up = nullptr;
     int width = 0;                 // sinks per task and entries of a partial row
     int ntasks = 0, prows = 0;     // (FP64: a row per task)
     int4 *near = nullptr;          // FP64 tasks, list entries and slices per leaf
@@ -561,11 +573,13 @@ struct P2PPlan {
     int *nts = nullptr, *toff = nullptr, *moff = nullptr, *chain = nullptr;
 };
 
-P2PPlan plan_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false) {
+P2PPlan begin_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false) {
     const hipStream_t s = side ? c->side : c->stream;
     const int nl = c->nleaves;
     TreeArrays t = tree_arrays(c);
     P2PPlan pl;
+    pl.side = side;
+    pl.active = active;
     pl.width = width;
     int *ntask = ensure<int>(c->pt_n, (size_t)nl + 1), *mtask = ensure<int>(c->pt_m, (size_t)nl + 1);
     pl.nts = ensure<int>(c->pt_s, (size_t)nl + 1);
@@ -573,24 +587,30 @@ P2PPlan plan_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false
     pl.moff = ensure<int>(c->pt_moff, (size_t)nl + 1);
     int *tmp = side ? ensure<int>(c->tmp_side, scan_tmp_ints(nl + 1)) : tmp_ints(c, scan_tmp_ints(nl + 1));
     int *totals = ptr<int>(c->nonfinite) + (side ? 6 : 1);
-    int *host = c->hint + (side ? 4 : 0);
     const int *leaf_cell = ptr<int>(c->leaf_cell);
     const int64_t *off = ptr<int64_t>(c->p2p_off);
     const int2 *rg = ptr<int2>(c->ranges);
-    int *up = ensure<int>(c->rup, (size_t)std::max(c->ncells, 1));
-    CK(launch_range_up(c->ncells, t.parent, off, up, s));
+    pl.up = ensure<int>(c->rup, (size_t)std::max(c->ncells, 1));
+    CK(launch_range_up(c->ncells, t.parent, off, pl.up, s));
     if (width == 64) {
         pl.chain = ensure<int>(c->pchain, (size_t)std::max(nl, 1) * P2P_CHAIN);
-        CK(launch_p2p_plan(nl, leaf_cell, off, rg, up, t, active, ntask, mtask, pl.nts, pl.toff,
+        CK(launch_p2p_plan(nl, leaf_cell, off, rg, pl.up, t, active, ntask, mtask, pl.nts, pl.toff,
                            pl.moff, pl.chain, tmp, totals, s));
     } else {
-        CK(launch_near_count(nl, width, leaf_cell, off, rg, up, t, active, ntask, pl.nts, mtask,
+        CK(launch_near_count(nl, width, leaf_cell, off, rg, pl.up, t, active, ntask, pl.nts, mtask,
                              pl.toff, pl.moff, tmp, totals, s));
     }
-    CK(hipMemcpyAsync(host, totals, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    CK(hipMemcpyAsync(c->hint + (side ? 4 : 0), totals, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    return pl;
+}
+
+void finish_p2p(fmm_ctx *c, P2PPlan &pl) {
+    const hipStream_t s = pl.side ? c->side : c->stream;
+    const int nl = c->nleaves;
+    const int *host = c->hint + (pl.side ? 4 : 0);
     CK(hipStreamSynchronize(s));
     pl.ntasks = host[0];
-    if (width == 64) {
+    if (pl.width == 64) {
         pl.prows = host[1];
         pl.tasks = ensure<int2>(c->ptasks, std::max(pl.ntasks, 1));
         CK(launch_p2p_tasks(nl, pl.toff, pl.tasks, s));
@@ -598,10 +618,10 @@ P2PPlan plan_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false
         pl.prows = pl.ntasks;
         pl.near = ensure<int4>(c->ptasks, std::max(pl.ntasks, 1));
         pl.entry = ensure<int2>(c->pentry, (size_t)host[1] + 64);
-        CK(launch_near_fill(nl, width, leaf_cell, off, rg, up, t, pl.nts, pl.toff, pl.moff,
+        CK(launch_near_fill(nl, pl.width, ptr<int>(c->leaf_cell), ptr<int64_t>(c->p2p_off),
+                            ptr<int2>(c->ranges), pl.up, tree_arrays(c), pl.nts, pl.toff, pl.moff,
                             pl.near, pl.entry, s));
     }
-    return pl;
 }
 
 // the direct sums of a plan, added into out4 (and the jerk into jo4)
@@ -659,11 +679,13 @@ void sink_scale(fmm_ctx *c, bool want_f, const double *eps_b) {
         c->st.n_est_p2p_pairs = L.pairs;
         uint64_t *ml = sort_list(c, c->m2l, c->m2l2, L.n_m2l, c->ncells, c->m2l_off);
         prepare_p2p(c, L.n_p2p, false);
+        P2PPlan pl = begin_p2p(c, nullptr, NEAR_R);
         double4 *Fe = ensure<double4>(c->Fe, c->ncells);
         CK(launch_est_m2l(want_f, t, c->ncells, ptr<int64_t>(c->m2l_off), ml, c->sh, Fe, s));
         double4 *e4 = ensure<double4>(c->est4, n);
         CK(launch_est_down(want_f, t, ptr<int>(c->leaf_cell), c->nleaves, Fe, e4, s));
-        exec_p2p(c, plan_p2p(c, nullptr, NEAR_R), want_f, 0, e4, false);
+        finish_p2p(c, pl);
+        exec_p2p(c, pl, want_f, 0, e4, false);
         CK(launch_scale(want_f, n, e4, scale, s));
     }
     if (eps_b) CK(launch_scale_eps(n, c->perm, eps_b, scale, s));
@@ -771,10 +793,14 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     c->st.n_m2l = L.n_m2l;
     c->st.n_p2p_lists = L.n_p2p;
     c->st.n_p2p_pairs = L.pairs;
-    // The direct-sum list is sorted and merged on the side stream while the
-    // main stream sorts the M2L list and runs M2L: M2L holds one wavefront
-    // per SIMD and no LDS, which leaves room for the sort's small waves.
+    // The direct-sum list is sorted, merged and counted on the side stream while
+    // the main stream sorts the M2L list and runs M2L and the downward pass; the
+    // host waits for its counts only after all of that is queued.
     CK(hipEventRecord(c->ev_fork, s));
+    CK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
+    const bool near32 = c->opts.precision == FMM_PREC_MIXED && !vel;
+    prepare_p2p(c, L.n_p2p, true, true);
+    P2PPlan near = begin_p2p(c, cell_active, near32 ? 64 : vel ? NEAR_JERK_R : NEAR_R, true);
     c->m2l_sorted = sort_list(c, c->m2l, c->m2l2, L.n_m2l, c->ncells, c->m2l_off);
     mark(c, PH_WALK);
     // M2L: the rotation kernel over 64-entry windows of the list, or the
@@ -801,52 +827,39 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
         if (c->opts.timing) CK(hipEventRecord(c->ev_m2l[1], s));
         CK(launch_m2l_reduce(p, c->ncells, coff, Fpart, F, s));
     } else {
-        const int chunk = 16;
         int *cnt = ensure<int>(c->ccnt, (size_t)c->ncells + 1);
         int *coff = ensure<int>(c->coff, (size_t)c->ncells + 1);
         int *tmp = tmp_ints(c, scan_tmp_ints(c->ncells + 1));
-        int *total = ptr<int>(c->nonfinite) + 1;
-        CK(launch_chunks(c->ncells, ptr<int64_t>(c->m2l_off), chunk, cnt, coff, tmp, total,
-                         nullptr, false, s));
-        CK(hipMemcpyAsync(c->hint, total, sizeof(int), hipMemcpyDeviceToHost, s));
-        sync(c);
-        const int nchunks = c->hint[0];
-        int4 *chunks = ensure<int4>(c->chunks, std::max(nchunks, 1));
-        CK(launch_chunks(c->ncells, ptr<int64_t>(c->m2l_off), chunk, cnt, coff, tmp, total,
-                         chunks, true, s));
+        const int bound = c->n_m2l > 0 ? (int)(c->n_m2l / M2L_CHUNK + c->ncells) : 0;
+        const int *nchunks = coff + c->ncells;
+        int4 *chunks = ensure<int4>(c->chunks, std::max(bound, 1));
+        CK(launch_chunks(c->ncells, ptr<int64_t>(c->m2l_off), cnt, coff, tmp, chunks, s));
         if (c->opts.precision == FMM_PREC_MIXED && p <= FMM_M2L_FIXED_MAX) {
             float *M32 = ensure<float>(c->M32, 2 * (size_t)nc * c->ncells);
-            float *Fpart = ensure<float>(c->Fpart, 2 * (size_t)nc * std::max(nchunks, 1));
-            double *sig = ensure<double>(c->sig, std::max(nchunks, 1));
+            float *Fpart = ensure<float>(c->Fpart, 2 * (size_t)nc * std::max(bound, 1));
+            double *sig = ensure<double>(c->sig, std::max(bound, 1));
             double *Flow = ensure<double>(c->Flow, 2 * (size_t)ncplx(FMM_M2L32_JLO) *
-                                                       std::max(nchunks, 1));
+                                                       std::max(bound, 1));
             CK(launch_m2l32_multipoles(p, c->ncells, t, M, M32, s));
             if (c->opts.timing) CK(hipEventRecord(c->ev_m2l[0], s));
-            CK(launch_m2l32(p, nchunks, chunks, c->m2l_sorted, c->sh, t, M, M32, Fpart, Flow, sig,
-                            s));
+            CK(launch_m2l32(p, bound, nchunks, chunks, c->m2l_sorted, c->sh, t, M, M32, Fpart, Flow,
+                            sig, s));
             if (c->opts.timing) CK(hipEventRecord(c->ev_m2l[1], s));
             CK(launch_m2l32_reduce(p, c->ncells, coff, Fpart, Flow, sig, F, s));
         } else {
-            double *Fpart = ensure<double>(c->Fpart, 2 * (size_t)nc * std::max(nchunks, 1));
+            double *Fpart = ensure<double>(c->Fpart, 2 * (size_t)nc * std::max(bound, 1));
             if (c->opts.timing) CK(hipEventRecord(c->ev_m2l[0], s));
-            CK(launch_m2l(p, nchunks, chunks, c->m2l_sorted, c->sh, t, M, Fpart, s));
+            CK(launch_m2l(p, bound, nchunks, chunks, c->m2l_sorted, c->sh, t, M, Fpart, s));
             if (c->opts.timing) CK(hipEventRecord(c->ev_m2l[1], s));
             CK(launch_m2l_reduce(p, c->ncells, coff, Fpart, F, s));
         }
         if (vel) {   // eq:M2L:dot: the same pairs applied to the rates, FP64
             double *Fd = ensure<double>(c->Fd, 2 * (size_t)nc * c->ncells);
-            double *Fp = ensure<double>(c->jFpart, 2 * (size_t)nc * std::max(nchunks, 1));
-            CK(launch_m2l(p, nchunks, chunks, c->m2l_sorted, c->sh, t, Md, Fp, s));
+            double *Fp = ensure<double>(c->jFpart, 2 * (size_t)nc * std::max(bound, 1));
+            CK(launch_m2l(p, bound, nchunks, chunks, c->m2l_sorted, c->sh, t, Md, Fp, s));
             CK(launch_m2l_reduce(p, c->ncells, coff, Fp, Fd, s));
         }
     }
-    // the direct-sum lists, on the side stream (overlapping M2L, queued above)
-    CK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-    prepare_p2p(c, L.n_p2p, true, true);
-    const bool near32 = c->opts.precision == FMM_PREC_MIXED && !vel;
-    const P2PPlan near = plan_p2p(c, cell_active, near32 ? 64 : vel ? NEAR_JERK_R : NEAR_R, true);
-    CK(hipEventRecord(c->ev_join, c->side));
-    c->join_pending = true;
     mark(c, PH_M2L);
     // downward pass, far field at the particles
     for (int Lv = 1; Lv <= c->depth; ++Lv) {
@@ -867,6 +880,9 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
                           ptr<double>(c->Fd), jo4, s, cell_active));
     }
     mark(c, PH_DOWN);
+    finish_p2p(c, near);
+    CK(hipEventRecord(c->ev_join, c->side));
+    c->join_pending = true;
     join_side(c);   // the direct-sum lists and tasks from the side stream
     // near field (with the jerk: FP64, potential and acceleration as the force-only
     // FP64 kernel sums them)
@@ -946,18 +962,27 @@ fmm_status fail(fmm_ctx *c, fmm_status st, const std::string &msg) {
     return st;
 }
 
+// a call that ended early: nothing of it stays queued on the side stream
+void settle(fmm_ctx *c) {
+    if (c->side) (void)hipStreamSynchronize(c->side);
+    c->join_pending = false;
+}
+
 template <class F>
 fmm_status guarded(fmm_ctx *c, F &&body) {
     try {
         CK(hipSetDevice(c->opts.device));
         return body();
     } catch (const HipFail &h) {
+        settle(c);
         return fail(c, FMM_E_HIP, std::string(h.what) + ": " + hipGetErrorString(h.e));
     } catch (const NoMem &m) {
+        settle(c);
         char b[128];
         std::snprintf(b, sizeof b, "device allocation of %zu bytes failed", m.bytes);
         return fail(c, FMM_E_NOMEM, b);
     } catch (...) {
+        settle(c);
         return fail(c, FMM_E_HIP, "unexpected internal error");
     }
 }

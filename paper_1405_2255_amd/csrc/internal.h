@@ -218,8 +218,9 @@ hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *
                        const WalkBuffers &wb, int launch, bool small, unsigned long long *btmp,
                        hipStream_t s);
 // offsets of the sorted (sink << sh | source) list per sink: off[c] for c in [0, nsinks]
+// (count: device, the list's length in place of nlist where not null)
 hipError_t launch_list_offsets(const uint64_t *list, int64_t nlist, int nsinks, int sh,
-                               int64_t *off, hipStream_t s);
+                               int64_t *off, hipStream_t s, const int *count = nullptr);
 // merge key-sorted direct-sum entries into maximal particle ranges per sink:
 // first call (write = false) flags and scans (flag: n + 1 ints, *total = runs);
 // second call writes range[run] = (begin, end) and rkey[run] = (sink << pb) |
@@ -229,15 +230,18 @@ hipError_t launch_range_merge(const uint64_t *key, const uint32_t *end, int64_t 
                               uint64_t *rkey, bool write, hipStream_t s);
 
 // ---- m2l.hip ------------------------------------------------------------
-// chunk table of the sink-sorted M2L list: first call (fill = false) counts the
-// chunks per cell into cnt and scans them into coff (ncells + 1 entries,
-// *total = chunks); second call (fill = true) writes chunks[] = (sink, e0, e1).
-hipError_t launch_chunks(int ncells, const int64_t *off, int chunk, int *cnt, int *coff,
-                         int *tmp, int *total, int4 *chunks, bool fill, hipStream_t s);
+// Chunk table of the sink-sorted M2L list: the chunks per cell counted into cnt
+// and scanned into coff (ncells + 1 entries, the last one the number of chunks),
+// then chunks[] = (sink, e0, e1).  A list of n entries has at most
+// n / M2L_CHUNK + ncells chunks; the M2L launchers take such a bound (it sizes the grid and the
+// buffers) and the number itself on the device.
+#define M2L_CHUNK 16
+hipError_t launch_chunks(int ncells, const int64_t *off, int *cnt, int *coff, int *tmp,
+                         int4 *chunks, hipStream_t s);
 // orders up to FMM_M2L_FIXED_MAX use register-resident kernels compiled per
 // order; higher orders (or generic = true) use the LDS-staged generic kernel
 #define FMM_M2L_FIXED_MAX 16
-hipError_t launch_m2l(int p, int nchunks, const int4 *chunks, const uint64_t *list, int sh,
+hipError_t launch_m2l(int p, int bound, const int *nchunks, const int4 *chunks, const uint64_t *list, int sh,
                       const TreeArrays &t, const double *M, double *Fpart, hipStream_t s,
                       bool generic = false);
 // Mixed precision (orders up to FMM_M2L_FIXED_MAX): scaled FP32 multipoles,
@@ -247,7 +251,7 @@ hipError_t launch_m2l(int p, int nchunks, const int4 *chunks, const uint64_t *li
 #define FMM_M2L32_JLO 3
 hipError_t launch_m2l32_multipoles(int p, int ncells, const TreeArrays &t, const double *M,
                                    float *M32, hipStream_t s);
-hipError_t launch_m2l32(int p, int nchunks, const int4 *chunks, const uint64_t *list, int sh,
+hipError_t launch_m2l32(int p, int bound, const int *nchunks, const int4 *chunks, const uint64_t *list, int sh,
                         const TreeArrays &t, const double *M, const float *M32, float *Fpart,
                         double *Flow, double *sig, hipStream_t s);
 hipError_t launch_m2l32_reduce(int p, int ncells, const int *coff, const float *Fpart,

@@ -17,14 +17,14 @@
 
 namespace fmm {
 #define FMM_M2L_FIXED_DECL(P)                                                                  \
-    hipError_t launch_m2l_fixed_##P(int, const int4 *, const uint64_t *, uint64_t, const TreeArrays &, \
-                                    const double *, double *, hipStream_t);
+    hipError_t launch_m2l_fixed_##P(int, const int *, const int4 *, const uint64_t *, uint64_t,  \
+                                    const TreeArrays &, const double *, double *, hipStream_t);
 FMM_M2L_FIXED_DECL(1) FMM_M2L_FIXED_DECL(2) FMM_M2L_FIXED_DECL(3) FMM_M2L_FIXED_DECL(4)
 FMM_M2L_FIXED_DECL(5) FMM_M2L_FIXED_DECL(6) FMM_M2L_FIXED_DECL(7) FMM_M2L_FIXED_DECL(8)
 FMM_M2L_FIXED_DECL(9) FMM_M2L_FIXED_DECL(10) FMM_M2L_FIXED_DECL(11) FMM_M2L_FIXED_DECL(12)
 FMM_M2L_FIXED_DECL(13) FMM_M2L_FIXED_DECL(14) FMM_M2L_FIXED_DECL(15) FMM_M2L_FIXED_DECL(16)
 #define FMM_M2L32_FIXED_DECL(P)                                                                \
-    hipError_t launch_m2l32_fixed_##P(int, const int4 *, const uint64_t *, uint64_t,            \
+    hipError_t launch_m2l32_fixed_##P(int, const int *, const int4 *, const uint64_t *, uint64_t, \
                                       const TreeArrays &, const double *, const float *, float *, \
                                       double *, double *, hipStream_t);
 FMM_M2L32_FIXED_DECL(1) FMM_M2L32_FIXED_DECL(2) FMM_M2L32_FIXED_DECL(3) FMM_M2L32_FIXED_DECL(4)
@@ -42,12 +42,12 @@ namespace {
 // by the recurrence in App. A.5) into LDS while the others stage M_A; then
 // thread o accumulates output coefficient o = tri(n, m) from LDS.
 __global__ void __launch_bounds__(256)
-k_m2l_generic(int p, int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask,
+k_m2l_generic(int p, const int *nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask,
               TreeArrays t, const double *M, double *Fpart) {
     __shared__ cplx th[tri(FMM_PMAX + 1, 0)];
     __shared__ cplx ma[tri(FMM_PMAX + 1, 0)];
     const int ch = blockIdx.x;
-    if (ch >= nchunks) return;
+    if (ch >= *nchunks) return;
     const int4 c = chunks[ch];
     const int nc = tri(p + 1, 0);
     const int o = threadIdx.x;
@@ -187,33 +187,32 @@ inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-hipError_t launch_chunks(int ncells, const int64_t *off, int chunk, int *cnt, int *coff,
-                         int *tmp, int *total, int4 *chunks, bool fill, hipStream_t s) {
-    if (!fill) {
-        hipLaunchKernelGGL(k_chunk_count, dim3(blocks(ncells + 1, 256)), dim3(256), 0, s, ncells,
-                           off, chunk, cnt);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        // coff has ncells + 1 entries: cnt[ncells] must be 0
-        return exclusive_scan(cnt, coff, ncells + 1, tmp, total, s);
-    }
+hipError_t launch_chunks(int ncells, const int64_t *off, int *cnt, int *coff, int *tmp,
+                         int4 *chunks, hipStream_t s) {
+    hipLaunchKernelGGL(k_chunk_count, dim3(blocks(ncells + 1, 256)), dim3(256), 0, s, ncells, off,
+                       M2L_CHUNK, cnt);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // coff has ncells + 1 entries: cnt[ncells] must be 0
+    e = exclusive_scan(cnt, coff, ncells + 1, tmp, nullptr, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_chunk_fill, dim3(blocks(ncells, 256)), dim3(256), 0, s, ncells, off,
-                       chunk, coff, chunks);
+                       M2L_CHUNK, coff, chunks);
     return hipGetLastError();
 }
 
-hipError_t launch_m2l(int p, int nchunks, const int4 *chunks, const uint64_t *list, int sh,
+hipError_t launch_m2l(int p, int bound, const int *nchunks, const int4 *chunks, const uint64_t *list, int sh,
                       const TreeArrays &t, const double *M, double *Fpart, hipStream_t s,
                       bool generic) {
-    if (nchunks <= 0) return hipSuccess;
+    if (bound <= 0) return hipSuccess;
     if (p < 1 || p > FMM_PMAX) return hipErrorInvalidValue;
     const uint64_t mask = (1ull << sh) - 1;
     if (generic || p > FMM_M2L_FIXED_MAX) {
-        hipLaunchKernelGGL(k_m2l_generic, dim3(nchunks), dim3(256), 0, s, p, nchunks, chunks, list,
+        hipLaunchKernelGGL(k_m2l_generic, dim3(bound), dim3(256), 0, s, p, nchunks, chunks, list,
                            mask, t, M, Fpart);
         return hipGetLastError();
     }
-#define CALL(P) return launch_m2l_fixed_##P(nchunks, chunks, list, mask, t, M, Fpart, s)
+#define CALL(P) return launch_m2l_fixed_##P(bound, nchunks, chunks, list, mask, t, M, Fpart, s)
     switch (p) {
     case 1: CALL(1);   case 2: CALL(2);   case 3: CALL(3);   case 4: CALL(4);
     case 5: CALL(5);   case 6: CALL(6);   case 7: CALL(7);   case 8: CALL(8);
@@ -244,13 +243,13 @@ hipError_t launch_m2l32_multipoles(int p, int ncells, const TreeArrays &t, const
     return hipGetLastError();
 }
 
-hipError_t launch_m2l32(int p, int nchunks, const int4 *chunks, const uint64_t *list, int sh,
+hipError_t launch_m2l32(int p, int bound, const int *nchunks, const int4 *chunks, const uint64_t *list, int sh,
                         const TreeArrays &t, const double *M, const float *M32, float *Fpart,
                         double *Flow, double *sig, hipStream_t s) {
-    if (nchunks <= 0) return hipSuccess;
+    if (bound <= 0) return hipSuccess;
     const uint64_t mask = (1ull << sh) - 1;
 #define CALL(P)                                                                                \
-    return launch_m2l32_fixed_##P(nchunks, chunks, list, mask, t, M, M32, Fpart, Flow, sig, s)
+    return launch_m2l32_fixed_##P(bound, nchunks, chunks, list, mask, t, M, M32, Fpart, Flow, sig, s)
     switch (p) {
     case 1: CALL(1);   case 2: CALL(2);   case 3: CALL(3);   case 4: CALL(4);
     case 5: CALL(5);   case 6: CALL(6);   case 7: CALL(7);   case 8: CALL(8);

@@ -187,10 +187,10 @@ __device__ __forceinline__ void m2l32_passes(int pass, int B, int e0, int e1, do
 // from this one's by nearly 1e-9 of the forces.)
 template <int P>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-k_m2l32(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, TreeArrays t,
+k_m2l32(const int *nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, TreeArrays t,
         const double *M, const float *M32, float *Fpart, double *Flow, double *sig) {
-    const int ch = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (ch >= nchunks) return;
+    const int ch = m2l_detail::my_chunk(*nchunks);
+    if (ch < 0) return;
     const int4 c = chunks[ch];
     if (blockIdx.y == pass_count32(P)) {
         constexpr int JL = P < M2L32_JLO ? P : M2L32_JLO;
@@ -219,12 +219,13 @@ k_m2l32(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, Tr
 
 #define FMM_M2L32_FIXED_DEFINE(P)                                                            \
     namespace fmm {                                                                          \
-    hipError_t launch_m2l32_fixed_##P(int nchunks, const int4 *chunks, const uint64_t *list, \
-                                      uint64_t mask, const TreeArrays &t, const double *M,   \
-                                      const float *M32, float *Fpart, double *Flow,          \
+    hipError_t launch_m2l32_fixed_##P(int bound, const int *nchunks, const int4 *chunks,  \
+                                      const uint64_t *list, uint64_t mask,                   \
+                                      const TreeArrays &t, const double *M, const float *M32, \
+                                      float *Fpart, double *Flow,          \
                                       double *sig, hipStream_t s) {                          \
         hipLaunchKernelGGL(m2l32_detail::k_m2l32<P>,                                         \
-                           dim3(m2l_detail::m2l_blocks(nchunks),                             \
+                           dim3(m2l_detail::m2l_blocks(bound),                                \
                                 m2l32_detail::pass_count32(P) + 1),                          \
                            dim3(64), 0, s, nchunks, chunks, list, mask, t, M, M32, Fpart,    \
                            Flow, sig);                                                       \

@@ -221,26 +221,35 @@ __device__ __forceinline__ void m2l_passes(int pass, int B, int e0, int e1, cons
         m2l_passes<P, N1 + 1>(pass - 1, B, e0, e1, list, mask, t, M, out);
 }
 
+// blocks of 64 chunks, rounded up to the XCD count
+__host__ __device__ constexpr int m2l_blocks(int nchunks) {
+    return ((nchunks + 63) / 64 + FMM_NXCD - 1) / FMM_NXCD * FMM_NXCD;
+}
+
+// the chunk of this lane, or -1.  The grid is sized by a bound of the chunk
+// count; each XCD takes a contiguous eighth of the blocks that hold chunks.
+__device__ __forceinline__ int my_chunk(int nchunks) {
+    const int nb = m2l_blocks(nchunks);
+    if ((int)blockIdx.x >= nb) return -1;
+    const int ch = xcd_block(blockIdx.x, nb) * 64 + threadIdx.x;
+    return ch < nchunks ? ch : -1;
+}
+
 // One lane per chunk and pass: the grid's y dimension takes the passes, so that
 // a short list still has several wavefronts per 64 chunks.  gridDim.x is a
 // multiple of the XCD count, so that a chunk's passes share an L2.
 template <int P>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-k_m2l(int nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, TreeArrays t,
+k_m2l(const int *nchunks, const int4 *chunks, const uint64_t *list, uint64_t mask, TreeArrays t,
       const double *M, double *Fpart) {
-    const int ch = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (ch >= nchunks) return;
+    const int ch = my_chunk(*nchunks);
+    if (ch < 0) return;
     const int4 c = chunks[ch];
     cplx *out = reinterpret_cast<cplx *>(Fpart) + (size_t)ch * tri(P + 1, 0);
     m2l_passes<P, 0>(blockIdx.y, c.x, c.y, c.z, list, mask, t, reinterpret_cast<const cplx *>(M),
                      out);
 }
 
-// blocks of 64 chunks, rounded up to the XCD count
-inline unsigned m2l_blocks(int nchunks) {
-    const unsigned b = (unsigned)((nchunks + 63) / 64);
-    return (b + FMM_NXCD - 1) / FMM_NXCD * FMM_NXCD;
-}
 
 }  // namespace m2l_detail
 }  // namespace fmm
@@ -248,11 +257,11 @@ inline unsigned m2l_blocks(int nchunks) {
 // launcher of the order-P register kernel (defined in the m2l_p*.hip units)
 #define FMM_M2L_FIXED_DEFINE(P)                                                              \
     namespace fmm {                                                                          \
-    hipError_t launch_m2l_fixed_##P(int nchunks, const int4 *chunks, const uint64_t *list,   \
-                                    uint64_t mask, const TreeArrays &t, const double *M,     \
-                                    double *Fpart, hipStream_t s) {                          \
+    hipError_t launch_m2l_fixed_##P(int bound, const int *nchunks, const int4 *chunks,    \
+                                    const uint64_t *list, uint64_t mask, const TreeArrays &t, \
+                                    const double *M, double *Fpart, hipStream_t s) {         \
         hipLaunchKernelGGL(m2l_detail::k_m2l<P>,                                             \
-                           dim3(m2l_detail::m2l_blocks(nchunks), m2l_detail::pass_count(P)), \
+                           dim3(m2l_detail::m2l_blocks(bound), m2l_detail::pass_count(P)),   \
                            dim3(64), 0, s, nchunks, chunks, list, mask, t, M, Fpart);       \
         return hipGetLastError();                                                            \
     }                                                                                        \

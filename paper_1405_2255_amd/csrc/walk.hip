@@ -455,11 +455,12 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
     cnt[2] = cnt[WALK_CUM + 3 * sweep + 2] = pairs0 + (unsigned long long)pairs;
 }
 
-__global__ void k_list_offsets(const uint64_t *list, int64_t nlist, int nsinks, int sh,
-                               int64_t *off) {
-    // list sorted by key; the sink is key >> sh
+__global__ void k_list_offsets(const uint64_t *list, int64_t nlist, const int *count, int nsinks,
+                               int sh, int64_t *off) {
+    // list sorted by key; the sink is key >> sh; its length is *count where given
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s > nsinks) return;
+    if (count) nlist = *count;
     // first entry whose sink is >= s
     int64_t lo = 0, hi = nlist;
     while (lo < hi) {
@@ -567,9 +568,9 @@ hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *
 }
 
 hipError_t launch_list_offsets(const uint64_t *list, int64_t nlist, int nsinks, int sh,
-                               int64_t *off, hipStream_t s) {
+                               int64_t *off, hipStream_t s, const int *count) {
     hipLaunchKernelGGL(k_list_offsets, dim3(blocks(nsinks + 1, 256)), dim3(256), 0, s, list, nlist,
-                       nsinks, sh, off);
+                       count, nsinks, sh, off);
     return hipGetLastError();
 }
 
