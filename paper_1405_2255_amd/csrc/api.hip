@@ -129,7 +129,7 @@ struct fmm_ctx {
         tmp_side;
     uint32_t *perm = nullptr;  // points into idx or idx2
     // cells
-    DevBuf beg, end, parent, child0, nchild, level, leaf_lo, leaf_hi, cen, com, mass, lo, hi,
+    DevBuf beg, end, parent, child0, nchild, level, leaf_lo, leaf_hi, info, cen, com, mass, lo, hi,
         rho2, bsph, smin, leaf_cell, M, F, P, U, Fe;
     // walk
     DevBuf fa, fb, m2l, m2l2, p2p, p2p2, p2pe, p2pe2, m2l_off, p2p_off, chunks, ccnt, coff, Fpart;
@@ -187,6 +187,7 @@ TreeArrays tree_arrays(fmm_ctx *c) {
     t.beg = ptr<int>(c->beg); t.end = ptr<int>(c->end); t.parent = ptr<int>(c->parent);
     t.child0 = ptr<int>(c->child0); t.nchild = ptr<int>(c->nchild); t.level = ptr<int>(c->level);
     t.leaf_lo = ptr<int>(c->leaf_lo); t.leaf_hi = ptr<int>(c->leaf_hi);
+    t.info = ptr<int4>(c->info);
     t.cen = ptr<double4>(c->cen); t.com = ptr<double4>(c->com); t.mass = ptr<double>(c->mass);
     t.lo = ptr<double>(c->lo); t.hi = ptr<double>(c->hi);
     t.rho2 = ptr<unsigned long long>(c->rho2); t.smin = ptr<double>(c->smin);
@@ -340,6 +341,7 @@ void build_tree(fmm_ctx *c, int64_t n, const double *pos, const double *mass, in
     c->pb = std::max(1, bitlen((uint64_t)n));
     c->pack = c->sh + 2 * c->pb <= 64;
     ensure<int>(c->leaf_lo, ncells); ensure<int>(c->leaf_hi, ncells);
+    ensure<int4>(c->info, ncells);
     ensure<double4>(c->cen, ncells); ensure<double4>(c->com, ncells);
     ensure<double>(c->mass, ncells); ensure<double>(c->lo, 3 * (size_t)ncells);
     ensure<double>(c->hi, 3 * (size_t)ncells); ensure<unsigned long long>(c->rho2, 3 * (size_t)ncells);
@@ -425,9 +427,6 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
     wp.sh = c->sh;
     wp.pb = c->pb;
     wp.pack = c->pack;
-    wp.binom[0] = 1.0;
-    for (int k = 1; k <= std::min(wp.p, FMM_PMAX); ++k)
-        wp.binom[k] = wp.binom[k - 1] * (double)(wp.p - k + 1) / (double)k;
     const int64_t n = c->n;
     // every sweep descends one level in A or in B
     const int sweeps = 2 * c->depth + 4;
@@ -671,7 +670,7 @@ void sink_scale(fmm_ctx *c, bool want_f, const double *eps_b) {
         done = true;
     }
     if (!done) {
-        WalkParams wp{2, 1, 0.0, 1.0, 0.0, 0, 0, 0, {}};
+        WalkParams wp{2, 1, 0.0, 1.0, 0.0, 0, 0, 0};
         Lists L = walk(c, wp, nullptr);
         c->st.est_walk_pairs = c->last_walk_pairs;
         c->st.t_est_sweeps = c->last_sweep_ms;
@@ -742,7 +741,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     const int nc = ncplx(p);
     double *M = ensure<double>(c->M, 2 * (size_t)nc * c->ncells);
     double *U = ensure<double>(c->U, 2 * (size_t)nc * c->ncells);
-    double *P = ensure<double>(c->P, (size_t)(p + 1) * c->ncells);
+    double *P = ensure<double>(c->P, (size_t)power_stride(p) * c->ncells);
     short *plans = ensure<short>(c->plans, 2 * XP_SIZE);
     double *Tsh = ensure<double>(c->Tsh, 2 * (size_t)nc * c->ncells);
     double4 *v4 = vel ? ensure<double4>(c->vel4, n + NEAR_PAD) : nullptr;
@@ -781,7 +780,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     mark(c, PH_UP);
     // walk
     WalkParams wp{c->opts.mac == FMM_MAC_THETA ? 1 : 0, p, eps, c->opts.theta_crit,
-                  c->opts.p2p_factor * (p + 1.0) * (p + 1.0) * (p + 1.0), 0, 0, 0, {}};
+                  c->opts.p2p_factor * (p + 1.0) * (p + 1.0) * (p + 1.0), 0, 0, 0};
     wp.active = cell_active;
     if (eps_b) wp.eps = 1.0;      // eps_b is in the cell minimum of the scale
     Lists L = walk(c, wp, P);
@@ -1087,7 +1086,7 @@ void fmm_destroy(fmm_ctx *c) {
     DevBuf *bufs[] = {&c->bbox, &c->key, &c->key2, &c->idx, &c->idx2, &c->x, &c->y, &c->z, &c->m,
                       &c->xyzm, &c->leaf_of, &c->out4, &c->est4, &c->scale, &c->flags, &c->tmp,
                       &c->beg, &c->end, &c->parent, &c->child0, &c->nchild, &c->level,
-                      &c->leaf_lo, &c->leaf_hi, &c->cen, &c->com, &c->mass, &c->lo, &c->hi,
+                      &c->leaf_lo, &c->leaf_hi, &c->info, &c->cen, &c->com, &c->mass, &c->lo, &c->hi,
                       &c->rho2, &c->bsph, &c->smin, &c->leaf_cell, &c->M, &c->F, &c->P, &c->U, &c->Fe,
                       &c->fa, &c->fb, &c->m2l, &c->m2l2, &c->p2p, &c->p2p2, &c->p2pe,
                       &c->p2pe2, &c->rflag, &c->ranges, &c->rkey, &c->pt_n, &c->pt_m,

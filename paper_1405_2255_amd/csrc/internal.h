@@ -31,6 +31,7 @@ hipError_t radix_sort(uint64_t **keys, uint64_t **keys_alt, uint32_t **vals,
 struct TreeArrays {
     int *beg, *end, *parent, *child0, *nchild, *level;
     int *leaf_lo, *leaf_hi;     // leaves [leaf_lo, leaf_hi) in Morton leaf order
+    int4 *info;                 // (begin, end, first child, child count) for the walk
     double4 *cen;               // (x, y, z, rho): expansion centre z = s, radius
     double4 *com;               // (x, y, z, rho_com): centre of mass, radius about it
     double *mass;
@@ -156,6 +157,8 @@ void translation_plans(int p, short *m2m, short *l2l);
 // roots).  Run from the deepest level up to level 0.
 hipError_t launch_m2m_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
                             double *M, double *T, const short *plan, hipStream_t s);
+// C(p, n) P_n per cell, rows of power_stride(p) doubles (16-byte aligned)
+inline __host__ __device__ int power_stride(int p) { return (p + 2) & ~1; }
 hipError_t launch_power(int p, int ncells, const double *M, double *P, hipStream_t s);
 // (active: when not null, cells / leaves without listed sinks are skipped)
 hipError_t launch_l2l_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
@@ -183,7 +186,6 @@ struct WalkParams {
     int nroots;        // the walk starts from (r, r) for every root r < nroots
     int sh;            // M2L keys are (sink << sh) | source cell
     int pb;            // direct-sum keys are (sink << pb) | first source particle
-    double binom[FMM_PMAX + 1];   // C(p, k)
     int pack;          // nonzero: direct-sum keys carry the range end too,
                        // (sink << 2pb) | (first << pb) | end (needs sh + 2 pb <= 64)
     const uint8_t *active;   // not null: pairs whose sink cell holds no listed

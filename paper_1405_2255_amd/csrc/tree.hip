@@ -462,7 +462,9 @@ __global__ void k_leaf_ranges(TreeArrays t, int ncells, const int *scan, int *le
     const int lo = scan[t.beg[c]], hi = scan[t.end[c]];
     t.leaf_lo[c] = lo;
     t.leaf_hi[c] = hi;
-    if (t.nchild[c] == 0) leaf_cell[lo] = c;
+    const int nch = t.nchild[c];
+    t.info[c] = make_int4(t.beg[c], t.end[c], t.child0[c], nch);
+    if (nch == 0) leaf_cell[lo] = c;
 }
 
 __global__ void k_leaf_of(const int *scan, int64_t n, int *leaf_of) {

@@ -44,10 +44,11 @@ struct Decision {
 __device__ __forceinline__ Decision decide(const WalkParams &wp, const TreeArrays &t,
                                            const double *P, int A, int B) {
     if (wp.active && !wp.active[B]) return {0, 0, 0.0};   // no listed sink below B
-    const int nchA = t.nchild[A], nchB = t.nchild[B];
+    const int4 ia = t.info[A], ib = t.info[B];
+    const int nchA = ia.w, nchB = ib.w;
     if (A == B) {
         if (nchA == 0) {
-            const double na = (double)(t.end[A] - t.beg[A]);
+            const double na = (double)(ia.y - ia.x);
             return {4, 0, na * (na - 1.0)};
         }
         return {1, nchA * nchA, 0.0};
@@ -61,21 +62,26 @@ __device__ __forceinline__ Decision decide(const WalkParams &wp, const TreeArray
     bool acc = rA + rB < tc * r;
     if (acc && wp.mode == 0) {
         // Etilde M_A = 8 max/(sum) * sum_k C(p,k) P_k rho_B^{p-k} / r^p, by Horner
-        // in q = rho_B / r
+        // in q = rho_B / r (the rows hold C(p,k) P_k).  The lanes read different
+        // cells, so each load visits the L1 cache once per lane, and these
+        // visits are what the sweeps cost: two coefficients per load.
         const int p = wp.p;
-        const double *Pa = P + (size_t)A * (p + 1);
+        const double2 *Pa = reinterpret_cast<const double2 *>(P + (size_t)A * power_stride(p));
         const double u = 1.0 / r, q = rB * u;
-        double S = Pa[0], up = 1.0;
+        double2 v = Pa[0];
+        double S = v.x, up = 1.0;
+#pragma unroll 4
         for (int k = 1; k <= p; ++k) {
+            if (k % 2 == 0) v = Pa[k / 2];
             up *= u;
-            S = fma(S, q, wp.binom[k] * Pa[k] * up);
+            S = fma(S, q, (k % 2 ? v.y : v.x) * up);
         }
         const double sum = rA + rB;
         const double fac = sum > 0.0 ? 8.0 * fmax(rA, rB) / sum : 8.0;
         acc = fac * S * u * u < wp.eps * t.smin[B];
     }
-    const double na = (double)(t.end[A] - t.beg[A]);
-    const double nb = (double)(t.end[B] - t.beg[B]);
+    const double na = (double)(ia.y - ia.x);
+    const double nb = (double)(ib.y - ib.x);
     if (acc) {
         if (wp.mode != 2 && na * nb < wp.p2p_pairs) return {4, 0, na * nb};
         return {5, 0, 0.0};
@@ -244,9 +250,10 @@ __device__ __forceinline__ void walk_offsets(const unsigned long long *btot, boo
 // the outputs of one pair (A, B): frontier pairs from pf on, or the M2L entry
 // pm, or the direct-sum entry pp (dropped past the buffers' ends)
 __device__ __forceinline__ void write_outputs(const WalkParams &wp, const WalkBuffers &wb,
-                                              uint2 *out, int kind, int n, int A, int B, int kA,
-                                              int kB, int nchA, int begA, int endA, int64_t pf,
-                                              int64_t pm, int64_t pp) {
+                                              uint2 *out, int kind, int n, int A, int B,
+                                              int4 ia, int4 ib, int64_t pf, int64_t pm,
+                                              int64_t pp) {
+    const int begA = ia.x, endA = ia.y, kA = ia.z, nchA = ia.w, kB = ib.z;
     switch (kind) {
     case 1:     // all ordered daughter pairs of A
         if (pf + n <= wb.cap_out)
@@ -325,15 +332,11 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
             kind[r] = (int)(code & 7u);
             nf[r] = (int)(code >> 3);
         }
-        int kA[WALK_WBATCH], kB[WALK_WBATCH], nchA[WALK_WBATCH], begA[WALK_WBATCH],
-            endA[WALK_WBATCH];
+        int4 ia[WALK_WBATCH], ib[WALK_WBATCH];
 #pragma unroll
         for (int r = 0; r < WALK_WBATCH; ++r) {
-            kA[r] = t.child0[A[r]];
-            kB[r] = t.child0[B[r]];
-            nchA[r] = t.nchild[A[r]];
-            begA[r] = t.beg[A[r]];
-            endA[r] = t.end[A[r]];
+            ia[r] = t.info[A[r]];
+            ib[r] = t.info[B[r]];
         }
 #pragma unroll
         for (int r = 0; r < WALK_WBATCH; ++r) {
@@ -344,8 +347,7 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
             block_scan3(sf, sm, sp, tot);
             const int64_t pf = of + sf - n, pm = om + sm - (k == 5), pp = op + sp - (k == 4);
             const int a0 = A[r], b0 = B[r];
-            write_outputs(wp, wb, out, k, n, a0, b0, kA[r], kB[r], nchA[r], begA[r], endA[r], pf,
-                          pm, pp);
+            write_outputs(wp, wb, out, k, n, a0, b0, ia[r], ib[r], pf, pm, pp);
             of += tot[0];
             om += tot[1];
             op += tot[2];
@@ -428,9 +430,9 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
             if (kind[r] == 0) continue;
             const unsigned long long o = ws[r * SMALL_WAVES + w] + incl[r] - c[r];
             const int a = A[r], b = B[r];
-            write_outputs(wp, wb, out, kind[r], nf[r], a, b, t.child0[a], t.child0[b],
-                          t.nchild[a], t.beg[a], t.end[a], (int64_t)(o & 0xffffffu),
-                          (int64_t)(m0 + ((o >> 24) & 0xfffffu)), (int64_t)(p0 + (o >> 44)));
+            write_outputs(wp, wb, out, kind[r], nf[r], a, b, t.info[a], t.info[b],
+                          (int64_t)(o & 0xffffffu), (int64_t)(m0 + ((o >> 24) & 0xfffffu)),
+                          (int64_t)(p0 + (o >> 44)));
         }
         n_in = (int64_t)(total & 0xffffffu);
         m0 += (total >> 24) & 0xfffffu;
