@@ -138,7 +138,7 @@ struct fmm_ctx {
     DevBuf counters, nonfinite, walktmp, coffsets, ckey, ckey2, order, order2;
     DevBuf actflag, actf, actinv, actpre, cellact, actbad;   // forces for a listed subset
     DevBuf epsmin;                                           // smallest individual eps
-    DevBuf vel4, Md, Fd, jFpart, jo4, jpart;   // jerk: velocities, rates of M and F, M2L
+    DevBuf vel4, Md, Fd, jFpart, jo4, jfar4, jpart;   // jerk: velocities, rates of M and F, M2L
                                                // chunk parts of the rates, jerk per
                                                // particle, direct-sum partial rows
     DevBuf dkey, dsort, dsort2, runstart;   // deep refinement below level 21
@@ -623,10 +623,11 @@ void finish_p2p(fmm_ctx *c, P2PPlan &pl) {
     }
 }
 
-// the direct sums of a plan, added into out4 (and the jerk into jo4)
+// the direct sums of a plan, added into out4 (and the jerk into jo4), on the
+// plan's stream
 void exec_p2p(fmm_ctx *c, const P2PPlan &pl, int want_f, int with_pot, double4 *out4, bool timed,
               const double4 *v4 = nullptr, double4 *jo4 = nullptr) {
-    hipStream_t s = c->stream;
+    const hipStream_t s = pl.side ? c->side : c->stream;
     TreeArrays t = tree_arrays(c);
     const int *leaf_cell = ptr<int>(c->leaf_cell), *leaf_of = ptr<int>(c->leaf_of);
     const double4 *xyzm = ptr<double4>(c->xyzm);
@@ -792,9 +793,13 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     c->st.n_m2l = L.n_m2l;
     c->st.n_p2p_lists = L.n_p2p;
     c->st.n_p2p_pairs = L.pairs;
-    // The direct-sum list is sorted, merged and counted on the side stream while
-    // the main stream sorts the M2L list and runs M2L and the downward pass; the
-    // host waits for its counts only after all of that is queued.
+    // The near field is the side stream's: its list is sorted, merged and counted
+    // and its sums run while the main stream sorts the M2L list and runs M2L and
+    // the downward pass.  The levels' chain leaves most of the device idle, and
+    // the direct sums fill it (3e5 bodies refitted 6.83 -> 6.52 ms, 2e5 with jerk
+    // 8.05 -> 7.65, 1e4 listed of 1e6 2.45 -> 2.33); the two fields meet in the
+    // output kernel.  The host waits for the direct sums' counts only after
+    // everything else is queued.
     CK(hipEventRecord(c->ev_fork, s));
     CK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
     const bool near32 = c->opts.precision == FMM_PREC_MIXED && !vel;
@@ -868,35 +873,41 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
             CK(launch_l2l_level(p, t, c->ls[Lv], c->ls[Lv + 1], U, ptr<double>(c->Fd),
                                 ptr<short>(c->plans) + XP_SIZE, s, cell_active));
     }
-    double4 *o4 = ensure<double4>(c->out4, n);
+    double4 *far4 = ensure<double4>(c->est4, n);   // (the estimate is in smin by now)
     CK(launch_l2p(p, t, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), n, ptr<double>(c->x),
-                  ptr<double>(c->y), ptr<double>(c->z), F, o4, s, cell_active));
-    double4 *jo4 = nullptr;
+                  ptr<double>(c->y), ptr<double>(c->z), F, far4, s, cell_active));
+    double4 *jfar4 = nullptr;
     if (vel) {   // eq:L2P:dot, assigns the far-field jerk of every particle
-        jo4 = ensure<double4>(c->jo4, n);
+        jfar4 = ensure<double4>(c->jfar4, n);
         CK(launch_l2p_dot(p, t, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), n,
                           ptr<double>(c->x), ptr<double>(c->y), ptr<double>(c->z), v4, F,
-                          ptr<double>(c->Fd), jo4, s, cell_active));
+                          ptr<double>(c->Fd), jfar4, s, cell_active));
     }
     mark(c, PH_DOWN);
-    finish_p2p(c, near);
-    CK(hipEventRecord(c->ev_join, c->side));
-    c->join_pending = true;
-    join_side(c);   // the direct-sum lists and tasks from the side stream
     // near field (with the jerk: FP64, potential and acceleration as the force-only
     // FP64 kernel sums them)
+    finish_p2p(c, near);
+    double4 *o4 = ensure<double4>(c->out4, n), *jo4 = nullptr;
+    CK(launch_zero(o4, n, c->side));
+    if (vel) {
+        jo4 = ensure<double4>(c->jo4, n);
+        CK(launch_zero(jo4, n, c->side));
+    }
     exec_p2p(c, near, 0, 1, o4, true, v4, jo4);
+    CK(hipEventRecord(c->ev_join, c->side));
+    c->join_pending = true;
+    join_side(c);
     mark(c, PH_P2P);
     int *nonfinite = ptr<int>(c->nonfinite);
     CK(hipMemsetAsync(nonfinite, 0, sizeof(int), s));
     if (act)
-        CK(launch_output_listed(n, nact, act, inv, o4, G, pot, acc, nonfinite, s));
+        CK(launch_output_listed(n, nact, act, inv, far4, o4, G, pot, acc, nonfinite, s));
     else
-        CK(launch_output(n, c->perm, o4, G, pot, acc, nonfinite, s));
+        CK(launch_output(n, c->perm, far4, o4, G, pot, acc, nonfinite, s));
     if (vel && act)
-        CK(launch_output_jerk_listed(n, nact, act, inv, jo4, G, jerk, nonfinite, s));
+        CK(launch_output_jerk_listed(n, nact, act, inv, jfar4, jo4, G, jerk, nonfinite, s));
     else if (vel)
-        CK(launch_output_jerk(n, c->perm, jo4, G, jerk, nonfinite, s));
+        CK(launch_output_jerk(n, c->perm, jfar4, jo4, G, jerk, nonfinite, s));
     if (c->opts.scale_source == FMM_SCALE_PREVIOUS && !act) {
         CK(launch_norm3(acc, n, G, ensure<double>(c->prev_scale, n), s));
         c->have_prev_scale = true;
@@ -1097,7 +1108,7 @@ void fmm_destroy(fmm_ctx *c) {
                       &c->actflag, &c->actf, &c->actinv, &c->actpre, &c->cellact, &c->actbad,
                       &c->dkey, &c->dsort, &c->dsort2, &c->runstart, &c->plans, &c->Tsh,
                       &c->M32, &c->sig, &c->Flow, &c->epsmin, &c->vel4, &c->Md, &c->Fd,
-                      &c->jFpart, &c->jo4, &c->jpart, &c->dspart, &c->tg, &c->tpre, &c->tsuf,
+                      &c->jFpart, &c->jo4, &c->jfar4, &c->jpart, &c->dspart, &c->tg, &c->tpre, &c->tsuf,
                       &c->tcell, &c->tcell2, &c->tls};
     for (DevBuf *b : bufs)
         if (b->p) (void)hipFree(b->p);

@@ -332,8 +332,11 @@ hipError_t launch_p2p_mixed(int ntasks, const int2 *tasks, const int *leaf_cell,
 hipError_t launch_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell,
                              const int *nsrc_tasks, const int *moff, const TreeArrays &t,
                              const double4 *partial, double4 *out4, hipStream_t s);
-hipError_t launch_output(int64_t n, const uint32_t *perm, const double4 *out4, double G,
-                         double *pot, double *acc, int *nonfinite, hipStream_t s);
+// pot, acc of every particle from its far and near field (sorted order)
+hipError_t launch_output(int64_t n, const uint32_t *perm, const double4 *far4,
+                         const double4 *near4, double G, double *pot, double *acc,
+                         int *nonfinite, hipStream_t s);
+hipError_t launch_zero(double4 *p, int64_t n, hipStream_t s);
 // forces for a listed subset of sinks (Sec. 7.1): flag_in (n ints, zeroed by the
 // caller) marks the listed input indices, *bad = 1 if one is outside [0, n);
 // then per sorted position f (n + 1), inv (input -> sorted, n), the exclusive
@@ -352,8 +355,8 @@ hipError_t launch_eps_min(int64_t n, const double *eps_b, unsigned long long *mi
 hipError_t launch_scale_eps(int64_t n, const uint32_t *perm, const double *eps_b, double *scale,
                            hipStream_t s);
 hipError_t launch_output_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                const double4 *out4, double G, double *pot, double *acc,
-                                int *nonfinite, hipStream_t s);
+                                const double4 *far4, const double4 *near4, double G,
+                                double *pot, double *acc, int *nonfinite, hipStream_t s);
 hipError_t launch_scale(int want_f, int64_t n, const double4 *est4, double *scale,
                         hipStream_t s);
 // Exact sums for listed sinks (sinks null: nsinks = n, every particle; an index

@@ -41,10 +41,12 @@ hipError_t launch_direct_jerk_sinks(int64_t n, const double *pos, const double *
                                    int *bad, hipStream_t s);
 // listed sinks (input indices act[j], inverse permutation inv): jerk in list order
 hipError_t launch_output_jerk_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                     const double4 *jo4, double G, double *jerk, int *nonfinite,
+                                     const double4 *far4, const double4 *jo4, double G,
+                                     double *jerk, int *nonfinite,
                                      hipStream_t s);
-// jerk[3 perm[i] + d] = G jo4[i].(y, z, w); *nonfinite = 1 on a non-finite value
-hipError_t launch_output_jerk(int64_t n, const uint32_t *perm, const double4 *jo4, double G,
-                              double *jerk, int *nonfinite, hipStream_t s);
+// jerk[3 perm[i] + d] = G (far4[i] + jo4[i]).(y, z, w); *nonfinite = 1 on a
+// non-finite value
+hipError_t launch_output_jerk(int64_t n, const uint32_t *perm, const double4 *far4,
+                              const double4 *jo4, double G, double *jerk, int *nonfinite, hipStream_t s);
 
 }  // namespace fmm

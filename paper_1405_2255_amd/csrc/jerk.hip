@@ -305,29 +305,30 @@ k_p2p_jerk(int ntasks, const int4 *tasks, const int2 *entry, const double4 *xyzm
 #undef FMM_NEAR
 }
 
-// listed sinks: jerk[3 j + d] = G jo4[inv[act[j]]].(y, z, w) (indices out of
+// listed sinks: jerk[3 j + d] = G (far4 + jo4)[inv[act[j]]].(y, z, w) (indices out of
 // range are skipped; the caller reports them)
 __global__ void k_output_jerk_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                     const double4 *jo4, double G, double *jerk, int *nonfinite) {
+                                     const double4 *far4, const double4 *jo4, double G,
+                                     double *jerk, int *nonfinite) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= nact) return;
     const int64_t idx = act[j];
     if (idx < 0 || idx >= n) return;
-    const double4 v = jo4[inv[idx]];
-    const double a = G * v.y, b = G * v.z, c = G * v.w;
+    const double4 f = far4[inv[idx]], v = jo4[inv[idx]];
+    const double a = G * (f.y + v.y), b = G * (f.z + v.z), c = G * (f.w + v.w);
     jerk[3 * j] = a;
     jerk[3 * j + 1] = b;
     jerk[3 * j + 2] = c;
     if (!(isfinite(a) && isfinite(b) && isfinite(c))) atomicOr(nonfinite, 1);
 }
 
-__global__ void k_output_jerk(int64_t n, const uint32_t *perm, const double4 *jo4, double G,
-                              double *jerk, int *nonfinite) {
+__global__ void k_output_jerk(int64_t n, const uint32_t *perm, const double4 *far4,
+                              const double4 *jo4, double G, double *jerk, int *nonfinite) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double4 v = jo4[i];
+    const double4 f = far4[i], v = jo4[i];
     const int64_t j = perm[i];
-    const double a = G * v.y, b = G * v.z, c = G * v.w;
+    const double a = G * (f.y + v.y), b = G * (f.z + v.z), c = G * (f.w + v.w);
     jerk[3 * j] = a;
     jerk[3 * j + 1] = b;
     jerk[3 * j + 2] = c;
@@ -494,18 +495,19 @@ hipError_t launch_direct_jerk_sinks(int64_t n, const double *pos, const double *
 }
 
 hipError_t launch_output_jerk_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                     const double4 *jo4, double G, double *jerk, int *nonfinite,
+                                     const double4 *far4, const double4 *jo4, double G,
+                                     double *jerk, int *nonfinite,
                                      hipStream_t s) {
     if (nact <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_output_jerk_listed, dim3(blocks(nact, 256)), dim3(256), 0, s, n, nact, act,
-                       inv, jo4, G, jerk, nonfinite);
+                       inv, far4, jo4, G, jerk, nonfinite);
     return hipGetLastError();
 }
 
-hipError_t launch_output_jerk(int64_t n, const uint32_t *perm, const double4 *jo4, double G,
-                              double *jerk, int *nonfinite, hipStream_t s) {
+hipError_t launch_output_jerk(int64_t n, const uint32_t *perm, const double4 *far4,
+                              const double4 *jo4, double G, double *jerk, int *nonfinite, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_output_jerk, dim3(blocks(n, 256)), dim3(256), 0, s, n, perm, jo4, G,
+    hipLaunchKernelGGL(k_output_jerk, dim3(blocks(n, 256)), dim3(256), 0, s, n, perm, far4, jo4, G,
                        jerk, nonfinite);
     return hipGetLastError();
 }

@@ -608,11 +608,22 @@ __global__ void k_fill_int(int *p, int64_t count, int v) {
     if (i < count) p[i] = v;
 }
 
-__global__ void k_output(int64_t n, const uint32_t *perm, const double4 *out4, double G,
-                         double *pot, double *acc, int *nonfinite) {
+__global__ void k_zero(double4 *p, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = {0.0, 0.0, 0.0, 0.0};
+}
+
+__device__ __forceinline__ double4 add4(const double4 &a, const double4 &b) {
+    return {a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w};
+}
+
+// far + near field of every particle in input order
+__global__ void k_output(int64_t n, const uint32_t *perm, const double4 *far4,
+                         const double4 *near4, double G, double *pot, double *acc,
+                         int *nonfinite) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double4 v = out4[i];
+    const double4 v = add4(far4[i], near4[i]);
     const int64_t j = perm[i];
     const double p = -G * v.x, a = G * v.y, b = G * v.z, c = G * v.w;
     pot[j] = p;
@@ -658,13 +669,13 @@ __global__ void k_cell_active(int ncells, const int *beg, const int *end, const 
 
 // results of the listed particles, in list order (indices out of range are skipped)
 __global__ void k_output_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                const double4 *out4, double G, double *pot, double *acc,
-                                int *nonfinite) {
+                                const double4 *far4, const double4 *near4, double G,
+                                double *pot, double *acc, int *nonfinite) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= nact) return;
     const int64_t idx = act[j];
     if (idx < 0 || idx >= n) return;
-    const double4 v = out4[inv[idx]];
+    const double4 v = add4(far4[inv[idx]], near4[inv[idx]]);
     const double p = -G * v.x, a = G * v.y, b = G * v.z, c = G * v.w;
     pot[j] = p;
     acc[3 * j] = a;
@@ -811,10 +822,16 @@ hipError_t launch_near_reduce(int64_t n, int width, const int *leaf_of, const in
     return hipGetLastError();
 }
 
-hipError_t launch_output(int64_t n, const uint32_t *perm, const double4 *out4, double G,
-                         double *pot, double *acc, int *nonfinite, hipStream_t s) {
-    hipLaunchKernelGGL(k_output, dim3(blocks(n, 256)), dim3(256), 0, s, n, perm, out4, G, pot, acc,
-                       nonfinite);
+hipError_t launch_zero(double4 *p, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero, dim3(blocks(n, 256)), dim3(256), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_output(int64_t n, const uint32_t *perm, const double4 *far4,
+                         const double4 *near4, double G, double *pot, double *acc,
+                         int *nonfinite, hipStream_t s) {
+    hipLaunchKernelGGL(k_output, dim3(blocks(n, 256)), dim3(256), 0, s, n, perm, far4, near4, G,
+                       pot, acc, nonfinite);
     return hipGetLastError();
 }
 
@@ -841,11 +858,11 @@ hipError_t launch_cell_active(int64_t n, const uint32_t *perm, const int *flag_i
 }
 
 hipError_t launch_output_listed(int64_t n, int64_t nact, const int64_t *act, const int *inv,
-                                const double4 *out4, double G, double *pot, double *acc,
-                                int *nonfinite, hipStream_t s) {
+                                const double4 *far4, const double4 *near4, double G,
+                                double *pot, double *acc, int *nonfinite, hipStream_t s) {
     if (nact <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_output_listed, dim3(blocks(nact, 256)), dim3(256), 0, s, n, nact, act, inv,
-                       out4, G, pot, acc, nonfinite);
+                       far4, near4, G, pot, acc, nonfinite);
     return hipGetLastError();
 }
 
