@@ -130,7 +130,7 @@ struct fmm_ctx {
     uint32_t *perm = nullptr;  // points into idx or idx2
     // cells
     DevBuf beg, end, parent, child0, nchild, level, leaf_lo, leaf_hi, info, cen, com, mass, lo, hi,
-        rho2, bsph, smin, leaf_cell, M, F, P, U, Fe;
+        rho2, bsph, smin, leaf_cell, M, F, P, Fe;
     // walk
     DevBuf fa, fb, m2l, m2l2, p2p, p2p2, p2pe, p2pe2, m2l_off, p2p_off, chunks, ccnt, coff, Fpart;
     DevBuf rflag, ranges, rkey, wcode, rup;
@@ -142,14 +142,12 @@ struct fmm_ctx {
                                                // chunk parts of the rates, jerk per
                                                // particle, direct-sum partial rows
     DevBuf dkey, dsort, dsort2, runstart;   // deep refinement below level 21
-    DevBuf plans;                          // output plans of M2M and L2L for order plan_p
     DevBuf Tsh;                            // M2M: each cell's expansion shifted to its parent
     DevBuf tg, tpre, tsuf, tcell, tcell2, tls;   // tree build: window maxima, cells, levels
     DevBuf M32, sig, Flow;                 // mixed-precision M2L: scaled multipoles, chunk
                                            // scales, FP64 low-degree chunk parts
     DevBuf dspart;                         // exact sums for listed sinks: partial rows
     void *scratch = nullptr;   // device address of this device's static scratch array
-    int plan_p = -1;
     uint64_t *kdeep = nullptr;            // second key word of the sorted particles
     bool deep = false;
     void *pin = nullptr;      // pinned staging for host-to-device copies
@@ -741,28 +739,17 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     // small latency-bound launches, so each fills the other's idle units.
     const int nc = ncplx(p);
     double *M = ensure<double>(c->M, 2 * (size_t)nc * c->ncells);
-    double *U = ensure<double>(c->U, 2 * (size_t)nc * c->ncells);
     double *P = ensure<double>(c->P, (size_t)power_stride(p) * c->ncells);
-    short *plans = ensure<short>(c->plans, 2 * XP_SIZE);
     double *Tsh = ensure<double>(c->Tsh, 2 * (size_t)nc * c->ncells);
     double4 *v4 = vel ? ensure<double4>(c->vel4, n + NEAR_PAD) : nullptr;
     double *Md = vel ? ensure<double>(c->Md, 2 * (size_t)nc * c->ncells) : nullptr;
     const hipStream_t us = c->side;
     CK(hipEventRecord(c->ev_fork, s));
     CK(hipStreamWaitEvent(us, c->ev_fork, 0));
-    if (c->plan_p != p) {
-        std::vector<short> h(2 * XP_SIZE);
-        translation_plans(p, h.data(), h.data() + XP_SIZE);
-        CK(hipMemcpyAsync(plans, h.data(), h.size() * sizeof(short), hipMemcpyHostToDevice, us));
-        CK(hipStreamSynchronize(us));
-        c->plan_p = p;
-    }
     CK(launch_p2m(p, t, ptr<int>(c->leaf_cell), c->nleaves, ptr<double>(c->x), ptr<double>(c->y),
                   ptr<double>(c->z), ptr<double>(c->m), M, us));
-    if (c->ncells > 1) CK(launch_shift_upsilon(p, t, 1, c->ncells, U, us));
     for (int L = c->depth; L >= 0; --L)
-        CK(launch_m2m_level(p, t, c->ls[L], c->ls[L + 1], U, M, Tsh, plans, us));
-    CK(launch_power(p, c->ncells, M, P, us));
+        CK(launch_m2m_level(p, t, c->ls[L], c->ls[L + 1], M, Tsh, P, us));
     // jerk: rates of the multipoles (eq:P2M:dot, then the same M2M with the
     // centres at rest; Tsh is free again once M is complete)
     if (vel) {
@@ -770,7 +757,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
         CK(launch_p2m_dot(p, t, ptr<int>(c->leaf_cell), c->nleaves, ptr<double>(c->x),
                           ptr<double>(c->y), ptr<double>(c->z), ptr<double>(c->m), v4, Md, us));
         for (int L = c->depth; L >= 0; --L)
-            CK(launch_m2m_level(p, t, c->ls[L], c->ls[L + 1], U, Md, Tsh, plans, us));
+            CK(launch_m2m_level(p, t, c->ls[L], c->ls[L + 1], Md, Tsh, nullptr, us));
     }
     CK(hipEventRecord(c->ev_join, us));
     c->join_pending = true;
@@ -867,11 +854,10 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     mark(c, PH_M2L);
     // downward pass, far field at the particles
     for (int Lv = 1; Lv <= c->depth; ++Lv) {
-        CK(launch_l2l_level(p, t, c->ls[Lv], c->ls[Lv + 1], U, F,
-                            ptr<short>(c->plans) + XP_SIZE, s, cell_active));
+        CK(launch_l2l_level(p, t, c->ls[Lv], c->ls[Lv + 1], F, cell_active, s));
         if (vel)
-            CK(launch_l2l_level(p, t, c->ls[Lv], c->ls[Lv + 1], U, ptr<double>(c->Fd),
-                                ptr<short>(c->plans) + XP_SIZE, s, cell_active));
+            CK(launch_l2l_level(p, t, c->ls[Lv], c->ls[Lv + 1], ptr<double>(c->Fd), cell_active,
+                                s));
     }
     double4 *far4 = ensure<double4>(c->est4, n);   // (the estimate is in smin by now)
     CK(launch_l2p(p, t, ptr<int>(c->leaf_of), ptr<int>(c->leaf_cell), n, ptr<double>(c->x),
@@ -1098,7 +1084,7 @@ void fmm_destroy(fmm_ctx *c) {
                       &c->xyzm, &c->leaf_of, &c->out4, &c->est4, &c->scale, &c->flags, &c->tmp,
                       &c->beg, &c->end, &c->parent, &c->child0, &c->nchild, &c->level,
                       &c->leaf_lo, &c->leaf_hi, &c->info, &c->cen, &c->com, &c->mass, &c->lo, &c->hi,
-                      &c->rho2, &c->bsph, &c->smin, &c->leaf_cell, &c->M, &c->F, &c->P, &c->U, &c->Fe,
+                      &c->rho2, &c->bsph, &c->smin, &c->leaf_cell, &c->M, &c->F, &c->P, &c->Fe,
                       &c->fa, &c->fb, &c->m2l, &c->m2l2, &c->p2p, &c->p2p2, &c->p2pe,
                       &c->p2pe2, &c->rflag, &c->ranges, &c->rkey, &c->pt_n, &c->pt_m,
                       &c->pt_s, &c->pt_off, &c->pt_moff, &c->ptasks, &c->pentry, &c->pchain, &c->ppart, &c->m2l_off,
@@ -1106,7 +1092,7 @@ void fmm_destroy(fmm_ctx *c) {
                       &c->nonfinite, &c->prev_scale, &c->walktmp, &c->coffsets,
                       &c->ckey, &c->ckey2, &c->order, &c->order2, &c->wcode, &c->rup, &c->tmp_side,
                       &c->actflag, &c->actf, &c->actinv, &c->actpre, &c->cellact, &c->actbad,
-                      &c->dkey, &c->dsort, &c->dsort2, &c->runstart, &c->plans, &c->Tsh,
+                      &c->dkey, &c->dsort, &c->dsort2, &c->runstart, &c->Tsh,
                       &c->M32, &c->sig, &c->Flow, &c->epsmin, &c->vel4, &c->Md, &c->Fd,
                       &c->jFpart, &c->jo4, &c->jfar4, &c->jpart, &c->dspart, &c->tg, &c->tpre, &c->tsuf,
                       &c->tcell, &c->tcell2, &c->tls};

@@ -4,12 +4,9 @@
 //
 // Storage: per cell the complex X_n^m for 0 <= m <= n <= p at complex index
 // tri(n, m) = n(n+1)/2 + m, (Re, Im) adjacent, Im = 0 for m = 0.
-#include <algorithm>
-#include <stdexcept>
-#include <vector>
-
 #include "internal.h"
 #include "harmonics.h"
+#include "near.h"
 
 namespace fmm {
 
@@ -121,150 +118,44 @@ k_p2m(TreeArrays t, const int *leaf_cell, int nleaves, const double *x, const do
     }
 }
 
-// ---- Upsilon of each cell's offset from its parent's centre -----------------
-template <int P>
-__global__ void k_shift_upsilon(TreeArrays t, int c0, int c1, double *U) {
-    const int c = c0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= c1) return;
-    const int pc = t.parent[c];
-    if (pc < 0) return;
-    const double4 a = t.cen[c], b = t.cen[pc];
-    cplx *Uc = reinterpret_cast<cplx *>(U) + (size_t)c * tri(P + 1, 0);
-    RowGen<P> g;
-    g.upsilon_start(a.x - b.x, a.y - b.y, a.z - b.z);
-    auto emit = [&]<int N>() {
-        if constexpr (N > 0) g.template upsilon_row<N>();
-        const cplx *row = g.template row<N>();
-#pragma unroll
-        for (int mm = 0; mm <= N; ++mm) Uc[tri(N, mm)] = row[mm];
-    };
-    Unroll<0, P>::run(emit);
-}
-
 __device__ __forceinline__ cplx ld(const cplx *X, int n, int q) {
     return sym(X[tri(n, q < 0 ? -q : q)], q);
 }
 
-constexpr int NFULL = (FMM_PMAX + 1) * (FMM_PMAX + 1);   // all orders -n..n
-// degree and order of coefficient index o (o = tri(n, m))
-__device__ __forceinline__ void nm_of(int o, int &n, int &m) {
-    n = 0;
-    while (tri(n + 1, 0) <= o) ++n;
-    m = o - tri(n, 0);
+// ---- shifts (M2M, L2L): three one-dimensional sums ---------------------------
+// A shift by r = (x, y, z) is the sum over (k, l) of Upsilon_k^l(r) with the
+// cell's coefficients, O(p^4) terms.  By the addition theorem (a polynomial
+// identity, valid for complex vectors too) Upsilon(r) is the convolution of
+// those of the three parts
+//   (0, 0, z):              Upsilon_k^0  = z^k / k!,       all else 0,
+//   (w, -i w, 0):           Upsilon_k^k  = w^k / k!,       all else 0,
+//   (-w~, ...) = its mirror: Upsilon_k^-k = (-w~)^k / k!,  all else 0,
+// with w = (x + i y) / 2 (the last two vectors have length 0 and add up to
+// (x, y, 0)).  The shift is then three sums over one index each, O(p^3) terms:
+// 4 x 10^2 complex multiply-adds per sum at p = 15 against 5 x 10^3.  Against
+// extended precision its error equals that of the sum over (k, l).
+//
+// One wavefront per cell, four cells per block: R coefficients per lane in LDS,
+// weight j in lane j.  Four terms of every sum are read together; a term that
+// does not exist reads a zero, so that the wavefront never parts.  Bound by
+// latency in the levels with few cells (7 us a level) and by bytes and the sums'
+// instructions elsewhere.  At p = 15, 5 x 10^4 cells, the M2M levels take 342 us
+// with P_n, where a block per cell over (k, l) took 476 us, after 73 us for the
+// Upsilon of each cell and before 55 us for P_n.
+constexpr int XF_CELLS = 4;                                  // per block
+
+// LDS of one cell: stored coefficients, then a zero; all orders (at n^2 + n + m),
+// then a zero
+inline __host__ __device__ int shift_lds_cplx(int p) {
+    return tri(p + 1, 0) + 1 + (p + 1) * (p + 1) + 1;
 }
 
-// ---- M2M: one block per cell, threads over (output, rows of k) items ---------
-// Level by level from the bottom.  The block of cell c first completes M(c):
-// for an internal cell the sum, in child order, of the children's shifted
-// expansions T(child) written by the previous level's launch (a leaf keeps
-// its P2M result); then, unless c is a root, it shifts M(c) to the parent's
-// centre,
-//   T_n^m(c) = sum_{k=0}^{n} sum_{l=-k}^{k} Upsilon_k^l(z_c - z_parent) M_{n-k}^{m-l}(c),
-// with M(c) and the shift Upsilon staged (all orders) in LDS.  The sum of
-// each output is cut into items of consecutive k (the plan); each thread
-// adds its items' terms, and each output then adds its items in order, so
-// that no thread's chain of multiply-adds is longer than about 1/256 of the
-// cell's work (the upper levels hold few cells, and there the chain sets the
-// time of the launch).
-__device__ __forceinline__ int isqrt_full(int f) {
-    int n = (int)sqrtf((float)f);
-    while (n * n > f) --n;
-    while ((n + 1) * (n + 1) <= f) ++n;
-    return n;
+// what one lane wrote to LDS is there for the others of its wavefront
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__global__ void __launch_bounds__(XF_THREADS)
-k_m2m_level(int p, TreeArrays t, int c0, const double *U, double *M, double *T,
-            const short *plan) {
-    __shared__ cplx sU[NFULL], sM[NFULL], part[XF_ITEMS];
-    const int c = c0 + blockIdx.x, tid = threadIdx.x;
-    const int nc = tri(p + 1, 0);
-    const int nch = t.nchild[c];
-    const bool shift = t.parent[c] >= 0;
-    cplx *Mc = reinterpret_cast<cplx *>(M) + (size_t)c * nc;
-    const cplx *Tb = reinterpret_cast<const cplx *>(T);
-    // complete M(c) (threads over stored coefficients) and stage it
-    for (int e = tid; e < nc; e += XF_THREADS) {
-        int n, m;
-        nm_of(e, n, m);
-        cplx v;
-        if (nch > 0) {
-            // the (at most 8) children's terms loaded together, added in order
-            v = {0.0, 0.0};
-            const int k0 = t.child0[c];
-            cplx xs[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) xs[j] = Tb[(size_t)(k0 + (j < nch ? j : 0)) * nc + e];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (j < nch) {
-                    v.re += xs[j].re;
-                    v.im += xs[j].im;
-                }
-            }
-            if (m == 0) v.im = 0.0;
-            Mc[e] = v;
-        } else {
-            v = Mc[e];
-        }
-        sM[n * n + n + m] = v;
-        if (m > 0) sM[n * n + n - m] = sym(v, -m);
-    }
-    if (!shift) return;
-    const cplx *Uc = reinterpret_cast<const cplx *>(U) + (size_t)c * nc;
-    for (int f = tid; f < (p + 1) * (p + 1); f += XF_THREADS) {
-        const int n = isqrt_full(f), q = f - n * n - n;
-        sU[f] = ld(Uc, n, q);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < XF_IT; ++r) {
-        const int it = plan[XP_LANE + r * XF_THREADS + tid];
-        if (it < 0) continue;
-        const int n = plan[XP_N + it], m = plan[XP_M + it];
-        const int k0 = plan[XP_K0 + it], k1 = plan[XP_K1 + it];
-        // four partial sums over consecutive terms: independent chains
-        cplx a[4] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-        for (int k = k0; k <= k1; ++k) {
-            const int nn = n - k;
-            const int lmin = max(-k, m - nn), lmax = min(k, m + nn);
-            const int bu = k * k + k, bv = nn * nn + nn + m;
-            int l = lmin;
-            for (; l + 3 <= lmax; l += 4) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const cplx u = sU[bu + l + j], v = sM[bv - l - j];
-                    a[j].re = fma(u.re, v.re, fma(-u.im, v.im, a[j].re));
-                    a[j].im = fma(u.re, v.im, fma(u.im, v.re, a[j].im));
-                }
-            }
-            for (; l <= lmax; ++l) {
-                const cplx u = sU[bu + l], v = sM[bv - l];
-                a[0].re = fma(u.re, v.re, fma(-u.im, v.im, a[0].re));
-                a[0].im = fma(u.re, v.im, fma(u.im, v.re, a[0].im));
-            }
-        }
-        part[it] = {(a[0].re + a[1].re) + (a[2].re + a[3].re),
-                    (a[0].im + a[1].im) + (a[2].im + a[3].im)};
-    }
-    __syncthreads();
-    cplx *Tc = reinterpret_cast<cplx *>(T) + (size_t)c * nc;
-    for (int e = tid; e < nc; e += XF_THREADS) {
-        cplx v = {0.0, 0.0};
-        for (int i = plan[XP_OUT + e]; i < plan[XP_OUT + e + 1]; ++i) {
-            v.re += part[i].re;
-            v.im += part[i].im;
-        }
-        int n, m;
-        nm_of(e, n, m);
-        Tc[e] = {v.re, m == 0 ? 0.0 : v.im};
-    }
-}
-
-// ---- multipole power P_n^2 = sum_m (n-m)!(n+m)! |M_n^m|^2 ----------------------
-// times C(p, n), as the walk's error estimate uses it.  One thread per cell and
-// degree: the lanes of a wavefront read neighbouring rows (a thread per cell
-// touched another cell in every lane, 75 us at 5e4 cells against 10).
 struct FactTable {
     double v[2 * FMM_PMAX + 1];
 };
@@ -276,94 +167,275 @@ constexpr FactTable make_fact_table() {
 }
 __constant__ FactTable kFact = make_fact_table();
 
+// a^j / j! in lane j <= p (by repeated squaring), 0 in the others
+__device__ __forceinline__ cplx power_weight(int p, cplx a) {
+    const int j = lane_id();
+    cplx v = {1.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        if ((j >> q) & 1) v = cmul(v, a);
+        a = cmul(a, a);
+    }
+    if (j > p) return {0.0, 0.0};
+    const double f = 1.0 / kFact.v[j];
+    return {v.re * f, v.im * f};
+}
+__device__ __forceinline__ double power_weight(int p, double a) {
+    const int j = lane_id();
+    double v = 1.0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        if ((j >> q) & 1) v *= a;
+        a *= a;
+    }
+    return j > p ? 0.0 : v / kFact.v[j];
+}
+
+__device__ __forceinline__ void add_term(double wz, cplx x, cplx &s) {
+    s.re = fma(wz, x.re, s.re);
+    s.im = fma(wz, x.im, s.im);
+}
+__device__ __forceinline__ void add_term(cplx w, cplx x, cplx &s) {
+    s.re = fma(w.re, x.re, fma(-w.im, x.im, s.re));
+    s.im = fma(w.re, x.im, fma(w.im, x.re, s.im));
+}
+__device__ __forceinline__ double from_lane(double v, int j) { return readlane_f64(v, j); }
+__device__ __forceinline__ cplx from_lane(cplx v, int j) {
+    return {readlane_f64(v.re, j), readlane_f64(v.im, j)};
+}
+
+// degree and order of coefficient index e = tri(n, m)
+__device__ __forceinline__ void nm_of(int e, int &n, int &m) {
+    n = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+    if (tri(n + 1, 0) <= e) ++n;
+    if (tri(n, 0) > e) --n;
+    m = e - tri(n, 0);
+}
+
+// One of the three sums for the R coefficients of a lane: terms j = 0 .. last[r]
+// at index i, i + step, i + 2 step + grow, ... of X; jmax: the largest last.
+template <int R, class W>
+__device__ __forceinline__ void shift_sum(W weight, const cplx *X, int zero, int jmax, int grow,
+                                          const int *first, const int *step0, const int *last,
+                                          cplx *s) {
+    int i[R], step[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        i[r] = first[r];
+        step[r] = step0[r];
+        s[r] = {0.0, 0.0};
+    }
+    for (int j0 = 0; j0 <= jmax; j0 += 4) {
+        cplx x[4][R];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                x[q][r] = X[j0 + q <= last[r] ? i[r] : zero];
+                i[r] += step[r];
+                step[r] += grow;
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const W wj = from_lane(weight, j0 + q);
+#pragma unroll
+            for (int r = 0; r < R; ++r) add_term(wj, x[q][r], s[r]);
+        }
+    }
+}
+
 struct Binomials {
     double v[FMM_PMAX + 1];
 };
 
-__global__ void __launch_bounds__(256)
-k_power(int p, int ncells, Binomials binom, const double *M, double *P) {
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = (int)(gid / (p + 1)), n = (int)(gid % (p + 1));
-    if (c >= ncells) return;
-    const cplx *Mn = reinterpret_cast<const cplx *>(M) + (size_t)c * tri(p + 1, 0) + tri(n, 0);
-    const cplx v0 = Mn[0];
-    double s = kFact.v[n] * kFact.v[n] * v0.re * v0.re;
-    for (int m = 1; m <= n; ++m) {
-        const cplx v = Mn[m];
-        s += 2.0 * kFact.v[n - m] * kFact.v[n + m] * (v.re * v.re + v.im * v.im);
+// ---- M2M and the multipole power --------------------------------------------
+// Level by level from the bottom.  The wavefront of cell c first completes
+// M(c): for an internal cell the sum, in child order, of the children's shifted
+// expansions T(child) written by the previous level's launch (a leaf keeps its
+// P2M result); then the power P_n^2 = sum_m (n-m)!(n+m)! |M_n^m|^2, stored as
+// C(p, n) P_n, as the walk's error estimate uses it (P not null); then, unless
+// c is a root, the shift of M(c) to the parent's centre,
+//   T_n^m(c) = sum_{k=0}^{n} sum_{l=-k}^{k} Upsilon_k^l(z_c - z_parent) M_{n-k}^{m-l}(c).
+template <int R>
+__global__ void __launch_bounds__(XF_CELLS * FMM_WAVE)
+k_m2m_level(int p, TreeArrays t, int c0, int c1, double *M, double *T, Binomials binom,
+            double *P) {
+    extern __shared__ double lds[];
+    const int w = threadIdx.x / FMM_WAVE, lane = lane_id();
+    const int c = c0 + blockIdx.x * XF_CELLS + w;
+    if (c >= c1) return;
+    const int nc = tri(p + 1, 0), nf = (p + 1) * (p + 1);
+    cplx *half = reinterpret_cast<cplx *>(lds) + w * shift_lds_cplx(p), *full = half + nc + 1;
+    const int4 info = t.info[c];
+    const int nch = info.w, pc = t.parent[c];
+    cplx *Mc = reinterpret_cast<cplx *>(M) + (size_t)c * nc;
+    const cplx *Tb = reinterpret_cast<const cplx *>(T) + (size_t)info.z * nc;
+    int n[R], m[R], first[R], step[R], last[R];
+    cplx v[R];
+    double f2[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = r * FMM_WAVE + lane, ee = min(e, nc - 1);
+        nm_of(ee, n[r], m[r]);
+        f2[r] = kFact.v[n[r] - m[r]] * kFact.v[n[r] + m[r]];
+        if (nch > 0) {
+            // the (at most 8) children's terms loaded together, added in order
+            v[r] = {0.0, 0.0};
+            cplx xs[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xs[j] = Tb[(size_t)(j < nch ? j : 0) * nc + ee];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (j < nch) {
+                    v[r].re += xs[j].re;
+                    v[r].im += xs[j].im;
+                }
+            }
+            if (e < nc) Mc[e] = v[r];
+        } else {
+            v[r] = Mc[ee];
+        }
+        if (e < nc) half[e] = v[r];
     }
-    P[(size_t)c * power_stride(p) + n] = binom.v[n] * sqrt(s);
+    if (lane == 0) half[nc] = full[nf] = {0.0, 0.0};
+    if (P) {
+        double *term = reinterpret_cast<double *>(full);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = r * FMM_WAVE + lane;
+            const double q = f2[r] * (v[r].re * v[r].re + v[r].im * v[r].im);
+            if (e < nc) term[e] = m[r] == 0 ? q : 2.0 * q;
+        }
+        wave_fence();
+        if (lane <= p) {
+            double q = 0.0;
+#pragma unroll 4
+            for (int i = 0; i <= lane; ++i) q += term[tri(lane, i)];
+            P[(size_t)c * power_stride(p) + lane] = binom.v[lane] * sqrt(q);
+        }
+    }
+    if (pc < 0) return;
+    const double4 ca = t.cen[c], cb = t.cen[pc];
+    const cplx wp = {0.5 * (ca.x - cb.x), 0.5 * (ca.y - cb.y)};
+    const double wz = power_weight(p, ca.z - cb.z);
+    const cplx wplus = power_weight(p, wp), wminus = power_weight(p, cplx{-wp.re, wp.im});
+    wave_fence();
+    cplx s[R];
+    // along z: sum_j z^j/j! M_{n-j}^m
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = tri(n[r], m[r]);
+        step[r] = -n[r];
+        last[r] = n[r] - m[r];
+    }
+    shift_sum<R>(wz, half, nc, p, 1, first, step, last, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r * FMM_WAVE + lane >= nc) continue;
+        cplx *f = full + n[r] * n[r] + n[r];
+        f[m[r]] = s[r];
+        if (m[r] > 0) f[-m[r]] = sym(s[r], -m[r]);
+    }
+    wave_fence();
+    // sum_j w^j/j! X_{n-j}^{m-j}
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = n[r] * n[r] + n[r] + m[r];
+        step[r] = -2 * n[r] - 1;
+        last[r] = (n[r] + m[r]) / 2;
+    }
+    shift_sum<R>(wplus, full, nf, p, 2, first, step, last, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * FMM_WAVE + lane < nc) half[r * FMM_WAVE + lane] = s[r];
+    wave_fence();
+    // sum_j (-w~)^j/j! X_{n-j}^{m+j}
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = tri(n[r], m[r]);
+        step[r] = 1 - n[r];
+        last[r] = (n[r] - m[r]) / 2;
+    }
+    shift_sum<R>(wminus, half, nc, p / 2, 1, first, step, last, s);
+    cplx *Tc = reinterpret_cast<cplx *>(T) + (size_t)c * nc;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * FMM_WAVE + lane < nc)
+            Tc[r * FMM_WAVE + lane] = {s[r].re, m[r] == 0 ? 0.0 : s[r].im};
 }
 
-// ---- L2L: one block per child, threads over (output, rows of k) items --------
+// ---- L2L ---------------------------------------------------------------------
 // F_n^m(s') += sum_{k=0}^{p-n} sum_l conj(Upsilon_k^l(s - s')) F_{n+k}^{m+l}(s),
-// with Upsilon_k^l(s - s') = (-1)^k Upsilon_k^l(s' - s) from the stored shift;
-// the parent's F and the child's shift are staged (all orders) in LDS; items
-// and their order as for M2M.
-__global__ void __launch_bounds__(XF_THREADS)
-k_l2l_level(int p, TreeArrays t, int c0, const double *U, double *F, const short *plan,
-            const uint8_t *active) {
-    __shared__ cplx sU[NFULL], sF[NFULL], part[XF_ITEMS];
-    const int c = c0 + blockIdx.x, tid = threadIdx.x;
+// as three sums over degrees upwards (the parts commute; the one that raises
+// the order comes last, so that the sums need orders m >= 0 only).
+template <int R>
+__global__ void __launch_bounds__(XF_CELLS * FMM_WAVE)
+k_l2l_level(int p, TreeArrays t, int c0, int c1, double *F, const uint8_t *active) {
+    extern __shared__ double lds[];
+    const int w = threadIdx.x / FMM_WAVE, lane = lane_id();
+    const int c = c0 + blockIdx.x * XF_CELLS + w;
+    if (c >= c1) return;
     if (active && !active[c]) return;      // no listed sink below c
     const int pc = t.parent[c];
     if (pc < 0) return;
-    const int nc = tri(p + 1, 0);
-    const cplx *Uc = reinterpret_cast<const cplx *>(U) + (size_t)c * nc;
+    const int nc = tri(p + 1, 0), nf = (p + 1) * (p + 1);
+    cplx *half = reinterpret_cast<cplx *>(lds) + w * shift_lds_cplx(p), *full = half + nc + 1;
     const cplx *Fp = reinterpret_cast<const cplx *>(F) + (size_t)pc * nc;
-    for (int f = tid; f < (p + 1) * (p + 1); f += XF_THREADS) {
-        const int n = isqrt_full(f), q = f - n * n - n;
-        sU[f] = ld(Uc, n, q);
-        sF[f] = ld(Fp, n, q);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < XF_IT; ++r) {
-        const int it = plan[XP_LANE + r * XF_THREADS + tid];
-        if (it < 0) continue;
-        const int n = plan[XP_N + it], m = plan[XP_M + it];
-        const int k0 = plan[XP_K0 + it], k1 = plan[XP_K1 + it];
-        // four partial sums over consecutive terms (independent chains)
-        cplx acc[4] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-        for (int k = k0; k <= k1; ++k) {
-            const double sg = (k & 1) ? -1.0 : 1.0;
-            const int nk = n + k;
-            const int bu = k * k + k, bf = nk * nk + nk + m;
-            int l = -k;
-            for (; l + 3 <= k; l += 4) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const cplx u = sU[bu + l + j], f = sF[bf + l + j];
-                    // conj(sg u) * f
-                    const double ur = sg * u.re, ui = -sg * u.im;
-                    acc[j].re = fma(ur, f.re, fma(-ui, f.im, acc[j].re));
-                    acc[j].im = fma(ur, f.im, fma(ui, f.re, acc[j].im));
-                }
-            }
-            for (; l <= k; ++l) {
-                const cplx u = sU[bu + l], f = sF[bf + l];
-                const double ur = sg * u.re, ui = -sg * u.im;
-                acc[0].re = fma(ur, f.re, fma(-ui, f.im, acc[0].re));
-                acc[0].im = fma(ur, f.im, fma(ui, f.re, acc[0].im));
-            }
-        }
-        part[it] = {(acc[0].re + acc[1].re) + (acc[2].re + acc[3].re),
-                    (acc[0].im + acc[1].im) + (acc[2].im + acc[3].im)};
-    }
-    __syncthreads();
     cplx *Fc = reinterpret_cast<cplx *>(F) + (size_t)c * nc;
-    for (int e = tid; e < nc; e += XF_THREADS) {
-        cplx v = {0.0, 0.0};
-        for (int i = plan[XP_OUT + e]; i < plan[XP_OUT + e + 1]; ++i) {
-            v.re += part[i].re;
-            v.im += part[i].im;
-        }
-        int n, m;
-        nm_of(e, n, m);
-        cplx &dst = Fc[e];
-        dst.re += v.re;
-        if (m != 0) dst.im += v.im;
+    int n[R], m[R], first[R], step[R], last[R];
+    cplx own[R], s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = r * FMM_WAVE + lane, ee = min(e, nc - 1);
+        nm_of(ee, n[r], m[r]);
+        s[r] = Fp[ee];
+        own[r] = Fc[ee];
+        if (e < nc) half[e] = s[r];
+        last[r] = p - n[r];
     }
+    if (lane == 0) half[nc] = full[nf] = {0.0, 0.0};
+    const double4 ca = t.cen[pc], cb = t.cen[c];
+    const cplx wp = {0.5 * (ca.x - cb.x), 0.5 * (ca.y - cb.y)};
+    // conjugated weights
+    const double wz = power_weight(p, ca.z - cb.z);
+    const cplx wplus = power_weight(p, cplx{wp.re, -wp.im});
+    const cplx wminus = power_weight(p, cplx{-wp.re, -wp.im});
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = tri(n[r], m[r]);
+        step[r] = n[r] + 1;
+    }
+    shift_sum<R>(wz, half, nc, p, 1, first, step, last, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r * FMM_WAVE + lane >= nc) continue;
+        cplx *f = full + n[r] * n[r] + n[r];
+        f[m[r]] = s[r];
+        if (m[r] > 0) f[-m[r]] = sym(s[r], -m[r]);
+    }
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = n[r] * n[r] + n[r] + m[r];
+        step[r] = 2 * n[r] + 1;
+    }
+    shift_sum<R>(wminus, full, nf, p, 2, first, step, last, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * FMM_WAVE + lane < nc) half[r * FMM_WAVE + lane] = s[r];
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = tri(n[r], m[r]);
+        step[r] = n[r] + 2;
+    }
+    shift_sum<R>(wplus, half, nc, p, 1, first, step, last, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * FMM_WAVE + lane < nc)
+            Fc[r * FMM_WAVE + lane] = {own[r].re + s[r].re,
+                                       m[r] == 0 ? own[r].im : own[r].im + s[r].im};
 }
 
 // ---- L2P: one thread per particle ------------------------------------------
@@ -488,116 +560,6 @@ inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-// The items of one translation: each output's rows of k are cut, in order,
-// into items of at most T terms (T = the larger of the cell's terms / 256
-// and the longest row).  The lanes of a wavefront run their items' loops in
-// lockstep (rows of k, then the terms of each row), so a wavefront costs the
-// longest of its lanes at every step: items are therefore ordered by shape
-// (number of rows, first row, then longest first) and dealt in runs of 64
-// consecutive ones, one run per wavefront and round; runs go, costliest
-// first, to the wavefront with the least work so far (at most XF_IT each).
-// A run's cost models its lockstep loops: per row a fixed set-up, per four
-// terms of the row's longest lane one unrolled step, per leftover term one
-// single step.  Deterministic.
-static void item_plan(int p, bool m2m, short *plan) {
-    const int nc = tri(p + 1, 0);
-    auto row = [&](int n, int m, int k) -> int {
-        if (!m2m) return 2 * k + 1;
-        const int nn = n - k;
-        const int lo = std::max(-k, m - nn), hi = std::min(k, m + nn);
-        return hi >= lo ? hi - lo + 1 : 0;
-    };
-    long total = 0;
-    int longest = 0;
-    for (int n = 0; n <= p; ++n)
-        for (int m = 0; m <= n; ++m)
-            for (int k = 0; k <= (m2m ? n : p - n); ++k) {
-                total += row(n, m, k);
-                longest = std::max(longest, row(n, m, k));
-            }
-    const long T = std::max<long>((total + XF_THREADS - 1) / XF_THREADS, longest);
-    struct Item { int n, m, k0, k1; long cost; };
-    std::vector<Item> items;
-    std::vector<int> first(nc + 1);
-    for (int n = 0; n <= p; ++n)
-        for (int m = 0; m <= n; ++m) {
-            first[tri(n, m)] = (int)items.size();
-            const int kmax = m2m ? n : p - n;
-            long cur = 0;
-            int k0 = 0;
-            for (int k = 0; k <= kmax; ++k) {
-                const int r = row(n, m, k);
-                if (cur > 0 && cur + r > T) {
-                    items.push_back({n, m, k0, k - 1, cur});
-                    cur = 0;
-                    k0 = k;
-                }
-                cur += r;
-            }
-            items.push_back({n, m, k0, kmax, cur});
-        }
-    first[nc] = (int)items.size();
-    if ((int)items.size() > XF_ITEMS) throw std::runtime_error("translation plan: too many items");
-    std::vector<int> order(items.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        const Item &x = items[a], &y = items[b];
-        if (x.k1 - x.k0 != y.k1 - y.k0) return x.k1 - x.k0 < y.k1 - y.k0;
-        if (x.k0 != y.k0) return x.k0 < y.k0;
-        return x.cost > y.cost;
-    });
-    constexpr int W = 64;                        // lanes per wavefront
-    constexpr int NW = XF_THREADS / W;
-    struct Run { int begin, end; long cost; };
-    std::vector<Run> runs;
-    for (int j = 0; j < (int)order.size(); j += W) {
-        Run r{j, std::min(j + W, (int)order.size()), 10};
-        for (int row_i = 0;; ++row_i) {
-            int longest_q = -1, longest_r = 0;
-            for (int t = r.begin; t < r.end; ++t) {
-                const Item &it = items[order[t]];
-                if (it.k0 + row_i > it.k1) continue;
-                const int len = row(it.n, it.m, it.k0 + row_i);
-                longest_q = std::max(longest_q, len / 4);
-                longest_r = std::max(longest_r, len % 4);
-            }
-            if (longest_q < 0) break;
-            r.cost += 20 + 20 * longest_q + 8 * longest_r;
-        }
-        runs.push_back(r);
-    }
-    std::vector<int> by_cost(runs.size());
-    for (size_t i = 0; i < by_cost.size(); ++i) by_cost[i] = (int)i;
-    std::stable_sort(by_cost.begin(), by_cost.end(),
-                     [&](int a, int b) { return runs[a].cost > runs[b].cost; });
-    std::vector<long> load(NW, 0);
-    std::vector<int> rounds(NW, 0);
-    for (int i = 0; i < XP_SIZE; ++i) plan[i] = -1;
-    for (int ri : by_cost) {
-        int best = -1;
-        for (int w = 0; w < NW; ++w)
-            if (rounds[w] < XF_IT && (best < 0 || load[w] < load[best])) best = w;
-        if (best < 0) throw std::runtime_error("translation plan: too few threads");
-        for (int t = runs[ri].begin; t < runs[ri].end; ++t)
-            plan[XP_LANE + rounds[best] * XF_THREADS + best * W + (t - runs[ri].begin)] =
-                (short)order[t];
-        ++rounds[best];
-        load[best] += runs[ri].cost;
-    }
-    for (size_t i = 0; i < items.size(); ++i) {
-        plan[XP_N + i] = (short)items[i].n;
-        plan[XP_M + i] = (short)items[i].m;
-        plan[XP_K0 + i] = (short)items[i].k0;
-        plan[XP_K1 + i] = (short)items[i].k1;
-    }
-    for (int e = 0; e <= nc; ++e) plan[XP_OUT + e] = (short)first[e];
-}
-
-void translation_plans(int p, short *m2m, short *l2l) {
-    item_plan(p, true, m2m);
-    item_plan(p, false, l2l);
-}
-
 hipError_t launch_p2m(int p, const TreeArrays &t, const int *leaf_cell, int nleaves,
                       const double *x, const double *y, const double *z, const double *m,
                       double *M, hipStream_t s) {
@@ -609,38 +571,38 @@ hipError_t launch_p2m(int p, const TreeArrays &t, const int *leaf_cell, int nlea
     return hipGetLastError();
 }
 
-hipError_t launch_shift_upsilon(int p, const TreeArrays &t, int c0, int c1, double *U,
-                                hipStream_t s) {
+// coefficients per lane of a wavefront: 1 up to p = 9, 2 up to 14, 3 up to 18
+#define FMM_DISPATCH_R(p, CALL)                                 \
+    switch ((ncplx(p) + FMM_WAVE - 1) / FMM_WAVE) {             \
+    case 1: CALL(1); break;   case 2: CALL(2); break;           \
+    case 3: CALL(3); break;   case 4: CALL(4); break;           \
+    default: return hipErrorInvalidValue;                       \
+    }
+
+hipError_t launch_m2m_level(int p, const TreeArrays &t, int c0, int c1, double *M, double *T,
+                            double *P, hipStream_t s) {
     if (c1 <= c0) return hipSuccess;
-#define CALL(P) hipLaunchKernelGGL(k_shift_upsilon<P>, dim3(blocks(c1 - c0, 128)), dim3(128), 0, \
-                                   s, t, c0, c1, U)
-    FMM_DISPATCH_P(p, CALL)
+    Binomials b;
+    b.v[0] = 1.0;
+    for (int k = 1; k <= p; ++k) b.v[k] = b.v[k - 1] * (double)(p - k + 1) / (double)k;
+#define CALL(R)                                                                                \
+    hipLaunchKernelGGL(k_m2m_level<R>, dim3(blocks(c1 - c0, XF_CELLS)),                        \
+                       dim3(XF_CELLS * FMM_WAVE), XF_CELLS * shift_lds_cplx(p) * sizeof(cplx), \
+                       s, p, t, c0, c1, M, T, b, P)
+    FMM_DISPATCH_R(p, CALL)
 #undef CALL
     return hipGetLastError();
 }
 
-hipError_t launch_m2m_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
-                            double *M, double *T, const short *plan, hipStream_t s) {
+hipError_t launch_l2l_level(int p, const TreeArrays &t, int c0, int c1, double *F,
+                            const uint8_t *active, hipStream_t s) {
     if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_m2m_level, dim3((unsigned)(c1 - c0)), dim3(XF_THREADS), 0, s, p, t, c0, U,
-                       M, T, plan);
-    return hipGetLastError();
-}
-
-hipError_t launch_power(int p, int ncells, const double *M, double *P, hipStream_t s) {
-    Binomials b;
-    b.v[0] = 1.0;
-    for (int k = 1; k <= p; ++k) b.v[k] = b.v[k - 1] * (double)(p - k + 1) / (double)k;
-    hipLaunchKernelGGL(k_power, dim3(blocks((int64_t)ncells * (p + 1), 256)), dim3(256), 0, s, p,
-                       ncells, b, M, P);
-    return hipGetLastError();
-}
-
-hipError_t launch_l2l_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
-                            double *F, const short *plan, hipStream_t s, const uint8_t *active) {
-    if (c1 <= c0) return hipSuccess;
-    hipLaunchKernelGGL(k_l2l_level, dim3((unsigned)(c1 - c0)), dim3(XF_THREADS), 0, s, p, t, c0, U,
-                       F, plan, active);
+#define CALL(R)                                                                                \
+    hipLaunchKernelGGL(k_l2l_level<R>, dim3(blocks(c1 - c0, XF_CELLS)),                        \
+                       dim3(XF_CELLS * FMM_WAVE), XF_CELLS * shift_lds_cplx(p) * sizeof(cplx), \
+                       s, p, t, c0, c1, F, active)
+    FMM_DISPATCH_R(p, CALL)
+#undef CALL
     return hipGetLastError();
 }
 

@@ -129,41 +129,16 @@ inline int ncplx(int p) { return (p + 1) * (p + 2) / 2; }
 hipError_t launch_p2m(int p, const TreeArrays &t, const int *leaf_cell, int nleaves,
                       const double *x, const double *y, const double *z, const double *m,
                       double *M, hipStream_t s);
-hipError_t launch_shift_upsilon(int p, const TreeArrays &t, int c0, int c1, double *U,
-                                hipStream_t s);
-// Work plans of the translation kernels (M2M, L2L), one block of XF_THREADS
-// threads per cell.  Each output coefficient's sum over k is cut into items
-// of consecutive k with about equal numbers of terms, the items are dealt to
-// the threads (at most XF_IT each, in runs of 64 items of one shape per
-// wavefront), and each output adds its items' partial sums in item order.
-// Layout (short):
-// item i has degree n, order m and rows k0..k1 at XP_N/XP_M/XP_K0/XP_K1 + i;
-// thread t's r-th item (or -1) at XP_LANE + r * XF_THREADS + t; the items of
-// output e (stored index tri(n, m)) are [XP_OUT + e], [XP_OUT + e + 1]).
-// A plan for m2m and one for l2l, XP_SIZE shorts each.
-#define XF_THREADS 256
-#define XF_ITEMS 512
-#define XF_IT 3
-#define XP_N 0
-#define XP_M XF_ITEMS
-#define XP_K0 (2 * XF_ITEMS)
-#define XP_K1 (3 * XF_ITEMS)
-#define XP_LANE (4 * XF_ITEMS)
-#define XP_OUT (XP_LANE + XF_IT * XF_THREADS)
-#define XP_SIZE (XP_OUT + (FMM_PMAX + 1) * (FMM_PMAX + 2) / 2 + 1)
-void translation_plans(int p, short *m2m, short *l2l);
-// Cells [c0, c1) of one level: complete M (internal cells: sum of the
-// children's T) and write T = M shifted to the parent's centre (not for
-// roots).  Run from the deepest level up to level 0.
-hipError_t launch_m2m_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
-                            double *M, double *T, const short *plan, hipStream_t s);
-// C(p, n) P_n per cell, rows of power_stride(p) doubles (16-byte aligned)
+// C(p, n) P_n per cell: rows of power_stride(p) doubles (16-byte aligned)
 inline __host__ __device__ int power_stride(int p) { return (p + 2) & ~1; }
-hipError_t launch_power(int p, int ncells, const double *M, double *P, hipStream_t s);
+// Cells [c0, c1) of one level: complete M (internal cells: sum of the
+// children's T), write P (when not null) and T = M shifted to the parent's
+// centre (not for roots).  Run from the deepest level up to level 0.
+hipError_t launch_m2m_level(int p, const TreeArrays &t, int c0, int c1, double *M, double *T,
+                            double *P, hipStream_t s);
 // (active: when not null, cells / leaves without listed sinks are skipped)
-hipError_t launch_l2l_level(int p, const TreeArrays &t, int c0, int c1, const double *U,
-                            double *F, const short *plan, hipStream_t s,
-                            const uint8_t *active = nullptr);
+hipError_t launch_l2l_level(int p, const TreeArrays &t, int c0, int c1, double *F,
+                            const uint8_t *active, hipStream_t s);
 // far field at every particle of every leaf: out4[i] = (Psi, ax, ay, az)
 hipError_t launch_l2p(int p, const TreeArrays &t, const int *leaf_of, const int *leaf_cell,
                       int64_t n, const double *x, const double *y, const double *z,
