@@ -20,10 +20,12 @@
 // rho = the largest distance of its particles from it (the definitions of
 // rho_z and rho_s in Sec. 4).  rho_com likewise about the centre of mass (the
 // centre of the low-order estimate, Sec. 5.4.2).
+#include <algorithm>
 #include <climits>
 
 #include "internal.h"
 #include "dev.h"
+#include "near.h"
 
 namespace fmm {
 
@@ -582,27 +584,21 @@ __device__ __forceinline__ double dist2_rn(double ax, double ay, double az, doub
 
 constexpr int RADII_ROWS = 4;   // rows of 64 consecutive particles per wavefront
 
-// atomicMax that first reads the current value and skips the atomic when it
-// cannot raise it: the top cells get one commit per wavefront, and most of
-// those atomics on a few addresses are needless once the maximum is in place.
-// A stale read is never above the current value, so nothing needed is
-// skipped.
-__device__ __forceinline__ void max_commit(unsigned long long *a, double v) {
-    const unsigned long long b = dbits(v);
-    if (b > __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a, b);
-}
-
 // Radii of every cell at every level in one pass over the particles.  Each
 // wavefront owns 64 * RADII_ROWS consecutive particles, holds their positions
 // and their current ancestors (with the ancestors' levels: a parent is one
 // level up), and goes up the tree level by level (deepest first): the centre
 // loads of all rows are issued together, then per row the squared distances
 // are reduced per cell across the 64 lanes (cells are contiguous particle
-// ranges, so equal cells are adjacent lanes), the cell that spills into the
-// next row is carried, and each cell's maximum is committed with one atomic
-// per wavefront.  CAND = false: squared distances to the box midpoint and the
-// centre of mass, into rho2[3c] and rho2[3c + 1]; CAND = true: to the
-// enclosing-sphere candidate, into rho2[3c + 2].
+// ranges, so equal cells are adjacent lanes): a maximum scan within each run
+// of equal cells, whose lane exchanges are DPP moves, the rows side by side.
+// Then the cell that spills into the next row is carried, and each cell's
+// maximum is committed with one atomic per wavefront.  CAND = false: squared
+// distances to the box midpoint and the centre of mass, into rho2[3c] and
+// rho2[3c + 1]; CAND = true: to the enclosing-sphere candidate, into
+// rho2[3c + 2].  Bound by the chain of parents, a load and a commit per level: 2000
+// bodies 47 -> 32 us, 3 x 10^5 in 28 levels 150 -> 114 (CAND 85 -> 72) against
+// cross-lane reads through LDS and commits one row after the other.
 template <bool CAND>
 __global__ void __launch_bounds__(256)
 k_radii(TreeArrays t, int64_t n, const int *leaf_of, const int *leaf_cell, int maxlevel,
@@ -654,59 +650,70 @@ k_radii(TreeArrays t, int64_t n, const int *leaf_of, const int *leaf_cell, int m
             anc[j] = has ? par[j] : anc[j];
             alev[j] = has ? L - 1 : alev[j];
         }
-        int ckey = -1;
-        double cv[NV];
-#pragma unroll
-        for (int u = 0; u < NV; ++u) cv[u] = 0.0;
+        // maximum from the first lane of each run of equal cells to every lane
+        unsigned long long heads[RADII_ROWS];
 #pragma unroll
         for (int j = 0; j < RADII_ROWS; ++j) {
-            const int kj = key[j];
-            // segmented maximum towards the first lane of each run of equal keys
+            const int prev = __shfl_up(key[j], 1, FMM_WAVE);
+            heads[j] = __ballot(lane == 0 || prev != key[j]);
+            const int start = 63 - __clzll(heads[j] & (~0ull >> (63 - lane)));
+            const int in_row = max(start, lane & ~15);
 #pragma unroll
-            for (int off = 1; off < FMM_WAVE; off <<= 1) {
-                const int ok = __shfl_down(kj, off, FMM_WAVE);
-                double o[NV];
-#pragma unroll
-                for (int u = 0; u < NV; ++u) o[u] = __shfl_down(v[j][u], off, FMM_WAVE);
-                if (lane + off < FMM_WAVE && ok == kj) {
-#pragma unroll
-                    for (int u = 0; u < NV; ++u) v[j][u] = fmax(v[j][u], o[u]);
-                }
-            }
-            const int prev = __shfl_up(kj, 1, FMM_WAVE);
-            const bool head = kj >= 0 && (lane == 0 || prev != kj);
-            const int last = __shfl(kj, FMM_WAVE - 1, FMM_WAVE);
-            const int first = __shfl(kj, 0, FMM_WAVE);
-            // merge or flush the carried run
-            if (lane == 0 && ckey >= 0) {
-                if (first == ckey) {
-#pragma unroll
-                    for (int u = 0; u < NV; ++u) v[j][u] = fmax(v[j][u], cv[u]);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < NV; ++u) max_commit(&t.rho2[3 * ckey + SLOT + u], cv[u]);
-                }
-            }
-            // the run containing lane 63 may continue into the next row
-            const bool open = head && kj == last;
-            if (head && !open) {
-#pragma unroll
-                for (int u = 0; u < NV; ++u) max_commit(&t.rho2[3 * kj + SLOT + u], v[j][u]);
-            }
-            // hand the open run to lane 0 as the new carry
-            const unsigned long long om = __ballot(open);
-            if (om) {
-                const int src = __ffsll((long long)om) - 1;
-#pragma unroll
-                for (int u = 0; u < NV; ++u) cv[u] = __shfl(v[j][u], src, FMM_WAVE);
-                ckey = last;
-            } else {
-                ckey = -1;
+            for (int u = 0; u < NV; ++u) {
+                double &m = v[j][u];
+                double o = dpp_double<DPP_ROW_SHR + 1>(m);
+                if (lane - 1 >= in_row) m = fmax(m, o);
+                o = dpp_double<DPP_ROW_SHR + 2>(m);
+                if (lane - 2 >= in_row) m = fmax(m, o);
+                o = dpp_double<DPP_ROW_SHR + 4>(m);
+                if (lane - 4 >= in_row) m = fmax(m, o);
+                o = dpp_double<DPP_ROW_SHR + 8>(m);
+                if (lane - 8 >= in_row) m = fmax(m, o);
+                o = dpp_double<DPP_BCAST15>(m);
+                if ((lane & 16) && (lane & ~15) > start) m = fmax(m, o);
+                o = dpp_double<DPP_BCAST31>(m);
+                if (lane >= 32 && 32 > start) m = fmax(m, o);
             }
         }
-        if (lane == 0 && ckey >= 0) {
+        // the run that reaches the end of a row may go on in the next one; the
+        // last lane of every run commits
+        unsigned long long commits[RADII_ROWS];
 #pragma unroll
-            for (int u = 0; u < NV; ++u) max_commit(&t.rho2[3 * ckey + SLOT + u], cv[u]);
+        for (int j = 0; j < RADII_ROWS; ++j) {
+            commits[j] = (heads[j] >> 1) | (1ull << (FMM_WAVE - 1));
+            if (j == 0) continue;
+            if (__builtin_amdgcn_readlane(key[j - 1], FMM_WAVE - 1) !=
+                __builtin_amdgcn_readlane(key[j], 0)) continue;
+            commits[j - 1] &= ~(1ull << (FMM_WAVE - 1));
+            const unsigned long long rest = heads[j] & ~1ull;
+            const bool cont = !rest || lane < __ffsll((long long)rest) - 1;
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                const double carry = readlane_f64(v[j - 1][u], FMM_WAVE - 1);
+                if (cont) v[j][u] = fmax(v[j][u], carry);
+            }
+        }
+        // Only where it raises the value seen: the top cells get one commit per
+        // wavefront, and most of those atomics on a few addresses are needless
+        // once the maximum is in place.  An old value is never above the current
+        // one, so nothing needed is skipped.  All rows read before any commits.
+        unsigned long long seen[RADII_ROWS][NV];
+#pragma unroll
+        for (int j = 0; j < RADII_ROWS; ++j) {
+            if (key[j] < 0 || !((commits[j] >> lane) & 1)) continue;
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                seen[j][u] = __hip_atomic_load(&t.rho2[3 * key[j] + SLOT + u], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int j = 0; j < RADII_ROWS; ++j) {
+            if (key[j] < 0 || !((commits[j] >> lane) & 1)) continue;
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                const unsigned long long b = dbits(v[j][u]);
+                if (b > seen[j][u]) atomicMax(&t.rho2[3 * key[j] + SLOT + u], b);
+            }
         }
     }
 }
@@ -983,8 +990,10 @@ __device__ __forceinline__ void enclosing_cell(const TreeArrays &t, int c, int s
 }
 
 // every leaf (lane groups of whole wavefronts), then the internal cells of
-// levels Lhi .. Llo as the geometry does (a run of levels: at most one block of
-// lane groups each)
+// levels Lhi .. Llo.  A cell needs its grand-daughters' spheres and those of
+// leaves, not its daughters': two levels at a time (their cells lie side by
+// side), which halves the chain of about 30 us steps that a deep tree has; a run
+// of pairs of at most one block of lane groups each is one launch.
 __global__ void __launch_bounds__(256)
 k_enclosing_leaves(TreeArrays t, int nleaves, const int *leaf_cell, const double *x,
                    const double *y, const double *z) {
@@ -998,10 +1007,10 @@ __global__ void __launch_bounds__(THREADS)
 k_enclosing_levels(TreeArrays t, LevelStart ls, int Lhi, int Llo, const double *x,
                    const double *y, const double *z) {
     const int gt = blockIdx.x * THREADS + threadIdx.x;
-    for (int L = Lhi; L >= Llo; --L) {
-        const int c = ls.first[L] + gt / ENC_G;
+    for (int L = Lhi; L >= Llo; L -= 2) {
+        const int c = ls.first[max(L - 1, 0)] + gt / ENC_G;
         if (c < ls.first[L + 1] && t.nchild[c] > 0) enclosing_cell(t, c, gt % ENC_G, x, y, z);
-        if (L > Llo) __syncthreads();     // (one block)
+        if (L - 2 >= Llo) __syncthreads();     // (one block)
     }
 }
 
@@ -1200,17 +1209,24 @@ hipError_t launch_enclosing(const TreeArrays &t, const LevelStart &ls, int depth
                             const double *z, hipStream_t s) {
     hipLaunchKernelGGL(k_enclosing_leaves, dim3(blocks((int64_t)nleaves * ENC_G, 256)), dim3(256),
                        0, s, t, nleaves, leaf_cell, x, y, z);
-    return up_levels(ls, depth, 1024 / ENC_G, [&](int Lhi, int Llo) {
-        if (Lhi > Llo) {
-            hipLaunchKernelGGL(k_enclosing_levels<1024>, dim3(1), dim3(1024), 0, s, t, ls, Lhi,
-                               Llo, x, y, z);
-        } else {
-            const int64_t nc = ls.first[Lhi + 1] - ls.first[Lhi];
-            hipLaunchKernelGGL(k_enclosing_levels<256>, dim3(blocks(nc * ENC_G, 256)), dim3(256),
-                               0, s, t, ls, Lhi, Llo, x, y, z);
-        }
-        return hipGetLastError();
-    });
+    // pairs (L, L - 1) from the level above the deepest, whose cells are leaves
+    auto cells = [&](int L) { return ls.first[L + 1] - ls.first[std::max(L - 1, 0)]; };
+    for (int L = depth - 1; L >= 0;) {
+        int lo = L;
+        const bool few = cells(L) <= 1024 / ENC_G;
+        while (few && lo >= 2 && cells(lo - 2) <= 1024 / ENC_G) lo -= 2;
+        if (few)
+            hipLaunchKernelGGL(k_enclosing_levels<1024>, dim3(1), dim3(1024), 0, s, t, ls, L, lo,
+                               x, y, z);
+        else
+            hipLaunchKernelGGL(k_enclosing_levels<256>,
+                               dim3(blocks((int64_t)cells(L) * ENC_G, 256)), dim3(256), 0, s, t,
+                               ls, L, L, x, y, z);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        L = lo - 2;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_radii(const TreeArrays &t, int64_t n, const int *leaf_of, const int *leaf_cell,
