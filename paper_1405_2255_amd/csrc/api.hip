@@ -447,19 +447,24 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
         // small frontiers is one launch, and one more ends the list, for the
         // sweeps that come out differently.  Without a last walk, or while pairs
         // are left, a few sweeps at a time.
-        std::vector<char> plan;
+        std::vector<WalkHow> plan;
         const std::vector<int64_t> &last = c->walk_front[wp.mode];
         for (size_t i = 0; i < last.size(); ++i) {
-            const bool small = last[i] <= WALK_SMALL - WALK_SMALL / 8;
-            if (!small || plan.empty() || !plan.back()) plan.push_back(small);
+            const WalkHow how = last[i] <= WALK_SMALL - WALK_SMALL / 8 ? WALK_SMALL_RUN
+                                : last[i] <= WALK_TILED               ? WALK_TILE_SWEEP
+                                                                      : WALK_FULL_SWEEP;
+            if (how != WALK_SMALL_RUN || plan.empty() || plan.back() != how) plan.push_back(how);
         }
-        if (last.empty()) plan.assign({1, 0, 0, 0, 0, 0, 0, 0, 0});
-        if (!plan.back()) plan.push_back(1);
+        if (last.empty()) {
+            plan.assign(9, WALK_FULL_SWEEP);
+            plan[0] = WALK_SMALL_RUN;
+        }
+        if (plan.back() != WALK_SMALL_RUN) plan.push_back(WALK_SMALL_RUN);
         int launched = 0, cur = 0;
         for (;;) {
             if (launched + (int)plan.size() > WALK_LAUNCHES)
                 throw HipFail{hipErrorUnknown, "walk did not terminate"};
-            for (char small : plan) CK(launch_walk(wp, t, P, wb, launched++, small != 0, btmp, s));
+            for (WalkHow how : plan) CK(launch_walk(wp, t, P, wb, launched++, how, btmp, s));
             if (c->opts.timing) CK(hipEventRecord(c->ev_walk[1], s));
             CK(hipMemcpyAsync(c->hcnt, cnt, (WALK_CUR + launched + 1) * sizeof(unsigned long long),
                               hipMemcpyDeviceToHost, s));
@@ -468,7 +473,8 @@ Lists walk(fmm_ctx *c, const WalkParams &wp0, const double *P) {
             if (c->hcnt[3] || cur >= sweeps || (cur > 0 && c->hcnt[4 + cur - 1] == 0)) break;
             // a frontier past its buffer: nothing more can run
             if (cur > 0 && (int64_t)c->hcnt[4 + cur - 1] > cap_f) break;
-            plan.assign({0, 0, 0, 0, 0, 0, 1});
+            plan.assign(7, WALK_FULL_SWEEP);
+            plan[6] = WALK_SMALL_RUN;
         }
         const unsigned long long *h = c->hcnt;
         int64_t maxf = 0, visited = 1;

@@ -173,26 +173,34 @@ struct WalkBuffers {
     uint64_t *p2p; uint32_t *p2p_end; int64_t cap_p2p;   // key, end of the source range
     unsigned long long *counters;   // [0] m2l, [1] direct entries, [2] direct particle
                                     // pairs, [3] overflow, [4 + i] frontier after sweep i,
-                                    // [WALK_CUM + 3 i + k] those three totals before sweep i,
-                                    // [WALK_CUR + j] the sweep that launch j begins with
+                                    // [WALK_CUM + 2 i + k] the first two before sweep i,
+                                    // [WALK_CUR + j] the sweep that launch j begins with,
+                                    // [WALK_TICKETS + i] tiles of sweep i drawn,
+                                    // [WALK_ENTRIES + 3 j + k] what tile j has published
     uint16_t *code;                 // cap_out: each input pair's decision (count -> write)
 };
 // Launch j takes the sweep in counters[WALK_CUR + j] (launch 0: sweep 0) and
 // leaves the next one in counters[WALK_CUR + j + 1]; sweep i reads its frontier
 // size from counters[4 + i - 1] (sweep 0: the roots) and does nothing if it is 0.
-// small: one block takes sweeps as long as their frontiers hold at most
-// WALK_SMALL pairs (none if the first is larger); else one sweep over the
-// whole chip.  btmp holds walk_tmp_u64() entries of per-block scratch.
+// A small run takes sweeps as long as their frontiers hold at most WALK_SMALL pairs
+// (none if the first is larger), a tile sweep one sweep of at most WALK_TILES
+// tiles (none if it is larger), a full sweep any.  btmp holds walk_tmp_u64()
+// entries of per-block scratch.
+enum WalkHow : char { WALK_FULL_SWEEP, WALK_SMALL_RUN, WALK_TILE_SWEEP };
+constexpr int WALK_TILES = 1024;                            // of 256 pairs
+constexpr int64_t WALK_TILED = 65536;                       // pairs: see walk.hip
 constexpr int WALK_SMALL = 4096;
 constexpr int WALK_SWEEPS = 2 * FMM_MAXLEVEL + 4;           // most sweeps of a walk
 constexpr int WALK_CUM = 4 + WALK_SWEEPS;
-constexpr int WALK_CUR = WALK_CUM + 3 * (WALK_SWEEPS + 1);
+constexpr int WALK_CUR = WALK_CUM + 2 * (WALK_SWEEPS + 1);
 constexpr int WALK_LAUNCHES = 4 * WALK_SWEEPS;              // most launches of a walk
-constexpr int WALK_COUNTERS = WALK_CUR + WALK_LAUNCHES + 1;
+constexpr int WALK_TICKETS = WALK_CUR + WALK_LAUNCHES + 1;
+constexpr int WALK_ENTRIES = WALK_TICKETS + WALK_SWEEPS;
+constexpr int WALK_COUNTERS = WALK_ENTRIES + 3 * WALK_TILES;
 size_t walk_tmp_u64();
 hipError_t launch_root_pairs(uint2 *f, int nroots, hipStream_t s);
 hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *P,
-                       const WalkBuffers &wb, int launch, bool small, unsigned long long *btmp,
+                       const WalkBuffers &wb, int launch, WalkHow how, unsigned long long *btmp,
                        hipStream_t s);
 // offsets of the sorted (sink << sh | source) list per sink: off[c] for c in [0, nsinks]
 // (count: device, the list's length in place of nlist where not null)

@@ -39,19 +39,21 @@ struct Decision {
     int kind;      // 0 none, 1 self-split, 2 split A, 3 split B, 4 direct, 5 M2L
     int nf;        // frontier pairs emitted
     double pairs;  // particle pairs summed directly
+    int o0, o1;    // what the outputs need: the split cell's first child and child
+                   // count, or A's particle range
 };
 
 __device__ __forceinline__ Decision decide(const WalkParams &wp, const TreeArrays &t,
                                            const double *P, int A, int B) {
-    if (wp.active && !wp.active[B]) return {0, 0, 0.0};   // no listed sink below B
+    if (wp.active && !wp.active[B]) return {0, 0, 0.0, 0, 0};   // no listed sink below B
     const int4 ia = t.info[A], ib = t.info[B];
     const int nchA = ia.w, nchB = ib.w;
     if (A == B) {
         if (nchA == 0) {
             const double na = (double)(ia.y - ia.x);
-            return {4, 0, na * (na - 1.0)};
+            return {4, 0, na * (na - 1.0), ia.x, ia.y};
         }
-        return {1, nchA * nchA, 0.0};
+        return {1, nchA * nchA, 0.0, ia.z, nchA};
     }
     const bool est = wp.mode == 2;
     const double4 ca = est ? t.com[A] : t.cen[A];
@@ -83,37 +85,213 @@ __device__ __forceinline__ Decision decide(const WalkParams &wp, const TreeArray
     const double na = (double)(ia.y - ia.x);
     const double nb = (double)(ib.y - ib.x);
     if (acc) {
-        if (wp.mode != 2 && na * nb < wp.p2p_pairs) return {4, 0, na * nb};
-        return {5, 0, 0.0};
+        if (wp.mode != 2 && na * nb < wp.p2p_pairs) return {4, 0, na * nb, ia.x, ia.y};
+        return {5, 0, 0.0, 0, 0};
     }
-    if (nchA == 0 && nchB == 0) return {4, 0, na * nb};
+    if (nchA == 0 && nchB == 0) return {4, 0, na * nb, ia.x, ia.y};
     if (nchB == 0 && rB >= tc * (r + rA) * (1.0 + 1e-12)) {
         // B cannot be split, and no cell below A can pass the radius test
         // against it: every centre below A lies in A's sphere, so its distance
         // to B is at most r + rho_A.  The recursion would end in direct sums
         // with all of A's leaves.
-        return {4, 0, na * nb};
+        return {4, 0, na * nb, ia.x, ia.y};
     }
     const bool splitA = nchA > 0 && (nchB == 0 || rA > rB);
-    return {splitA ? 2 : 3, splitA ? nchA : nchB, 0.0};
+    return {splitA ? 2 : 3, splitA ? nchA : nchB, 0.0, splitA ? ia.z : ib.z, 0};
 }
 
 // Sweeps run without host round trips: sweep i reads its frontier size from
-// counters[4 + i - 1].  A sweep with a large frontier is two launches over a fixed grid of
-// WALK_BLOCKS blocks, block b owning a contiguous chunk of the frontier:
-// count (per-block totals) and write (each block sums the totals of the
-// blocks before it for its offsets, block 0 the sweep's totals; then the
-// outputs at their offsets, in frontier order).  No atomics; the output order
-// is deterministic.  Sweeps whose frontier holds at most WALK_SMALL pairs are
-// bound by launches and by the latency of a chain of dependent loads: one
-// block takes a run of them in a single launch, in the same order.
+// counters[4 + i - 1].  Three ways, by the size of the frontier; the output order
+// is the frontier's in each, so the lists are the same:
+//  - up to WALK_SMALL pairs a sweep is bound by launches and by the latency of a
+//    chain of dependent loads: one block takes a run of sweeps in one launch;
+//  - up to WALK_TILES tiles of a pair per thread, one launch: a block draws a tile
+//    by ticket, decides its pairs, publishes the counts of their outputs, learns
+//    the outputs of the tiles before it from what those have published, and
+//    writes its own;
+//  - above, count (per-block totals) and write (each block sums the totals of
+//    the blocks before it for its offsets, block 0 the sweep's totals; then
+//    the outputs), over a fixed grid of WALK_BLOCKS blocks, block b owning a
+//    contiguous chunk of the frontier.
+// The tickets and the waits cost more than a second pass once there are many
+// tiles: whole calls of 10^4 bodies 1.29 ms with tiles and 1.37 without, of 10^6
+// 16.4 ms where all sweeps go by tiles and 16.0 where none does.  The host asks
+// for tiles up to WALK_TILED pairs (200000 and 32768: both within 1% of it).
 constexpr int WALK_BLOCKS = 1024;
 constexpr int WALK_THREADS = 256;
+constexpr int WALK_WAVES = WALK_THREADS / FMM_WAVE;
 constexpr int WALK_WBATCH = 4;  // rounds whose loads the write kernel issues together
 
 __device__ __forceinline__ int64_t sweep_input(const WalkParams &wp,
                                                const unsigned long long *cnt, int sweep) {
     return sweep == 0 ? wp.nroots : (int64_t)cnt[4 + sweep - 1];
+}
+
+// the outputs of one pair (A, B): frontier pairs from pf on, or the M2L entry
+// pm, or the direct-sum entry pp (dropped past the buffers' ends)
+__device__ __forceinline__ void write_outputs(const WalkParams &wp, const WalkBuffers &wb,
+                                              uint2 *out, int kind, int n, int A, int B, int o0,
+                                              int o1, int64_t pf, int64_t pm, int64_t pp) {
+    switch (kind) {
+    case 1:     // all ordered daughter pairs of A
+        if (pf + n <= wb.cap_out)
+            for (int a = 0; a < o1; ++a)
+                for (int b = 0; b < o1; ++b) out[pf + a * o1 + b] = make_uint2(o0 + a, o0 + b);
+        break;
+    case 2:
+        if (pf + n <= wb.cap_out)
+            for (int a = 0; a < n; ++a) out[pf + a] = make_uint2(o0 + a, B);
+        break;
+    case 3:
+        if (pf + n <= wb.cap_out)
+            for (int b = 0; b < n; ++b) out[pf + b] = make_uint2(A, o0 + b);
+        break;
+    case 4:     // direct sum of A's particles onto B's (B may be any cell)
+        if (pp + 1 <= wb.cap_p2p) {
+            if (wp.pack) {
+                wb.p2p[pp] = ((uint64_t)B << (2 * wp.pb)) | ((uint64_t)o0 << wp.pb) |
+                             (uint64_t)o1;
+            } else {
+                wb.p2p[pp] = ((uint64_t)B << wp.pb) | (uint64_t)o0;
+                wb.p2p_end[pp] = (uint32_t)o1;
+            }
+        }
+        break;
+    case 5:
+        if (pm + 1 <= wb.cap_m2l) wb.m2l[pm] = ((uint64_t)B << wp.sh) | (uint64_t)A;
+        break;
+    default:
+        break;
+    }
+}
+
+// The three counts of a pair's outputs share one 64-bit word: frontier pairs in
+// bits 0..23 (at most 64 per pair), M2L entries in 24..43, direct entries in
+// 44..63.
+__device__ __forceinline__ unsigned long long pack_counts(const Decision &d) {
+    return (unsigned long long)d.nf | ((unsigned long long)(d.kind == 5) << 24) |
+           ((unsigned long long)(d.kind == 4) << 44);
+}
+__device__ __forceinline__ unsigned long long count_of(unsigned long long c, int k) {
+    return k == 0 ? c & 0xffffffu : k == 1 ? (c >> 24) & 0xfffffu : c >> 44;
+}
+
+__device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int off = 1; off < FMM_WAVE; off <<= 1) {
+        const unsigned long long o = __shfl_up(v, off, FMM_WAVE);
+        if (lane >= off) v += o;
+    }
+    return v;
+}
+
+// A tile's published counts, one word per kind of output: the sweep (+ 1) in the
+// upper bits, so that the words of earlier sweeps count as empty; whether the
+// count is that of this and all earlier tiles; the count.
+constexpr int WALK_TAG = 57;
+constexpr unsigned long long WALK_RUNNING = 1ull << 56;
+
+// outputs of kind k in all tiles before this one (one wavefront: the lanes read
+// 64 tiles at a time, backwards, until a running count).  Tiles are drawn in
+// order by blocks that publish before they wait, so the wait ends.
+__device__ __forceinline__ unsigned long long
+walk_before(const unsigned long long *entry, int tile, int k, unsigned long long tag) {
+    const int lane = lane_id();
+    unsigned long long sum = 0;
+    for (int t0 = tile - 1; t0 >= 0;) {
+        const int j = t0 - lane;
+        const unsigned long long e =
+            j >= 0 ? __hip_atomic_load(entry + 3 * (size_t)j + k, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT)
+                   : tag << WALK_TAG | WALK_RUNNING;
+        const bool here = e >> WALK_TAG == tag;
+        const unsigned long long run = __ballot(here && (e & WALK_RUNNING));
+        const unsigned long long empty = __ballot(!here);
+        const int last = run ? __ffsll((long long)run) - 1 : FMM_WAVE - 1;
+        if (empty & (~0ull >> (63 - last))) {
+            __builtin_amdgcn_s_sleep(1);
+            continue;
+        }
+        unsigned long long v = lane <= last ? e & (WALK_RUNNING - 1) : 0;
+#pragma unroll
+        for (int o = FMM_WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, FMM_WAVE);
+        sum += v;
+        if (run) break;
+        t0 -= FMM_WAVE;
+    }
+    return sum;
+}
+
+__global__ void __launch_bounds__(WALK_THREADS)
+k_walk_tiles(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch) {
+    __shared__ unsigned long long ws[WALK_WAVES], before[3];
+    __shared__ double red[WALK_WAVES];
+    __shared__ int stile;
+    unsigned long long *cnt = wb.counters;
+    const int sweep = (int)cnt[WALK_CUR + launch];
+    const int64_t n_in = sweep_input(wp, cnt, sweep);
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / FMM_WAVE;
+    const bool can = n_in > 0 && n_in <= wb.cap_out &&
+                     n_in <= (int64_t)WALK_TILES * WALK_THREADS;
+    if (blockIdx.x == 0 && tid == 0) cnt[WALK_CUR + launch + 1] = sweep + can;
+    const int ntiles = (int)((n_in + WALK_THREADS - 1) / WALK_THREADS);
+    if (!can || (int)blockIdx.x >= ntiles) return;
+    unsigned long long *entry = cnt + WALK_ENTRIES;
+    const unsigned long long tag = sweep + 1;
+    const unsigned long long *cum = cnt + WALK_CUM + 2 * sweep;   // totals before this sweep
+    const unsigned long long m0 = cum[0], p0 = cum[1];
+    if (tid == 0) stile = (int)atomicAdd(cnt + WALK_TICKETS + sweep, 1ull);
+    __syncthreads();
+    const int tile = stile;
+    const int64_t i = (int64_t)tile * WALK_THREADS + tid;
+    Decision d{0, 0, 0.0, 0, 0};
+    uint2 pr = make_uint2(0u, 0u);
+    if (i < n_in) {
+        pr = wb.front[sweep & 1][i];
+        d = decide(wp, t, P, (int)pr.x, (int)pr.y);
+    }
+    const unsigned long long mine = pack_counts(d), incl = wave_incl_scan64(mine);
+    const double pairs = wave_sum(d.pairs);
+    if (lane == FMM_WAVE - 1) {
+        ws[w] = incl;
+        red[w] = pairs;
+    }
+    __syncthreads();
+    unsigned long long total = 0, first = incl - mine;   // in the tile, in this and earlier
+#pragma unroll
+    for (int q = 0; q < WALK_WAVES; ++q) {
+        if (q < w) first += ws[q];
+        total += ws[q];
+    }
+    if (w < 3) {
+        unsigned long long *own = entry + 3 * (size_t)tile + w;
+        const unsigned long long c = count_of(total, w), head = tag << WALK_TAG;
+        if (lane == 0)
+            __hip_atomic_store(own, head | (tile == 0 ? WALK_RUNNING : 0) | c, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long b = walk_before(entry, tile, w, tag);
+        if (lane == 0) {
+            if (tile > 0)
+                __hip_atomic_store(own, head | WALK_RUNNING | (b + c), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            before[w] = b;
+        }
+    } else if (lane == 0) {
+        double s = 0.0;
+        for (int q = 0; q < WALK_WAVES; ++q) s += red[q];
+        if (s > 0.0) atomicAdd(cnt + 2, (unsigned long long)s);
+    }
+    __syncthreads();
+    const unsigned long long of = before[0], om = m0 + before[1], op = p0 + before[2];
+    write_outputs(wp, wb, wb.front[(sweep + 1) & 1], d.kind, d.nf, (int)pr.x, (int)pr.y, d.o0,
+                  d.o1, (int64_t)(of + count_of(first, 0)), (int64_t)(om + count_of(first, 1)),
+                  (int64_t)(op + count_of(first, 2)));
+    if (tile == ntiles - 1 && tid == 0) {
+        cnt[4 + sweep] = of + count_of(total, 0);
+        cnt[0] = cnt[WALK_CUM + 2 * (sweep + 1)] = om + count_of(total, 1);
+        cnt[1] = cnt[WALK_CUM + 2 * (sweep + 1) + 1] = op + count_of(total, 2);
+    }
 }
 
 // block-wide inclusive scan of three ints (256 threads = 4 waves)
@@ -210,7 +388,7 @@ k_walk_count(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
 // Offsets of this block's outputs (the sum of the count pass's totals of the
 // blocks before it) and, in block 0, the sweep's totals: the frontier size
 // for the next sweep and the running list sizes, kept per sweep in
-// counters[WALK_CUM + 3 i + k] so that no block reads a value another block of
+// counters[WALK_CUM + 2 i + k] so that no block reads a value another block of
 // this launch writes.
 __device__ __forceinline__ void walk_offsets(const unsigned long long *btot, bool need_prefix,
                                              unsigned long long (&pre)[3],
@@ -247,46 +425,6 @@ __device__ __forceinline__ void walk_offsets(const unsigned long long *btot, boo
     }
 }
 
-// the outputs of one pair (A, B): frontier pairs from pf on, or the M2L entry
-// pm, or the direct-sum entry pp (dropped past the buffers' ends)
-__device__ __forceinline__ void write_outputs(const WalkParams &wp, const WalkBuffers &wb,
-                                              uint2 *out, int kind, int n, int A, int B,
-                                              int4 ia, int4 ib, int64_t pf, int64_t pm,
-                                              int64_t pp) {
-    const int begA = ia.x, endA = ia.y, kA = ia.z, nchA = ia.w, kB = ib.z;
-    switch (kind) {
-    case 1:     // all ordered daughter pairs of A
-        if (pf + n <= wb.cap_out)
-            for (int a = 0; a < nchA; ++a)
-                for (int b = 0; b < nchA; ++b) out[pf + a * nchA + b] = make_uint2(kA + a, kA + b);
-        break;
-    case 2:
-        if (pf + n <= wb.cap_out)
-            for (int a = 0; a < n; ++a) out[pf + a] = make_uint2(kA + a, B);
-        break;
-    case 3:
-        if (pf + n <= wb.cap_out)
-            for (int b = 0; b < n; ++b) out[pf + b] = make_uint2(A, kB + b);
-        break;
-    case 4:     // direct sum of A's particles onto B's (B may be any cell)
-        if (pp + 1 <= wb.cap_p2p) {
-            if (wp.pack) {
-                wb.p2p[pp] = ((uint64_t)B << (2 * wp.pb)) | ((uint64_t)begA << wp.pb) |
-                             (uint64_t)endA;
-            } else {
-                wb.p2p[pp] = ((uint64_t)B << wp.pb) | (uint64_t)begA;
-                wb.p2p_end[pp] = (uint32_t)endA;
-            }
-        }
-        break;
-    case 5:
-        if (pm + 1 <= wb.cap_m2l) wb.m2l[pm] = ((uint64_t)B << wp.sh) | (uint64_t)A;
-        break;
-    default:
-        break;
-    }
-}
-
 __global__ void __launch_bounds__(WALK_THREADS)
 k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch,
              const unsigned long long *btot) {
@@ -303,14 +441,14 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
     if (blockIdx.x != 0 && (!fits || lo >= hi)) return;   // nothing to write
     unsigned long long pre[3], tot[4];
     walk_offsets(btot, fits && lo < hi, pre, tot);
-    unsigned long long *cum = cnt + WALK_CUM + 3 * sweep;   // totals before this sweep
+    unsigned long long *cum = cnt + WALK_CUM + 2 * sweep;   // totals before this sweep
     const unsigned long long m0 = cum[0], p0 = cum[1];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!fits) cnt[3] = 1ull;
         cnt[4 + sweep] = tot[0];
-        cum[3] = cnt[0] = m0 + tot[1];
-        cum[4] = cnt[1] = p0 + tot[2];
-        cum[5] = cnt[2] = cum[2] + tot[3];
+        cum[2] = cnt[0] = m0 + tot[1];
+        cum[3] = cnt[1] = p0 + tot[2];
+        cnt[2] += tot[3];
     }
     if (!fits) return;
     int64_t of = (int64_t)pre[0];
@@ -347,7 +485,8 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
             block_scan3(sf, sm, sp, tot);
             const int64_t pf = of + sf - n, pm = om + sm - (k == 5), pp = op + sp - (k == 4);
             const int a0 = A[r], b0 = B[r];
-            write_outputs(wp, wb, out, k, n, a0, b0, ia[r], ib[r], pf, pm, pp);
+            const int o0 = k == 3 ? ib[r].z : k == 4 ? ia[r].x : ia[r].z;
+            write_outputs(wp, wb, out, k, n, a0, b0, o0, k == 4 ? ia[r].y : ia[r].w, pf, pm, pp);
             of += tot[0];
             om += tot[1];
             op += tot[2];
@@ -357,24 +496,12 @@ k_walk_write(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
 
 // A run of sweeps with small frontiers, one block: each thread decides up to
 // SMALL_B pairs (pair r * SMALL_THREADS + thread), the counts of all pairs are
-// scanned in frontier order, and the outputs are written.  The three counts of
-// a pair share one 64-bit word: frontier pairs in bits 0..23 (at most 64 per
-// pair), M2L entries in 24..43, direct entries in 44..63.
+// scanned in frontier order, and the outputs are written.
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_B = WALK_SMALL / SMALL_THREADS;
 constexpr int SMALL_WAVES = SMALL_THREADS / FMM_WAVE;
 static_assert(SMALL_B * SMALL_WAVES == FMM_WAVE, "one wavefront scans the wavefronts' totals");
 static_assert(WALK_SMALL * 64 < (1 << 24), "frontier count field");
-
-__device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < FMM_WAVE; off <<= 1) {
-        const unsigned long long o = __shfl_up(v, off, FMM_WAVE);
-        if (lane >= off) v += o;
-    }
-    return v;
-}
 
 __global__ void __launch_bounds__(SMALL_THREADS)
 k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int launch) {
@@ -384,9 +511,8 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
     const int tid = threadIdx.x, lane = lane_id(), w = tid / FMM_WAVE;
     int sweep = (int)cnt[WALK_CUR + launch];
     int64_t n_in = sweep_input(wp, cnt, sweep);
-    const unsigned long long *cum = cnt + WALK_CUM + 3 * sweep;
+    const unsigned long long *cum = cnt + WALK_CUM + 2 * sweep;
     unsigned long long m0 = cum[0], p0 = cum[1];
-    const unsigned long long pairs0 = cum[2];
     double pairs = 0.0;
     const int first = sweep;
     while (n_in > 0 && n_in <= WALK_SMALL && n_in <= wb.cap_out && sweep < WALK_SWEEPS) {
@@ -403,13 +529,12 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
         }
 #pragma unroll
         for (int r = 0; r < SMALL_B; ++r) {
-            Decision d{0, 0, 0.0};
+            Decision d{0, 0, 0.0, 0, 0};
             if (r * SMALL_THREADS + tid < n_in) d = decide(wp, t, P, A[r], B[r]);
             kind[r] = d.kind;
             nf[r] = d.nf;
             pairs += d.pairs;
-            c[r] = (unsigned long long)d.nf | ((unsigned long long)(d.kind == 5) << 24) |
-                   ((unsigned long long)(d.kind == 4) << 44);
+            c[r] = pack_counts(d);
         }
         unsigned long long incl[SMALL_B];
 #pragma unroll
@@ -429,18 +554,21 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
         for (int r = 0; r < SMALL_B; ++r) {
             if (kind[r] == 0) continue;
             const unsigned long long o = ws[r * SMALL_WAVES + w] + incl[r] - c[r];
-            const int a = A[r], b = B[r];
-            write_outputs(wp, wb, out, kind[r], nf[r], a, b, t.info[a], t.info[b],
-                          (int64_t)(o & 0xffffffu), (int64_t)(m0 + ((o >> 24) & 0xfffffu)),
-                          (int64_t)(p0 + (o >> 44)));
+            // (read again: there are no registers to keep them)
+            const int4 ia = t.info[A[r]], ib = t.info[B[r]];
+            const int o0 = kind[r] == 3 ? ib.z : kind[r] == 4 ? ia.x : ia.z;
+            const int o1 = kind[r] == 4 ? ia.y : ia.w;
+            write_outputs(wp, wb, out, kind[r], nf[r], A[r], B[r], o0, o1,
+                          (int64_t)count_of(o, 0), (int64_t)(m0 + count_of(o, 1)),
+                          (int64_t)(p0 + count_of(o, 2)));
         }
-        n_in = (int64_t)(total & 0xffffffu);
-        m0 += (total >> 24) & 0xfffffu;
-        p0 += total >> 44;
+        n_in = (int64_t)count_of(total, 0);
+        m0 += count_of(total, 1);
+        p0 += count_of(total, 2);
         if (tid == 0) {
             cnt[4 + sweep] = (unsigned long long)n_in;
-            cnt[WALK_CUM + 3 * (sweep + 1)] = m0;
-            cnt[WALK_CUM + 3 * (sweep + 1) + 1] = p0;
+            cnt[WALK_CUM + 2 * (sweep + 1)] = m0;
+            cnt[WALK_CUM + 2 * (sweep + 1) + 1] = p0;
         }
         ++sweep;
         __syncthreads();    // the outputs are this block's next inputs
@@ -454,7 +582,7 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
     for (int i = 1; i < SMALL_WAVES; ++i) pairs += red[i];
     cnt[0] = m0;
     cnt[1] = p0;
-    cnt[2] = cnt[WALK_CUM + 3 * sweep + 2] = pairs0 + (unsigned long long)pairs;
+    cnt[2] += (unsigned long long)pairs;
 }
 
 __global__ void k_list_offsets(const uint64_t *list, int64_t nlist, const int *count, int nsinks,
@@ -541,7 +669,6 @@ hipError_t launch_range_merge(const uint64_t *key, const uint32_t *end, int64_t 
     return hipGetLastError();
 }
 
-size_t walk_tmp_u64() { return 4 * (size_t)WALK_BLOCKS; }
 
 __global__ void k_root_pairs(uint2 *f, int nroots) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -553,11 +680,18 @@ hipError_t launch_root_pairs(uint2 *f, int nroots, hipStream_t s) {
     return hipGetLastError();
 }
 
+size_t walk_tmp_u64() { return 4 * (size_t)WALK_BLOCKS; }
+
 hipError_t launch_walk(const WalkParams &wp, const TreeArrays &t, const double *P,
-                       const WalkBuffers &wb, int launch, bool small, unsigned long long *btmp,
+                       const WalkBuffers &wb, int launch, WalkHow how, unsigned long long *btmp,
                        hipStream_t s) {
-    if (small) {
+    if (how == WALK_SMALL_RUN) {
         hipLaunchKernelGGL(k_walk_small, dim3(1), dim3(SMALL_THREADS), 0, s, wp, t, P, wb, launch);
+        return hipGetLastError();
+    }
+    if (how == WALK_TILE_SWEEP) {
+        hipLaunchKernelGGL(k_walk_tiles, dim3(WALK_TILES), dim3(WALK_THREADS), 0, s, wp, t, P, wb,
+                           launch);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_walk_count, dim3(WALK_BLOCKS), dim3(WALK_THREADS), 0, s, wp, t, P, wb,
