@@ -27,7 +27,7 @@
 #include <climits>
 
 #include "internal.h"
-#include "dev.h"
+#include "lanes.h"
 
 namespace fmm {
 
