@@ -1351,7 +1351,7 @@ fmm_status fmm_direct(fmm_ctx *c, int64_t n, const double *pos, const double *ma
         return fmm::fail(c, FMM_E_INVAL, "bad argument");
     if (n == 0) return FMM_OK;
     return fmm::guarded(c, [&]() -> fmm_status {
-        const int nchunk = fmm::direct_sinks_chunks(n, n);
+        const int nchunk = (int)fmm::direct_rows(n, n);
         double4 *part = nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * n) : nullptr;
         CK(fmm::launch_direct_sinks(n, pos, mass, G, n, nullptr, nchunk, pot, acc, part, nullptr,
                                     c->stream));
@@ -1382,7 +1382,7 @@ fmm_status fmm_direct_sinks(fmm_ctx *c, int64_t n, const double *pos, const doub
     fmm_status st = check_direct_sinks(c, n, pos, mass, G, nsinks, sinks, pot, acc);
     if (st != FMM_OK || nsinks == 0) return st;
     return fmm::guarded(c, [&]() -> fmm_status {
-        const int nchunk = fmm::direct_sinks_chunks(n, nsinks);
+        const int nchunk = (int)fmm::direct_rows(n, nsinks);
         double4 *part =
             nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * nsinks) : nullptr;
         int *bad = fmm::ensure<int>(c->nonfinite, 8) + 5;
@@ -1405,7 +1405,7 @@ fmm_status fmm_direct_sinks_noalloc(fmm_ctx *c, int64_t n, const double *pos,
     c->err.clear();
     fmm_status st = check_direct_sinks(c, n, pos, mass, G, nsinks, sinks, pot, acc);
     if (st != FMM_OK || nsinks == 0) return st;
-    const int nchunk = fmm::direct_sinks_chunks(n, nsinks);
+    const int nchunk = (int)fmm::direct_rows(n, nsinks);
     const size_t rows = nchunk > 1 ? (size_t)nchunk * (size_t)nsinks * sizeof(double4) : 0;
     if (256 + rows > FMM_NOALLOC_SCRATCH_BYTES)
         return fmm::fail(c, FMM_E_INVAL, "the partial sums exceed the static scratch buffer");
@@ -1481,7 +1481,7 @@ fmm_status fmm_direct_jerk_sinks(fmm_ctx *c, int64_t n, const double *pos, const
     return fmm::guarded(c, [&]() -> fmm_status {
         int *bad = fmm::ensure<int>(c->nonfinite, 8) + 5;
         CK(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
-        const int nchunk = fmm::direct_sinks_chunks(n, nsinks);
+        const int nchunk = (int)fmm::direct_rows(n, nsinks);
         double4 *part =
             nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * nsinks) : nullptr;
         CK(fmm::launch_direct_jerk_sinks(n, pos, vel, mass, G, nsinks, sinks, nchunk, jerk, part,

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "split.h"
+
 #define FMM_KEYLEVELS 21                  // levels resolved by one 63-bit key
 #define FMM_MAXLEVEL (2 * FMM_KEYLEVELS)  // levels 22..42 use the second key word
 #define FMM_PMAX 20
@@ -346,14 +348,7 @@ hipError_t launch_scale(int want_f, int64_t n, const double4 *est4, double *scal
 // outside [0, n) sets *bad and its outputs are left alone).  The sources are cut
 // into nchunk chunks of ceil(n / nchunk), one per grid row; with nchunk > 1 the
 // partial sums go to part (nchunk * nsinks double4) and are added per sink in
-// chunk order.  direct_sinks_chunks gives the library's choice: about
-// DIRECT_WAVES wavefronts of DIRECT_R sinks (16 per SIMD, so that the last ones
-// cost little), chunks of at least DIRECT_SOURCES sources.  When nchunk > 1,
-// nchunk * nsinks < 2 * DIRECT_WAVES * DIRECT_R.
-#define DIRECT_R 8
-#define DIRECT_WAVES 16384
-#define DIRECT_SOURCES 512
-int direct_sinks_chunks(int64_t n, int64_t nsinks);
+// chunk order.  direct_rows (split.h) gives the library's choice.
 hipError_t launch_direct_sinks(int64_t n, const double *pos, const double *mass, double G,
                                int64_t nsinks, const int64_t *sinks, int nchunk, double *pot,
                                double *acc, double4 *part, int *bad, hipStream_t s);

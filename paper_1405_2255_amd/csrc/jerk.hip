@@ -444,7 +444,7 @@ hipError_t launch_direct_jerk_sinks(int64_t n, const double *pos, const double *
                                    int *bad, hipStream_t s) {
     if (nsinks <= 0) return hipSuccess;
     if (nchunk < 1 || (nchunk > 1 && !part)) return hipErrorInvalidValue;
-    const int64_t chunk = (n + nchunk - 1) / nchunk;
+    const int64_t chunk = row_length(n, nchunk);
     hipLaunchKernelGGL(k_direct_jerk_sinks, dim3(blocks(nsinks, 4 * DIRECT_R), (unsigned)nchunk),
                        dim3(256), 0, s, n, pos, vel, mass, G, nsinks, sinks, chunk, jerk,
                        nchunk > 1 ? part : nullptr, bad);

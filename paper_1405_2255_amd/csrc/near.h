@@ -217,7 +217,7 @@ template <class Fast, class Checked>
 __device__ __forceinline__ void direct_steps(const DirectSinks &d, int64_t j0, int64_t j1,
                                              Fast &&fast, Checked &&checked) {
     const uint32_t lane = lane_id();
-    const uint32_t len = (uint32_t)(j1 - j0);        // chunks hold at most 2^31 sources
+    const uint32_t len = slice_length(j0, j1);       // chunks hold at most 2^31 sources
     uint32_t o = 0;
     while (o < len) {
         // the first sink from here on, if any

@@ -886,18 +886,12 @@ hipError_t launch_scale(int want_f, int64_t n, const double4 *est4, double *scal
     return hipGetLastError();
 }
 
-int direct_sinks_chunks(int64_t n, int64_t nsinks) {
-    const int64_t waves = (nsinks + DIRECT_R - 1) / DIRECT_R;
-    const int64_t want = (DIRECT_WAVES + waves - 1) / waves;
-    return (int)std::max<int64_t>(n / (1ll << 31) + 1, std::min<int64_t>(want, n / DIRECT_SOURCES));
-}
-
 hipError_t launch_direct_sinks(int64_t n, const double *pos, const double *mass, double G,
                                int64_t nsinks, const int64_t *sinks, int nchunk, double *pot,
                                double *acc, double4 *part, int *bad, hipStream_t s) {
     if (nsinks <= 0) return hipSuccess;
     if (nchunk < 1 || (nchunk > 1 && !part)) return hipErrorInvalidValue;
-    const int64_t chunk = (n + nchunk - 1) / nchunk;
+    const int64_t chunk = row_length(n, nchunk);
     hipLaunchKernelGGL(k_direct_sinks, dim3(blocks(nsinks, 4 * DIRECT_R), (unsigned)nchunk),
                        dim3(256), 0, s, n, pos, mass, G, nsinks, sinks, chunk, pot, acc,
                        nchunk > 1 ? part : nullptr, bad);

@@ -1,0 +1,36 @@
+// How exact sums split their sources over grid rows (host and device; plain
+// arithmetic, so that it can be checked without a device).
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace fmm {
+
+constexpr int DIRECT_R = 8;               // sinks of a wavefront
+constexpr int64_t DIRECT_WAVES = 16384;
+constexpr int64_t DIRECT_SOURCES = 512;
+
+// sources per row: row k holds [k len, min(n, (k + 1) len))
+constexpr int64_t row_length(int64_t n, int64_t rows) { return (n + rows - 1) / rows; }
+
+// The library's number of rows: about DIRECT_WAVES wavefronts of DIRECT_R sinks
+// (16 per SIMD, so that the last ones cost little), rows of at least
+// DIRECT_SOURCES and at most 2^31 sources.  Rounding the length up would leave
+// rows past the last source (10^6 sources in 1953 rows of 513 end in row
+// 1949), so the rows are counted again from the length: each then holds at
+// least one source.  With more than one row, rows * nsinks < 2 * DIRECT_WAVES *
+// DIRECT_R.
+constexpr int64_t direct_rows(int64_t n, int64_t nsinks) {
+    const int64_t waves = (nsinks + DIRECT_R - 1) / DIRECT_R;
+    const int64_t want = (DIRECT_WAVES + waves - 1) / waves;
+    const int64_t rows = std::max(n / (int64_t(1) << 31) + 1, std::min(want, n / DIRECT_SOURCES));
+    return row_length(n, row_length(n, rows));
+}
+
+// sources in [j0, j1) of a row; 0 where the row begins past its end
+constexpr uint32_t slice_length(int64_t j0, int64_t j1) {
+    return j1 > j0 ? (uint32_t)(j1 - j0) : 0u;
+}
+
+}  // namespace fmm
