@@ -134,7 +134,7 @@ struct fmm_ctx {
     // walk
     DevBuf fa, fb, m2l, m2l2, p2p, p2p2, p2pe, p2pe2, m2l_off, p2p_off, chunks, ccnt, coff, Fpart;
     DevBuf rflag, ranges, rkey, wcode, rup;
-    DevBuf pt_n, pt_m, pt_s, pt_off, pt_moff, ptasks, pentry, pchain, ppart;
+    DevBuf pt_n, pt_m, pt_s, pt_off, pt_moff, ptasks, pentry, pbounds, pchain, ppart;
     DevBuf counters, nonfinite, walktmp, coffsets, ckey, ckey2, order, order2;
     DevBuf actflag, actf, actinv, actpre, cellact, actbad;   // forces for a listed subset
     DevBuf epsmin;                                           // smallest individual eps
@@ -562,18 +562,21 @@ void prepare_p2p(fmm_ctx *c, int64_t nlist, bool by_source, bool side = false) {
 // ancestor chains and the task list (active: leaves without listed sinks get
 // none).  side: on the side stream with its own scratch, counters and host
 // slots (the caller joins the side stream before the tasks run).  begin_p2p
-// queues the counts and their copy to the host, finish_p2p waits for them,
-// sizes the buffers and queues the rest.
+// queues the counts and their copy to the host, finish_p2p waits for them and
+// sizes the buffers, exec_p2p queues the rest.
 struct P2PPlan {
     bool side = false;
     const uint8_t *active = nullptr;
     int *up = nullptr;
     int width = 0;                 // sinks per task and entries of a partial row
     int ntasks = 0, prows = 0;     // (FP64: a row per task)
-    int4 *near = nullptr;          // FP64 tasks, list entries and slices per leaf
-    int2 *entry = nullptr;
+    int4 *near = nullptr;          // FP64 tasks, their and the list entries' offsets per
+    int2 *entry = nullptr;         // leaf, the list entries of a part of the leaves, and
+    int64_t *toff = nullptr, *eoff = nullptr;   // the parts' bounds
+    std::vector<NearPart> bounds;
     int2 *tasks = nullptr;         // mixed-precision tasks and their partial rows
-    int *nts = nullptr, *toff = nullptr, *moff = nullptr, *chain = nullptr;
+    int *toff32 = nullptr, *moff = nullptr, *chain = nullptr;
+    int *nts = nullptr;            // slices per leaf
 };
 
 P2PPlan begin_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = false) {
@@ -586,10 +589,9 @@ P2PPlan begin_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = fals
     pl.width = width;
     int *ntask = ensure<int>(c->pt_n, (size_t)nl + 1), *mtask = ensure<int>(c->pt_m, (size_t)nl + 1);
     pl.nts = ensure<int>(c->pt_s, (size_t)nl + 1);
-    pl.toff = ensure<int>(c->pt_off, (size_t)nl + 1);
-    pl.moff = ensure<int>(c->pt_moff, (size_t)nl + 1);
-    int *tmp = side ? ensure<int>(c->tmp_side, scan_tmp_ints(nl + 1)) : tmp_ints(c, scan_tmp_ints(nl + 1));
-    int *totals = ptr<int>(c->nonfinite) + (side ? 6 : 1);
+    const size_t ntmp = 2 * scan_tmp_ints(nl + 1);     // (64-bit sums)
+    int *tmp = side ? ensure<int>(c->tmp_side, ntmp) : tmp_ints(c, ntmp);
+    int *totals = ptr<int>(c->nonfinite) + (side ? 12 : 8), *host = c->hint + (side ? 4 : 0);
     const int *leaf_cell = ptr<int>(c->leaf_cell);
     const int64_t *off = ptr<int64_t>(c->p2p_off);
     const int2 *rg = ptr<int2>(c->ranges);
@@ -597,13 +599,19 @@ P2PPlan begin_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = fals
     CK(launch_range_up(c->ncells, t.parent, off, pl.up, s));
     if (width == 64) {
         pl.chain = ensure<int>(c->pchain, (size_t)std::max(nl, 1) * P2P_CHAIN);
-        CK(launch_p2p_plan(nl, leaf_cell, off, rg, pl.up, t, active, ntask, mtask, pl.nts, pl.toff,
-                           pl.moff, pl.chain, tmp, totals, s));
+        pl.toff32 = ensure<int>(c->pt_off, (size_t)nl + 1);
+        pl.moff = ensure<int>(c->pt_moff, (size_t)nl + 1);
+        CK(launch_p2p_plan(nl, leaf_cell, off, rg, pl.up, t, active, ntask, mtask, pl.nts,
+                           pl.toff32, pl.moff, pl.chain, tmp, totals, s));
+        CK(hipMemcpyAsync(host, totals, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     } else {
+        pl.toff = ensure<int64_t>(c->pt_off, (size_t)nl + 1);
+        pl.eoff = ensure<int64_t>(c->pt_moff, (size_t)nl + 1);
         CK(launch_near_count(nl, width, leaf_cell, off, rg, pl.up, t, active, ntask, pl.nts, mtask,
-                             pl.toff, pl.moff, tmp, totals, s));
+                             pl.toff, pl.eoff, reinterpret_cast<int64_t *>(tmp),
+                             reinterpret_cast<int64_t *>(totals), s));
+        CK(hipMemcpyAsync(host, totals, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     }
-    CK(hipMemcpyAsync(c->hint + (side ? 4 : 0), totals, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     return pl;
 }
 
@@ -612,19 +620,33 @@ void finish_p2p(fmm_ctx *c, P2PPlan &pl) {
     const int nl = c->nleaves;
     const int *host = c->hint + (pl.side ? 4 : 0);
     CK(hipStreamSynchronize(s));
-    pl.ntasks = host[0];
     if (pl.width == 64) {
+        pl.ntasks = host[0];
         pl.prows = host[1];
         pl.tasks = ensure<int2>(c->ptasks, std::max(pl.ntasks, 1));
-        CK(launch_p2p_tasks(nl, pl.toff, pl.tasks, s));
-    } else {
-        pl.prows = pl.ntasks;
-        pl.near = ensure<int4>(c->ptasks, std::max(pl.ntasks, 1));
-        pl.entry = ensure<int2>(c->pentry, (size_t)host[1] + 64);
-        CK(launch_near_fill(nl, pl.width, ptr<int>(c->leaf_cell), ptr<int64_t>(c->p2p_off),
-                            ptr<int2>(c->ranges), pl.up, tree_arrays(c), pl.nts, pl.toff, pl.moff,
-                            pl.near, pl.entry, s));
+        return;
     }
+    int64_t tasks, entries;
+    std::memcpy(&tasks, host, sizeof(tasks));
+    std::memcpy(&entries, host + 2, sizeof(entries));
+    if (tasks >= INT32_MAX)     // their rows alone are above 400 GB
+        throw NoMem{(size_t)tasks * (sizeof(int4) + pl.width * sizeof(double4))};
+    pl.prows = pl.ntasks = (int)tasks;
+    const int parts = near_parts(entries);
+    pl.bounds.assign(parts + 1, NearPart{0, 0, 0});
+    pl.bounds[parts] = {nl, tasks, entries};
+    if (parts > 1) {
+        NearPart *b = ensure<NearPart>(c->pbounds, parts + 1);
+        CK(launch_near_parts(nl, pl.toff, pl.eoff, parts, b, s));
+        CK(hipMemcpyAsync(pl.bounds.data(), b, (parts + 1) * sizeof(NearPart),
+                          hipMemcpyDeviceToHost, s));
+        CK(hipStreamSynchronize(s));
+    }
+    int64_t most = 0;
+    for (int k = 0; k < parts; ++k)
+        most = std::max(most, pl.bounds[k + 1].entry - pl.bounds[k].entry);
+    pl.near = ensure<int4>(c->ptasks, std::max(pl.ntasks, 1));
+    pl.entry = ensure<int2>(c->pentry, (size_t)most + 64);
 }
 
 // the direct sums of a plan, added into out4 (and the jerk into jo4), on the
@@ -638,16 +660,33 @@ void exec_p2p(fmm_ctx *c, const P2PPlan &pl, int want_f, int with_pot, double4 *
     const size_t rows = (size_t)std::max(pl.prows, 1) * pl.width;
     double4 *part = ensure<double4>(c->ppart, rows);
     double4 *jpart = v4 ? ensure<double4>(c->jpart, rows) : nullptr;
-    if (timed && c->opts.timing) CK(hipEventRecord(c->ev_p2p[0], s));
-    if (pl.width == 64)
+    auto stamp = [&](int k) {
+        if (timed && c->opts.timing) CK(hipEventRecord(c->ev_p2p[k], s));
+    };
+    if (pl.width == 64) {
+        CK(launch_p2p_tasks(c->nleaves, pl.toff32, pl.tasks, s));
+        stamp(0);
         CK(launch_p2p_mixed(pl.ntasks, pl.tasks, leaf_cell, pl.nts, pl.moff,
                             ptr<int64_t>(c->p2p_off), ptr<int2>(c->ranges), pl.chain, t, xyzm,
                             out4, part, s));
-    else if (v4)
-        CK(launch_p2p_jerk(pl.ntasks, pl.near, pl.entry, xyzm, v4, out4, jo4, part, jpart, s));
-    else
-        CK(launch_near(want_f, with_pot, pl.ntasks, pl.near, pl.entry, xyzm, out4, part, s));
-    if (timed && c->opts.timing) CK(hipEventRecord(c->ev_p2p[1], s));
+    } else {
+        for (size_t k = 0; k + 1 < pl.bounds.size(); ++k) {
+            const NearPart &b = pl.bounds[k], &e = pl.bounds[k + 1];
+            CK(launch_near_fill((int)b.leaf, (int)e.leaf, pl.width, leaf_cell,
+                                ptr<int64_t>(c->p2p_off), ptr<int2>(c->ranges), pl.up, t, pl.nts,
+                                pl.toff, pl.eoff, b.entry, pl.near, pl.entry, s));
+            if (k == 0) stamp(0);
+            const int nt = (int)(e.task - b.task);
+            const int4 *tasks = pl.near + b.task;
+            double4 *row = part + b.task * pl.width;
+            if (v4)
+                CK(launch_p2p_jerk(nt, tasks, pl.entry, xyzm, v4, out4, jo4, row,
+                                   jpart + b.task * pl.width, s));
+            else
+                CK(launch_near(want_f, with_pot, nt, tasks, pl.entry, xyzm, out4, row, s));
+        }
+    }
+    stamp(1);
     if (pl.prows == 0) return;
     if (pl.width == 64) {
         CK(launch_p2p_reduce(c->n, leaf_of, leaf_cell, pl.nts, pl.moff, t, part, out4, s));
@@ -712,7 +751,7 @@ void forces(fmm_ctx *c, int64_t n, const double *pos, const double *mass, double
     c->st.p = p;
     c->st.n = n;
     c->t_m2l_kernel = c->t_p2p_kernel = 0;
-    ensure<int>(c->nonfinite, 8);
+    ensure<int>(c->nonfinite, 16);
     mark(c, PH_START);
     build_tree(c, n, pos, mass, K, off, refit);
     TreeArrays t = tree_arrays(c);
@@ -1093,7 +1132,7 @@ void fmm_destroy(fmm_ctx *c) {
                       &c->rho2, &c->bsph, &c->smin, &c->leaf_cell, &c->M, &c->F, &c->P, &c->Fe,
                       &c->fa, &c->fb, &c->m2l, &c->m2l2, &c->p2p, &c->p2p2, &c->p2pe,
                       &c->p2pe2, &c->rflag, &c->ranges, &c->rkey, &c->pt_n, &c->pt_m,
-                      &c->pt_s, &c->pt_off, &c->pt_moff, &c->ptasks, &c->pentry, &c->pchain, &c->ppart, &c->m2l_off,
+                      &c->pt_s, &c->pt_off, &c->pt_moff, &c->ptasks, &c->pentry, &c->pbounds, &c->pchain, &c->ppart, &c->m2l_off,
                       &c->p2p_off, &c->chunks, &c->ccnt, &c->coff, &c->Fpart, &c->counters,
                       &c->nonfinite, &c->prev_scale, &c->walktmp, &c->coffsets,
                       &c->ckey, &c->ckey2, &c->order, &c->order2, &c->wcode, &c->rup, &c->tmp_side,
@@ -1385,7 +1424,7 @@ fmm_status fmm_direct_sinks(fmm_ctx *c, int64_t n, const double *pos, const doub
         const int nchunk = (int)fmm::direct_rows(n, nsinks);
         double4 *part =
             nchunk > 1 ? fmm::ensure<double4>(c->dspart, (size_t)nchunk * nsinks) : nullptr;
-        int *bad = fmm::ensure<int>(c->nonfinite, 8) + 5;
+        int *bad = fmm::ensure<int>(c->nonfinite, 16) + 5;
         CK(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
         CK(fmm::launch_direct_sinks(n, pos, mass, G, nsinks, sinks, nchunk, pot, acc, part, bad,
                                     c->stream));
@@ -1479,7 +1518,7 @@ fmm_status fmm_direct_jerk_sinks(fmm_ctx *c, int64_t n, const double *pos, const
     if (nsinks == 0) return FMM_OK;
     if (n == 0) return fmm::fail(c, FMM_E_INVAL, "sink index out of range");
     return fmm::guarded(c, [&]() -> fmm_status {
-        int *bad = fmm::ensure<int>(c->nonfinite, 8) + 5;
+        int *bad = fmm::ensure<int>(c->nonfinite, 16) + 5;
         CK(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
         const int nchunk = (int)fmm::direct_rows(n, nsinks);
         double4 *part =

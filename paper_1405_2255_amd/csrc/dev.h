@@ -60,11 +60,12 @@ __device__ __forceinline__ double dist2_exact(double ax, double ay, double az, d
 }
 
 // Inclusive prefix sum over the wavefront (all 64 lanes active).
-__device__ __forceinline__ int wave_incl_scan(int v) {
+template <class T>
+__device__ __forceinline__ T wave_incl_scan(T v) {
     const int lane = lane_id();
 #pragma unroll
     for (int off = 1; off < FMM_WAVE; off <<= 1) {
-        const int o = __shfl_up(v, off, FMM_WAVE);
+        const T o = __shfl_up(v, off, FMM_WAVE);
         if (lane >= off) v += o;
     }
     return v;

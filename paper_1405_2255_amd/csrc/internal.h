@@ -20,6 +20,9 @@ namespace fmm {
 size_t scan_tmp_ints(int64_t n);
 hipError_t exclusive_scan(const int *in, int *out, int64_t n, int *tmp, int *total,
                           hipStream_t s);
+// The same with sums of 64 bits (tmp: scan_tmp_ints(n) of them).
+hipError_t exclusive_scan(const int *in, int64_t *out, int64_t n, int64_t *tmp, int64_t *total,
+                          hipStream_t s);
 // Stable LSD radix sort of (key, value) by key bits [0, bits), 8 per pass.
 // Buffers are ping-ponged; on return *keys/*vals point at the sorted data
 // (one of the two given buffers).  vals may be null (key-only sort).
@@ -273,26 +276,37 @@ hipError_t launch_range_up(int ncells, const int *parent, const int64_t *off, in
                            hipStream_t s);
 // FP64 sums: tasks of up to `width` sinks (NEAR_R; NEAR_JERK_R with the jerk,
 // jerk.h) x NEAR_TASK sources (near.h).  Count and scan: tasks and list entries
-// per leaf (ntask, nentry and their scans task_off, entry_off: nleaves + 1 ints
-// each), nslice (nleaves); totals[0] = tasks, totals[1] = entries.  Fill: tasks
-// and entry (entry padded by 64).  Every task has a partial row of `width`
-// entries, used by leaves with more than one slice; the reduction adds those.
+// per leaf (ntask, nentry and their scans task_off, entry_off: nleaves + 1
+// each), nslice (nleaves); totals[0] = tasks, totals[1] = entries.  The entries
+// of all leaves together have no 32-bit bound (a leaf of one particle has
+// hundreds), so the leaves are taken in parts of about NEAR_ENTRIES entries
+// (near_parts, split.h): launch_near_parts finds the bounds of the parts
+// (parts + 1 of them: leaf, its task and its entry offset).  Fill: the tasks of
+// the leaves [l0, l1) and their entries, from entry offset e0 on (entry padded
+// by 64).  Every task has a partial row of `width` entries, used by leaves with
+// more than one slice; the reduction adds those.
 #define NEAR_R 8
 #define NEAR_JERK_R 6
 #define NEAR_TASK 4096
 #define NEAR_PAD 128    // particles past n that the sums may load (and drop)
+struct NearPart {
+    int64_t leaf, task, entry;
+};
 hipError_t launch_near_count(int nleaves, int width, const int *leaf_cell, const int64_t *off,
                              const int2 *range, const int *up, const TreeArrays &t,
                              const uint8_t *active, int *ntask, int *nslice, int *nentry,
-                             int *task_off, int *entry_off, int *tmp, int *totals, hipStream_t s);
-hipError_t launch_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+                             int64_t *task_off, int64_t *entry_off, int64_t *tmp, int64_t *totals,
+                             hipStream_t s);
+hipError_t launch_near_parts(int nleaves, const int64_t *task_off, const int64_t *entry_off,
+                             int parts, NearPart *bounds, hipStream_t s);
+hipError_t launch_near_fill(int l0, int l1, int width, const int *leaf_cell, const int64_t *off,
                             const int2 *range, const int *up, const TreeArrays &t,
-                            const int *nslice, const int *task_off, const int *entry_off,
-                            int4 *tasks, int2 *entry, hipStream_t s);
+                            const int *nslice, const int64_t *task_off, const int64_t *entry_off,
+                            int64_t e0, int4 *tasks, int2 *entry, hipStream_t s);
 hipError_t launch_near(int want_f, int with_pot, int ntasks, const int4 *tasks, const int2 *entry,
                        const double4 *xyzm, double4 *out4, double4 *partial, hipStream_t s);
 hipError_t launch_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
-                              const int *nslice, const int *task_off, const TreeArrays &t,
+                              const int *nslice, const int64_t *task_off, const TreeArrays &t,
                               const double4 *partial, double4 *out4, hipStream_t s);
 // Mixed precision (FP32 pair arithmetic, separations in FP64, sums flushed to
 // FP64; potential and acceleration): tasks of up to 64 sinks x P2P_TASK sources.

@@ -48,7 +48,7 @@ __device__ __forceinline__ int group_of(int nb, int ngroups, int k) {
 
 // One wavefront's task: sinks [sb, sb + r) of a leaf, `count` sources of the
 // leaf's list from position j0 on; first: the list entry that holds j0 (an
-// index into NearList::entry); single: the leaf's only slice.
+// index into the entries of its part); single: the leaf's only slice.
 struct NearTask {
     int sb, first, j0, r, count;
     bool single;

@@ -414,33 +414,43 @@ __global__ void k_near_count(int nleaves, int width, const int *leaf_cell, const
                              const uint8_t *active, int *ntask, int *nslice, int *nentry) {
     const int leaf = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FMM_WAVE);
     if (leaf > nleaves) return;
-    int tasks = 0, slices = 0;
-    int64_t entries = 0;
+    int slices = 0;
+    int64_t tasks = 0, entries = 0;
     const int c = leaf < nleaves ? leaf_cell[leaf] : -1;
     if (c >= 0 && (!active || active[c])) {
         for (int a = first_with_ranges(c, up, off); a >= 0; a = up[a])
             entries += off[a + 1] - off[a];
         const int64_t S = leaf_sources(c, up, off, range);
         slices = (int)max((int64_t)1, (S + NEAR_TASK - 1) / NEAR_TASK);
-        tasks = slices * ((t.end[c] - t.beg[c] + width - 1) / width);
+        tasks = (int64_t)slices * ((t.end[c] - t.beg[c] + width - 1) / width);
         ++entries;
     }
     if (lane_id() != 0) return;
-    ntask[leaf] = tasks;
+    // (a count past 32 bits makes a total that the host refuses)
+    ntask[leaf] = (int)min(tasks, (int64_t)INT_MAX);
     nentry[leaf] = (int)entries;
     if (leaf < nleaves) nslice[leaf] = slices;
 }
 
-// Fill: the list entries (shift, end) of every leaf and its tasks, slice by
-// slice (the groups of a slice next to each other, so that the wavefronts of a
-// block read the same sources).
-__global__ void k_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+// the bounds of the parts, one thread each
+__global__ void k_near_parts(int nleaves, const int64_t *task_off, const int64_t *entry_off,
+                             int parts, NearPart *bounds) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k > parts) return;
+    const int64_t l = k < parts ? near_part_begin(entry_off, nleaves, k) : nleaves;
+    bounds[k] = {l, task_off[l], entry_off[l]};
+}
+
+// Fill: the list entries (shift, end) of the leaves [l0, l1), from entry offset
+// first_entry on, and their tasks, slice by slice (the groups of a slice next to
+// each other, so that the wavefronts of a block read the same sources).
+__global__ void k_near_fill(int l0, int l1, int width, const int *leaf_cell, const int64_t *off,
                             const int2 *range, const int *up, TreeArrays t, const int *nslice,
-                            const int *task_off, const int *entry_off, int4 *tasks,
-                            int2 *entry) {
-    const int leaf = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FMM_WAVE);
-    if (leaf >= nleaves) return;
-    const int e0 = entry_off[leaf], k0 = task_off[leaf];
+                            const int64_t *task_off, const int64_t *entry_off,
+                            int64_t first_entry, int4 *tasks, int2 *entry) {
+    const int leaf = l0 + (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FMM_WAVE);
+    if (leaf >= l1) return;
+    const int e0 = (int)(entry_off[leaf] - first_entry), k0 = (int)task_off[leaf];
     if (task_off[leaf + 1] == k0) return;
     const int lane = lane_id(), c = leaf_cell[leaf], nts = nslice[leaf];
     const int beg = t.beg[c], nb = t.end[c] - beg, ng = (nb + width - 1) / width;
@@ -488,7 +498,7 @@ __global__ void k_near_fill(int nleaves, int width, const int *leaf_cell, const 
 
 // add the slices' sums of leaves with more than one, in slice order
 __global__ void k_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
-                              const int *nslice, const int *task_off, TreeArrays t,
+                              const int *nslice, const int64_t *task_off, TreeArrays t,
                               const double4 *partial, double4 *out4) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -497,7 +507,7 @@ __global__ void k_near_reduce(int64_t n, int width, const int *leaf_of, const in
     const int c = leaf_cell[leaf];
     const int k = (int)(i - t.beg[c]), nb = t.end[c] - t.beg[c], ng = (nb + width - 1) / width;
     const int g = group_of(nb, ng, k);
-    add_rows(out4 + i, partial + ((int64_t)task_off[leaf] + g) * width + (k - group_begin(nb, ng, g)),
+    add_rows(out4 + i, partial + (task_off[leaf] + g) * width + (k - group_begin(nb, ng, g)),
              (int64_t)ng * width, nts);
 }
 
@@ -779,7 +789,7 @@ hipError_t launch_p2p_reduce(int64_t n, const int *leaf_of, const int *leaf_cell
 hipError_t launch_near_count(int nleaves, int width, const int *leaf_cell, const int64_t *off,
                              const int2 *range, const int *up, const TreeArrays &t,
                              const uint8_t *active, int *ntask, int *nslice, int *nentry,
-                             int *task_off, int *entry_off, int *tmp, int *totals,
+                             int64_t *task_off, int64_t *entry_off, int64_t *tmp, int64_t *totals,
                              hipStream_t s) {
     hipLaunchKernelGGL(k_near_count, dim3(blocks((int64_t)(nleaves + 1) * FMM_WAVE, 256)),
                        dim3(256), 0, s, nleaves, width, leaf_cell, off, range, up, t, active,
@@ -791,13 +801,21 @@ hipError_t launch_near_count(int nleaves, int width, const int *leaf_cell, const
     return exclusive_scan(nentry, entry_off, nleaves + 1, tmp, totals + 1, s);
 }
 
-hipError_t launch_near_fill(int nleaves, int width, const int *leaf_cell, const int64_t *off,
+hipError_t launch_near_parts(int nleaves, const int64_t *task_off, const int64_t *entry_off,
+                             int parts, NearPart *bounds, hipStream_t s) {
+    hipLaunchKernelGGL(k_near_parts, dim3(blocks(parts + 1, 256)), dim3(256), 0, s, nleaves,
+                       task_off, entry_off, parts, bounds);
+    return hipGetLastError();
+}
+
+hipError_t launch_near_fill(int l0, int l1, int width, const int *leaf_cell, const int64_t *off,
                             const int2 *range, const int *up, const TreeArrays &t,
-                            const int *nslice, const int *task_off, const int *entry_off,
-                            int4 *tasks, int2 *entry, hipStream_t s) {
-    hipLaunchKernelGGL(k_near_fill, dim3(blocks((int64_t)nleaves * FMM_WAVE, 256)), dim3(256), 0,
-                       s, nleaves, width, leaf_cell, off, range, up, t, nslice, task_off,
-                       entry_off, tasks, entry);
+                            const int *nslice, const int64_t *task_off, const int64_t *entry_off,
+                            int64_t e0, int4 *tasks, int2 *entry, hipStream_t s) {
+    if (l1 <= l0) return hipSuccess;
+    hipLaunchKernelGGL(k_near_fill, dim3(blocks((int64_t)(l1 - l0) * FMM_WAVE, 256)), dim3(256), 0,
+                       s, l0, l1, width, leaf_cell, off, range, up, t, nslice, task_off, entry_off,
+                       e0, tasks, entry);
     return hipGetLastError();
 }
 
@@ -815,7 +833,7 @@ hipError_t launch_near(int want_f, int with_pot, int ntasks, const int4 *tasks, 
 }
 
 hipError_t launch_near_reduce(int64_t n, int width, const int *leaf_of, const int *leaf_cell,
-                              const int *nslice, const int *task_off, const TreeArrays &t,
+                              const int *nslice, const int64_t *task_off, const TreeArrays &t,
                               const double4 *partial, double4 *out4, hipStream_t s) {
     hipLaunchKernelGGL(k_near_reduce, dim3(blocks(n, 256)), dim3(256), 0, s, n, width, leaf_of,
                        leaf_cell, nslice, task_off, t, partial, out4);

@@ -1,6 +1,6 @@
 // Device-wide exclusive scan and stable LSD radix sort for gfx950.
 //
-// Scan: tiles of 2048 ints (256 threads x 8); one launch sums the tiles, a
+// Scan: tiles of 2048 counts (256 threads x 8); one launch sums the tiles, a
 // second scans each tile behind the sum of the tiles before it.
 //
 // Radix sort: 8-bit digits.  Up to RS_BLOCK_KEYS keys are sorted by one block
@@ -24,14 +24,15 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
-__device__ int block_excl_scan(int v, int *total) {
+template <class T>
+__device__ T block_excl_scan(T v, T *total) {
     // 256 threads = 4 waves
-    __shared__ int wsum[SCAN_THREADS / FMM_WAVE];
+    __shared__ T wsum[SCAN_THREADS / FMM_WAVE];
     const int lane = lane_id(), w = threadIdx.x / FMM_WAVE;
-    const int inc = wave_incl_scan(v);
+    const T inc = wave_incl_scan(v);
     if (lane == FMM_WAVE - 1) wsum[w] = inc;
     __syncthreads();
-    int off = 0, tot = 0;
+    T off = 0, tot = 0;
 #pragma unroll
     for (int i = 0; i < SCAN_THREADS / FMM_WAVE; ++i) {
         if (i < w) off += wsum[i];
@@ -42,15 +43,16 @@ __device__ int block_excl_scan(int v, int *total) {
     return off + inc - v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const int *in, int64_t n, int *sums) {
+template <class I, class T>
+__global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const I *in, int64_t n, T *sums) {
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
-    int s = 0;
+    T s = 0;
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         const int64_t j = base + (int64_t)i * SCAN_THREADS + threadIdx.x;
         if (j < n) s += in[j];
     }
-    int tot;
+    T tot;
     block_excl_scan(s, &tot);
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
@@ -59,15 +61,16 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const int *in, int64
 // which each block adds up to its own (up to SCAN_TILES of them, from the
 // cache, cost less than a launch that scans them), or their prefixes.
 constexpr int SCAN_TILES = 8192;
+template <class I, class T>
 __global__ void __launch_bounds__(SCAN_THREADS)
-k_tile_scan(const int *in, int *out, int64_t n, const int *sums, bool prefixes, int *total) {
+k_tile_scan(const I *in, T *out, int64_t n, const T *sums, bool prefixes, T *total) {
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    int v[SCAN_ITEMS];
-    int s = 0, off = 0;
+    I v[SCAN_ITEMS];
+    T s = 0, off = 0;
     if (sums && prefixes) {
         off = sums[blockIdx.x];
     } else if (sums) {
-        int q = 0;
+        T q = 0;
 #pragma unroll 4
         for (int i = threadIdx.x; i < (int)blockIdx.x; i += SCAN_THREADS) q += sums[i];
         block_excl_scan(q, &off);
@@ -78,8 +81,8 @@ k_tile_scan(const int *in, int *out, int64_t n, const int *sums, bool prefixes, 
         v[i] = j < n ? in[j] : 0;
         s += v[i];
     }
-    int tot;
-    int run = block_excl_scan(s, &tot) + off;
+    T tot;
+    T run = block_excl_scan(s, &tot) + off;
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         const int64_t j = base + i;
@@ -96,24 +99,25 @@ k_tile_scan(const int *in, int *out, int64_t n, const int *sums, bool prefixes, 
 constexpr int SCAN1_THREADS = 1024;
 constexpr int64_t SCAN1_MAX = 1 << 14;
 
+template <class I, class T>
 __global__ void __launch_bounds__(SCAN1_THREADS)
-k_scan_single(const int *in, int *out, int64_t n, int *total) {
-    __shared__ int wsum[SCAN1_THREADS / FMM_WAVE];
+k_scan_single(const I *in, T *out, int64_t n, T *total) {
+    __shared__ T wsum[SCAN1_THREADS / FMM_WAVE];
     const int t = threadIdx.x, lane = lane_id(), w = t / FMM_WAVE;
     const int64_t chunk = (n + SCAN1_THREADS - 1) / SCAN1_THREADS;
     const int64_t lo = min(n, (int64_t)t * chunk), hi = min(n, lo + chunk);
-    int s = 0;
+    T s = 0;
 #pragma unroll 8
     for (int64_t i = lo; i < hi; ++i) s += in[i];
-    const int inc = wave_incl_scan(s);
+    const T inc = wave_incl_scan(s);
     if (lane == FMM_WAVE - 1) wsum[w] = inc;
     __syncthreads();
-    int run = inc - s;
+    T run = inc - s;
     for (int i = 0; i < w; ++i) run += wsum[i];
     if (total && t == SCAN1_THREADS - 1) *total = run + s;
 #pragma unroll 8
     for (int64_t i = lo; i < hi; ++i) {
-        const int v = in[i];
+        const I v = in[i];
         out[i] = run;
         run += v;
     }
@@ -437,34 +441,50 @@ size_t scan_tmp_ints(int64_t n) {
     return total + 1;
 }
 
-hipError_t exclusive_scan(const int *in, int *out, int64_t n, int *tmp, int *total,
-                          hipStream_t s) {
+namespace {
+
+template <class I, class T>
+hipError_t scan(const I *in, T *out, int64_t n, T *tmp, T *total, hipStream_t s) {
     if (n <= 0) {
-        if (total) return hipMemsetAsync(total, 0, sizeof(int), s);
+        if (total) return hipMemsetAsync(total, 0, sizeof(T), s);
         return hipSuccess;
     }
     const int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     if (tiles > 1 && n <= SCAN1_MAX) {
-        hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(SCAN1_THREADS), 0, s, in, out, n, total);
+        hipLaunchKernelGGL((k_scan_single<I, T>), dim3(1), dim3(SCAN1_THREADS), 0, s, in, out, n,
+                           total);
         return hipGetLastError();
     }
     if (tiles == 1) {
-        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(SCAN_THREADS), 0, s, in, out, n,
-                           (const int *)nullptr, false, total);
+        hipLaunchKernelGGL((k_tile_scan<I, T>), dim3(1), dim3(SCAN_THREADS), 0, s, in, out, n,
+                           (const T *)nullptr, false, total);
         return hipGetLastError();
     }
-    int *sums = tmp;
-    hipLaunchKernelGGL(k_tile_sums, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, in, n, sums);
+    T *sums = tmp;
+    hipLaunchKernelGGL((k_tile_sums<I, T>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, in, n,
+                       sums);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const bool prefixes = tiles > SCAN_TILES;
     if (prefixes) {
-        e = exclusive_scan(sums, sums, tiles, tmp + tiles, nullptr, s);
+        e = scan(sums, sums, tiles, tmp + tiles, (T *)nullptr, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, in, out, n,
-                       (const int *)sums, prefixes, total);
+    hipLaunchKernelGGL((k_tile_scan<I, T>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, in,
+                       out, n, (const T *)sums, prefixes, total);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t exclusive_scan(const int *in, int *out, int64_t n, int *tmp, int *total,
+                          hipStream_t s) {
+    return scan(in, out, n, tmp, total, s);
+}
+
+hipError_t exclusive_scan(const int *in, int64_t *out, int64_t n, int64_t *tmp, int64_t *total,
+                          hipStream_t s) {
+    return scan(in, out, n, tmp, total, s);
 }
 
 // Tiles of 2048 keys (256 threads); of 4096 above RS_WIDE keys, where the chip

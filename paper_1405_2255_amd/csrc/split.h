@@ -1,5 +1,6 @@
-// How exact sums split their sources over grid rows (host and device; plain
-// arithmetic, so that it can be checked without a device).
+// How the direct sums split their work: the sources of exact sums over grid rows,
+// the leaves of the near field over parts (host and device; plain arithmetic, so
+// that it can be checked without a device).
 #pragma once
 
 #include <algorithm>
@@ -31,6 +32,27 @@ constexpr int64_t direct_rows(int64_t n, int64_t nsinks) {
 // sources in [j0, j1) of a row; 0 where the row begins past its end
 constexpr uint32_t slice_length(int64_t j0, int64_t j1) {
     return j1 > j0 ? (uint32_t)(j1 - j0) : 0u;
+}
+
+// The near field takes its leaves in parts of about NEAR_ENTRIES list entries (8
+// bytes each; at most one leaf's entries more, which are fewer than its sources),
+// so that offsets inside a part fit 32 bits and the list's memory is bounded:
+// part k holds the leaves whose entries begin in [k NEAR_ENTRIES, (k + 1)
+// NEAR_ENTRIES).  10^6 bodies in leaves of 80 have 1.1e7 entries; in leaves of
+// one body up to 4.6e8.
+constexpr int64_t NEAR_ENTRIES = int64_t(1) << 27;
+constexpr int near_parts(int64_t entries) {
+    return (int)std::max<int64_t>(1, (entries + NEAR_ENTRIES - 1) / NEAR_ENTRIES);
+}
+// the first leaf of part k: entry_off holds nleaves + 1 offsets, not decreasing
+constexpr int64_t near_part_begin(const int64_t *entry_off, int64_t nleaves, int64_t k) {
+    int64_t lo = 0, hi = nleaves;
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (entry_off[mid] < k * NEAR_ENTRIES) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
 }
 
 }  // namespace fmm

@@ -176,16 +176,6 @@ __device__ __forceinline__ unsigned long long count_of(unsigned long long c, int
     return k == 0 ? c & 0xffffffu : k == 1 ? (c >> 24) & 0xfffffu : c >> 44;
 }
 
-__device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < FMM_WAVE; off <<= 1) {
-        const unsigned long long o = __shfl_up(v, off, FMM_WAVE);
-        if (lane >= off) v += o;
-    }
-    return v;
-}
-
 // A tile's published counts, one word per kind of output: the sweep (+ 1) in the
 // upper bits, so that the words of earlier sweeps count as empty; whether the
 // count is that of this and all earlier tiles; the count.
@@ -251,7 +241,7 @@ k_walk_tiles(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
         pr = wb.front[sweep & 1][i];
         d = decide(wp, t, P, (int)pr.x, (int)pr.y);
     }
-    const unsigned long long mine = pack_counts(d), incl = wave_incl_scan64(mine);
+    const unsigned long long mine = pack_counts(d), incl = wave_incl_scan(mine);
     const double pairs = wave_sum(d.pairs);
     if (lane == FMM_WAVE - 1) {
         ws[w] = incl;
@@ -539,12 +529,12 @@ k_walk_small(WalkParams wp, TreeArrays t, const double *P, WalkBuffers wb, int l
         unsigned long long incl[SMALL_B];
 #pragma unroll
         for (int r = 0; r < SMALL_B; ++r) {
-            incl[r] = wave_incl_scan64(c[r]);
+            incl[r] = wave_incl_scan(c[r]);
             if (lane == FMM_WAVE - 1) ws[r * SMALL_WAVES + w] = incl[r];
         }
         __syncthreads();
         if (w == 0) {       // exclusive scan of the wavefronts' totals, and the total
-            const unsigned long long v = ws[lane], s = wave_incl_scan64(v);
+            const unsigned long long v = ws[lane], s = wave_incl_scan(v);
             ws[lane] = s - v;
             if (lane == FMM_WAVE - 1) ws[FMM_WAVE] = s;
         }

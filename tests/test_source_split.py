@@ -1,6 +1,11 @@
-"""The rows that the exact sums cut their sources into (split.h), checked on the
-CPU: every row begins inside [0, n), the rows cover it, their number is what the
-partial sums have room for, and a row that began past its end would be empty."""
+"""How the direct sums split their work (split.h), checked on the CPU.
+
+Rows of sources of the exact sums: every row begins inside [0, n), the rows
+cover it, their number is what the partial sums have room for, and a row that
+began past its end would be empty.
+
+Parts of leaves of the near field, with totals past 32 bits: the parts cover the
+leaves in order, and an offset inside a part fits 32 bits."""
 import os
 import shutil
 import subprocess
@@ -9,7 +14,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-PROGRAM = r"""
+ROWS = r"""
 #include <cstdio>
 #include "split.h"
 int main() {
@@ -43,11 +48,51 @@ int main() {
 """
 
 
-def test_every_row_holds_sources(tmp_path):
+PARTS = r"""
+#include <cstdio>
+#include <vector>
+#include "split.h"
+int main() {
+    uint64_t x = 88172645463325252ull;
+    auto random = [&]() { x ^= x << 13; x ^= x >> 7; x ^= x << 17; return x; };
+    long long bad = 0;
+    // leaves and the most entries of one
+    const int64_t sizes[][2] = {{1, 1}, {1, 1 << 30}, {7, 100}, {1000, 1 << 28}, {100000, 500},
+                                {100000, 100000}, {3000000, 2000}, {3000000, 40}, {5, 0}};
+    for (auto &z : sizes) {
+        const int64_t nl = z[0];
+        std::vector<int64_t> off(nl + 1, 0);
+        int64_t largest = 0;
+        for (int64_t l = 0; l < nl; ++l) {
+            // (leaves without sinks have none)
+            const int64_t e = random() % 4 ? random() % (z[1] + 1) : 0;
+            off[l + 1] = off[l] + e;
+            largest = std::max(largest, e);
+        }
+        const int parts = fmm::near_parts(off[nl]);
+        bad += parts < 1 || (off[nl] <= fmm::NEAR_ENTRIES) != (parts == 1);
+        int64_t last = 0;
+        for (int k = 0; k < parts; ++k) {
+            const int64_t b = fmm::near_part_begin(off.data(), nl, k);
+            const int64_t e = k + 1 < parts ? fmm::near_part_begin(off.data(), nl, k + 1) : nl;
+            const int64_t size = off[e] - off[b];
+            bad += (k == 0 && b != 0) || (k > 0 && b != last) || e < b;
+            bad += size > fmm::NEAR_ENTRIES + largest || size >= (int64_t(1) << 31);
+            last = e;
+        }
+        std::printf("%lld leaves, %lld entries, %d parts\n", (long long)nl, (long long)off[nl],
+                    parts);
+    }
+    return bad != 0;
+}
+"""
+
+
+def _run(tmp_path, program):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     src, exe = tmp_path / "split.cpp", tmp_path / "split"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     r = subprocess.run(["g++", "-std=c++20", "-O1", "-Wall", "-Werror", "-fsanitize=undefined",
                         "-fno-sanitize-recover=undefined",
                         "-I", os.path.join(ROOT, "paper_1405_2255_amd", "csrc"), str(src), "-o",
@@ -55,3 +100,14 @@ def test_every_row_holds_sources(tmp_path):
     assert r.returncode == 0, r.stderr[-4000:]
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_every_row_holds_sources(tmp_path):
+    _run(tmp_path, ROWS)
+
+
+def test_offsets_inside_a_part_fit_32_bits(tmp_path):
+    out = _run(tmp_path, PARTS)
+    # the largest totals are past what 32 bits hold
+    assert max(int(line.split()[2]) for line in out.splitlines()) > 1 << 32
