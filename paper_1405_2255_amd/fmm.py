@@ -188,6 +188,15 @@ class Context:
         if st != OK:
             raise FMMError(st, _lib.fmm_last_error(self._h).decode())
 
+    def _ready(self):
+        """The handle, once the tensors of a call may be used.  The library
+        orders a call behind the work queued on the context's stream; for
+        torch's default stream (handle 0) it works on a stream of its own, which
+        does not wait for that one, so the wait is here."""
+        if self.stream.cuda_stream == 0 and not self.stream.query():
+            self.stream.synchronize()
+        return self._h
+
     def forces(self, pos: torch.Tensor, mass: torch.Tensor, G: float = 1.0, p: int = -1,
                target_err: float = 1e-7, pot: torch.Tensor | None = None,
                acc: torch.Tensor | None = None, refit: bool = False):
@@ -199,7 +208,7 @@ class Context:
         if acc is None:
             acc = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
         fn = _lib.fmm_forces_refit if refit else _lib.fmm_forces
-        self._check(fn(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(fn(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                     _dev_ptr(mass, "mass", (n,)), float(G), int(p),
                                     float(target_err), _dev_ptr(pot, "pot", (n,)),
                                     _dev_ptr(acc, "acc", (n, 3))))
@@ -217,7 +226,7 @@ class Context:
             pot = torch.empty(n, dtype=torch.float64, device=pos.device)
         if acc is None:
             acc = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_forces_batched(self._h, off.shape[0] - 1,
+        self._check(_lib.fmm_forces_batched(self._ready(), off.shape[0] - 1,
                                             off.ctypes.data_as(C.c_void_p),
                                             _dev_ptr(pos, "pos", (n, 3)),
                                             _dev_ptr(mass, "mass", (n,)), float(G), int(p),
@@ -237,7 +246,7 @@ class Context:
         k = active.shape[0]
         pot = torch.empty(k, dtype=torch.float64, device=pos.device)
         acc = torch.empty((k, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_forces_active(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_forces_active(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                            _dev_ptr(mass, "mass", (n,)), float(G), int(p),
                                            float(target_err), k, C.c_void_p(active.data_ptr()),
                                            int(bool(refit)), _dev_ptr(pot, "pot", (k,)),
@@ -251,7 +260,7 @@ class Context:
         n = pos.shape[0]
         pot = torch.empty(n, dtype=torch.float64, device=pos.device)
         acc = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_forces_eps(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_forces_eps(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                         _dev_ptr(mass, "mass", (n,)), float(G), int(p),
                                         _dev_ptr(eps_particle, "eps_particle", (n,)),
                                         _dev_ptr(pot, "pot", (n,)), _dev_ptr(acc, "acc", (n, 3))))
@@ -265,7 +274,7 @@ class Context:
         pot = torch.empty(n, dtype=torch.float64, device=pos.device)
         acc = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
         jerk = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_forces_jerk(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_forces_jerk(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                          _dev_ptr(vel, "vel", (n, 3)),
                                          _dev_ptr(mass, "mass", (n,)), float(G), int(p),
                                          float(target_err), _dev_ptr(pot, "pot", (n,)),
@@ -286,7 +295,7 @@ class Context:
         pot = torch.empty(k, dtype=torch.float64, device=pos.device)
         acc = torch.empty((k, 3), dtype=torch.float64, device=pos.device)
         jerk = torch.empty((k, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_forces_jerk_active(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_forces_jerk_active(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                                 _dev_ptr(vel, "vel", (n, 3)),
                                                 _dev_ptr(mass, "mass", (n,)), float(G), int(p),
                                                 float(target_err), k,
@@ -301,7 +310,7 @@ class Context:
         n = pos.shape[0]
         pot = torch.empty(n, dtype=torch.float64, device=pos.device)
         acc = torch.empty((n, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_direct(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_direct(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                     _dev_ptr(mass, "mass", (n,)), float(G),
                                     _dev_ptr(pot, "pot", (n,)), _dev_ptr(acc, "acc", (n, 3))))
         return pot, acc
@@ -322,7 +331,7 @@ class Context:
         if acc is None:
             acc = torch.empty((k, 3), dtype=torch.float64, device=pos.device)
         fn = _lib.fmm_direct_sinks_noalloc if noalloc else _lib.fmm_direct_sinks
-        self._check(fn(self._h, n, _dev_ptr(pos, "pos", (n, 3)), _dev_ptr(mass, "mass", (n,)),
+        self._check(fn(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)), _dev_ptr(mass, "mass", (n,)),
                        float(G), k, C.c_void_p(sinks.data_ptr()), _dev_ptr(pot, "pot", (k,)),
                        _dev_ptr(acc, "acc", (k, 3))))
         return pot, acc
@@ -336,7 +345,7 @@ class Context:
         sinks = sinks.contiguous()
         k = sinks.shape[0]
         jerk = torch.empty((k, 3), dtype=torch.float64, device=pos.device)
-        self._check(_lib.fmm_direct_jerk_sinks(self._h, n, _dev_ptr(pos, "pos", (n, 3)),
+        self._check(_lib.fmm_direct_jerk_sinks(self._ready(), n, _dev_ptr(pos, "pos", (n, 3)),
                                                _dev_ptr(vel, "vel", (n, 3)),
                                                _dev_ptr(mass, "mass", (n,)), float(G), k,
                                                C.c_void_p(sinks.data_ptr()),
