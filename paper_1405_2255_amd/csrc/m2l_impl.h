@@ -163,13 +163,17 @@ __device__ __forceinline__ void source_terms(cplx *acc, Rows &g, const cplx *Ma,
     Unroll<0, KMAX>::run(degree);
 }
 
-// azimuth of (x, y) and its distance from the z axis (on the axis any azimuth
-// does: 0)
+// azimuth of (x, y) and its distance from the z axis.  On the axis any azimuth
+// does (0), and so close to it that x^2 + y^2 is denormal x/rho and y/rho would
+// not be the cosine and sine of an angle: they would scale the accumulators that
+// they turn.  So within 1e-145 of the axis is on it (a separation as short as that
+// has no finite Theta_2 anyway).
 __device__ __forceinline__ Phase azimuth(double x, double y, double &rho) {
     const double r2 = fma(x, x, y * y);
-    const double ri = r2 > 0.0 ? rsqrt_nr(r2) : 0.0;
+    const bool off = r2 > 1e-290;
+    const double ri = off ? rsqrt_nr(r2) : 0.0;
     rho = r2 * ri;
-    return r2 > 0.0 ? Phase{x * ri, y * ri} : Phase{1.0, 0.0};
+    return off ? Phase{x * ri, y * ri} : Phase{1.0, 0.0};
 }
 
 // outputs N0..N1 of order P from multipoles of `stride` complex numbers per cell
