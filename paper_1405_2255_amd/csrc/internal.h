@@ -25,8 +25,8 @@ hipError_t exclusive_scan(const int *in, int64_t *out, int64_t n, int64_t *tmp, 
                           hipStream_t s);
 // Stable LSD radix sort of (key, value) by key bits [0, bits), 8 per pass.
 // Buffers are ping-ponged; on return *keys/*vals point at the sorted data
-// (one of the two given buffers).  vals may be null (key-only sort).
-size_t sort_tmp_ints(int64_t n);
+// (one of the two given buffers).  vals may be null (key-only sort).  tmp must
+// hold sort_tmp_ints(n) ints (split.h).
 // (Only key bits [lo_bit, lo_bit + bits) are sorted.)
 hipError_t radix_sort(uint64_t **keys, uint64_t **keys_alt, uint32_t **vals,
                       uint32_t **vals_alt, int64_t n, int bits, int *tmp, hipStream_t s,

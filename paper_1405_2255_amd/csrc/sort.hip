@@ -124,9 +124,7 @@ k_scan_single(const I *in, T *out, int64_t n, T *total) {
 }
 
 // ---- radix sort -------------------------------------------------------
-constexpr int RS_ITEMS = 8;               // keys per thread of a tile
 constexpr int RS_WINDOW = 4;              // entries of earlier tiles read at a time
-constexpr int RS_MAX_PASSES = 8;
 constexpr int RS_DIGITS_THREADS = 256;
 constexpr int RS_DIGITS_BLOCKS = 1024;
 constexpr int RS_BLOCK_THREADS = 1024;
@@ -487,17 +485,6 @@ hipError_t exclusive_scan(const int *in, int64_t *out, int64_t n, int64_t *tmp, 
     return scan(in, out, n, tmp, total, s);
 }
 
-// Tiles of 2048 keys (256 threads); of 4096 above RS_WIDE keys, where the chip
-// is full either way and half the tiles mean half the way back through their
-// entries (10^6 keys 17.5 us a pass against 22; 10^5 keys 9 us with both).
-constexpr int64_t RS_WIDE = 1 << 17;
-inline int sort_threads(int64_t n) { return n > RS_WIDE ? 512 : 256; }
-
-size_t sort_tmp_ints(int64_t n) {
-    const int64_t tile = (int64_t)sort_threads(n) * RS_ITEMS;
-    return RS_MAX_PASSES * 257 + 2 * 256 * (size_t)((n + tile - 1) / tile);
-}
-
 namespace {
 
 template <bool HAS_VAL>
@@ -537,8 +524,7 @@ hipError_t radix_sort(uint64_t **keys, uint64_t **keys_alt, uint32_t **vals,
         return hipGetLastError();
     }
     const int threads = sort_threads(n);
-    const int64_t tile = (int64_t)threads * RS_ITEMS;
-    const int ntiles = (int)((n + tile - 1) / tile);
+    const int ntiles = (int)sort_tiles(n, threads);
     SortTmp T;
     T.digits = tmp;
     T.tickets = tmp + RS_MAX_PASSES * 256;

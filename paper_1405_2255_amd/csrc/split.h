@@ -1,12 +1,33 @@
-// How the direct sums split their work: the sources of exact sums over grid rows,
-// the leaves of the near field over parts (host and device; plain arithmetic, so
-// that it can be checked without a device).
+// How work is split: the keys of a sort over tiles, the sources of exact sums over
+// grid rows, the leaves of the near field over parts (host and device; plain
+// arithmetic, so that it can be checked without a device).
 #pragma once
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 namespace fmm {
+
+// Radix sort, one launch per pass: tiles of 2048 keys (256 threads of RS_ITEMS);
+// of 4096 above RS_WIDE keys, where the chip is full either way and half the tiles
+// mean half the way back through their entries (10^6 keys 17.5 us a pass
+// against 22; 10^5 keys 9 us with both).
+constexpr int RS_ITEMS = 8;               // keys per thread of a tile
+constexpr int RS_MAX_PASSES = 8;
+constexpr int64_t RS_WIDE = 1 << 17;
+constexpr int sort_threads(int64_t n) { return n > RS_WIDE ? 512 : 256; }
+constexpr int64_t sort_tiles(int64_t n, int threads) {
+    return (n + threads * RS_ITEMS - 1) / (threads * RS_ITEMS);
+}
+// scratch of a sort of n keys or fewer: digit counts and a ticket per pass, two
+// arrays of 256 entries per tile.  2^17 keys have more tiles than a few more keys
+// do, and a scratch made for the latter takes them too.
+constexpr size_t sort_tmp_ints(int64_t n) {
+    const int64_t narrow = sort_tiles(std::min(n, RS_WIDE), 256);
+    const int64_t wide = n > RS_WIDE ? sort_tiles(n, 512) : 0;
+    return RS_MAX_PASSES * 257 + 2 * 256 * (size_t)std::max(narrow, wide);
+}
 
 constexpr int DIRECT_R = 8;               // sinks of a wavefront
 constexpr int64_t DIRECT_WAVES = 16384;

@@ -1,11 +1,14 @@
-"""How the direct sums split their work (split.h), checked on the CPU.
+"""How work is split (split.h), checked on the CPU.
 
 Rows of sources of the exact sums: every row begins inside [0, n), the rows
 cover it, their number is what the partial sums have room for, and a row that
 began past its end would be empty.
 
 Parts of leaves of the near field, with totals past 32 bits: the parts cover the
-leaves in order, and an offset inside a part fits 32 bits."""
+leaves in order, and an offset inside a part fits 32 bits.
+
+Scratch of a sort: what is enough for n keys is enough for fewer, also where the
+tiles change their width."""
 import os
 import shutil
 import subprocess
@@ -88,6 +91,26 @@ int main() {
 """
 
 
+SCRATCH = r"""
+#include <cstdio>
+#include "split.h"
+int main() {
+    long long bad = 0;
+    size_t before = 0;
+    for (int64_t n = 0; n <= (int64_t(1) << 31); n += n < 600000 ? 1 : n / 50) {
+        const size_t have = fmm::sort_tmp_ints(n);
+        const size_t used = fmm::RS_MAX_PASSES * 257 +
+                            512 * (size_t)fmm::sort_tiles(n, fmm::sort_threads(n));
+        if ((have < before || have < used) && bad++ < 5)
+            std::printf("n %lld: %zu ints, used %zu, before %zu\n", (long long)n, have, used,
+                        before);
+        before = have;
+    }
+    return bad != 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
@@ -111,3 +134,7 @@ def test_offsets_inside_a_part_fit_32_bits(tmp_path):
     out = _run(tmp_path, PARTS)
     # the largest totals are past what 32 bits hold
     assert max(int(line.split()[2]) for line in out.splitlines()) > 1 << 32
+
+
+def test_scratch_of_a_sort_grows_with_the_keys(tmp_path):
+    _run(tmp_path, SCRATCH)
