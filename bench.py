@@ -37,7 +37,7 @@ Prints ONE JSON line (rank 0): metric, value, ... plus
                 (continuous batching, HBM admission): the served capacity with
                 every request queued at once, then p50/p99 latency and
                 throughput for Poisson arrivals at offered loads of it; with the
-                FP32 roofline of its kernels and the accuracy of its results
+                accuracy of its results
   roofline_fp32 the mixed-precision P2P and M2L kernels against the FP32 peak
   cpu_baseline_fmm  the CPU oracle's plain FMM on a bounded sample
   tree          the tree phase as HBM traffic (~290 algorithmic bytes per
@@ -320,11 +320,11 @@ def eps_leg(args, fmm, pos, mass, params, full_ms, acc_direct):
     return out
 
 
-def jerk_leg(args, fmm, workloads, pos, mass, params, main_stats):
+def jerk_leg(args, fmm, workloads, pos, mass, params):
     """Jerk (Sec. 7, eqs:fmm:dot) on the N = 1e6 Plummer input moving with its
     equilibrium velocities (the main leg's order, eps, leaf size and
-    threshold): time of the force-and-jerk call against the force-only call
-    with the phase times of both (the paper: M2L work doubles), and the rms
+    threshold): time and phases of the force-and-jerk call (the main leg has
+    those of the force-only call; the paper: M2L work doubles), and the rms
     relative jerk and force errors on 2048 seeded sinks against the GPU
     direct sums."""
     import torch
@@ -356,7 +356,6 @@ def jerk_leg(args, fmm, workloads, pos, mass, params, main_stats):
                        f"n_L={leaf or 32}, p2p_factor={pf or 2.0:g}",
            "value": n / t, "unit": "particle-jerks/s", "ms": 1e3 * t,
            "phases_ms": {k: st[k] for k in phases},
-           "phases_ms_forces_only": {k: main_stats[k] for k in phases},
            "errors_vs_gpu_direct_2048": {"jerk": _summary(ej.cpu().numpy()),
                                          "acc": _summary(ea.cpu().numpy())}}
     print(f"jerk: {1e3 * t:.2f} ms", file=sys.stderr, flush=True)
@@ -583,6 +582,16 @@ def stream_leg(args, fmm, workloads, params):
             "latency_all_queued": serve.latency_summary(reqs), "offered_loads": loads,
             "errors_vs_gpu_direct": acc_err, "errors_pooled": pooled,
             "meets_target": bool(pooled["rms"] <= 1e-7)}
+
+
+def short(v, digits: int = 4):
+    """v with its floats to a few significant digits, so that the line stays within
+    the 15000 characters that a record of the run keeps of it."""
+    if isinstance(v, dict):
+        return {k: short(x, digits) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [short(x, digits) for x in v]
+    return float(f"{v:.{digits}g}") if isinstance(v, float) and np.isfinite(v) else v
 
 
 def main() -> int:
@@ -820,13 +829,12 @@ def main() -> int:
                         "achieved": f_m2l / (stm["t_m2l_kernel"] * 1e-3) / 1e12}}
         for k in ("k_p2p_mixed", "k_m2l32"):
             roofline_fp32[k]["frac"] = roofline_fp32[k]["achieved"] / FP32_PEAK_TFLOPS
-        mixed["roofline_fp32"] = roofline_fp32
     active = None if args.no_active else active_leg(args, fmm, pos, mass,
                                                     (leaf, pf, p_arg, eps, centre), ms_per_step)
     eps_b = None if args.no_eps else eps_leg(args, fmm, pos, mass,
                                              (leaf, pf, st["p"], eps, centre), ms_per_step, ad_all)
     jerk = None if args.no_jerk else jerk_leg(args, fmm, workloads, pos, mass,
-                                              (leaf, pf, st["p"], eps, centre), st)
+                                              (leaf, pf, st["p"], eps, centre))
     batched = None
     if not args.no_batched:
         batched = {"fp64": batched_leg(args, fmm, workloads, "fp64"),
@@ -838,7 +846,6 @@ def main() -> int:
         lm, pfm, pm_, em, cm = tuned_mixed
         stream = stream_leg(args, fmm, workloads,
                                (lm or 32, pfm or 2.0, pm_ if pm_ > 0 else st["p"], em, cm))
-        stream["roofline_fp32"] = roofline_fp32
         stream["vs_plain_fp64"] = stream["value"] / value
         stream["vs_gpu_direct"] = stream["value"] / direct["value"] if direct else None
     cpu_fmm = None
@@ -914,7 +921,8 @@ def main() -> int:
                                       "n_p2p_pairs", "n_est_m2l", "n_est_p2p_pairs",
                                       "walk_iterations")},
     }
-    print(json.dumps(out), flush=True)
+    print(json.dumps({k: v if k in ("value", "ms_per_step") else short(v) for k, v in out.items()},
+                     separators=(",", ":")), flush=True)
     return 0
 
 
