@@ -139,7 +139,9 @@ typedef struct {
        (phases as in the paper's tab:complexity).  Phases
        run at the same time on two streams: t_up is the part of the upward pass
        that the estimate does not hide, and t_p2p the part of the near field
-       (its list, its sums) that M2L and the downward pass do not hide. */
+       (its list, its sums) that M2L and the downward pass do not hide.  The sums
+       and the downward pass take turns as the device deals them: where the sums
+       fill it first, their time shows in t_down and t_p2p is short. */
     double t_tree, t_estimate, t_up, t_walk, t_m2l, t_p2p, t_down, t_total;
     /* average duration of one launch of the M2L and P2P kernels (ms) */
     double t_m2l_kernel, t_p2p_kernel;

@@ -7,8 +7,19 @@
 //   up        P2M, M2M, multipole power
 //   walk      breadth-first dual tree walk -> M2L and P2P lists; M2L; P2P
 //   down      L2L, L2P, output
-// Everything is ordered on one stream.  The host reads back a few counters
-// (cells per tree level, pairs per walk sweep) to size the next launch.
+// Work is ordered on two streams: the context's (`stream`) carries the path, and a
+// side stream takes what is independent of it, forked and joined by events
+// (ev_fork, ev_join; join_side before the first use of what it wrote):
+//  - after the octree: the enclosing-sphere centres, then the upward pass, beside
+//    the estimate of the sink scale; joined before the walk;
+//  - after the walk: the near field (its list, plan and sums), beside the M2L
+//    list's sort, M2L and the downward pass; joined before the output.
+// What both streams use at one time is kept apart: the main stream's scratch is
+// tmp, the side stream's tmp_side; of the device counters (nonfinite) the main
+// stream has 0..2, 4, 5 and 8..11, the side stream 3 and 12..15; of the host
+// slots (hint) the side stream has 4..7, the main stream the others.
+// The host reads back a few counters (cells, pairs per walk sweep, list sizes) to
+// size the next launches.
 #include "../../include/fmm.h"
 #include "internal.h"
 #include "jerk.h"
@@ -566,7 +577,6 @@ void prepare_p2p(fmm_ctx *c, int64_t nlist, bool by_source, bool side = false) {
 // sizes the buffers, exec_p2p queues the rest.
 struct P2PPlan {
     bool side = false;
-    const uint8_t *active = nullptr;
     int *up = nullptr;
     int width = 0;                 // sinks per task and entries of a partial row
     int ntasks = 0, prows = 0;     // (FP64: a row per task)
@@ -585,7 +595,6 @@ P2PPlan begin_p2p(fmm_ctx *c, const uint8_t *active, int width, bool side = fals
     TreeArrays t = tree_arrays(c);
     P2PPlan pl;
     pl.side = side;
-    pl.active = active;
     pl.width = width;
     int *ntask = ensure<int>(c->pt_n, (size_t)nl + 1), *mtask = ensure<int>(c->pt_m, (size_t)nl + 1);
     pl.nts = ensure<int>(c->pt_s, (size_t)nl + 1);

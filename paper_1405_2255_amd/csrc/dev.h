@@ -16,17 +16,7 @@ struct cplx {
 __device__ __forceinline__ cplx cmul(cplx a, cplx b) {
     return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
-__device__ __forceinline__ cplx cscale(cplx a, double s) { return {a.re * s, a.im * s}; }
 __device__ __forceinline__ cplx cadd(cplx a, cplx b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cplx csub(cplx a, cplx b) { return {a.re - b.re, a.im - b.im}; }
-
-// acc += s * conj?(a) * b with the conjugation of a chosen at compile time.
-template <bool CONJ_A>
-__device__ __forceinline__ void cmac(cplx &acc, cplx a, cplx b, double s) {
-    const double ar = a.re * s, ai = (CONJ_A ? -a.im : a.im) * s;
-    acc.re = fma(ar, b.re, fma(-ai, b.im, acc.re));
-    acc.im = fma(ar, b.im, fma(ai, b.re, acc.im));
-}
 
 // Non-negative doubles order like their bit patterns: max/min of them can be
 // taken with integer atomics.

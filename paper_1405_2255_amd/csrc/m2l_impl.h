@@ -24,6 +24,11 @@ namespace m2l_detail {
 // is loaded once per pass, in storage order, M2L_AHEAD ahead of its use.  The lanes
 // read different cells, so a load visits the L1 cache once per lane: the number
 // of loads and of multiply-adds bound the kernel about equally.
+//
+// At 10^6 bodies, p = 15 (1.9 x 10^6 pairs) / 10^5, p = 13 / a list of 5.7 x 10^4
+// pairs, p = 15: 2.05 / 0.24 / 0.20 ms.  With 150 registers (more passes) 2.42 /
+// 0.24 / 0.18, with 235 (spills) 2.01 / 0.32 / 0.25; with 2 multipoles ahead 1.99 /
+// 0.28 / 0.21, with 8 (more spills) 2.01 / 0.24 / 0.19.
 constexpr int M2L_REGS = 195;    // 32-bit registers of accumulators and rows
 constexpr int M2L_AHEAD = 4;     // multipoles in flight
 

@@ -8,7 +8,9 @@
 // pass: the digit counts of every pass are known beforehand (they do not depend
 // on the order), and a tile learns how many equal digits lie in the tiles
 // before it from what those have published (each publishes its own counts at
-// once and its running sum as soon as it knows it).  A key's rank inside its
+// once and its running sum as soon as it knows it): the prefix scan by looking
+// back of Merrill and Garland (2016), as Adinets and Merrill (2022) use it for
+// digits.  A key's rank inside its
 // tile comes from 64-wide ballot matching of equal digits.
 #include "internal.h"
 #include "dev.h"
