@@ -8,15 +8,15 @@
 // sink coordinate is one instruction with a scalar operand.  Each sink's sum
 // stays spread over the lanes until the end of the slice, where the lanes are
 // added once.  What bounds it is VALU issue: 16 FP64 operations and a
-// quarter-rate reciprocal square root per pair, 20 issue slots; 22.5 are
-// issued, 92% of the kernel's cycles.  Measured at N = 10^6 Plummer (1.47e10
-// pairs, leaves of 23 particles on average): 10.3 ms, 1.43e12 pairs/s, against
+// quarter-rate reciprocal square root per pair, 20 issue slots; 22.4 are
+// issued, 95% of the kernel's cycles.  Measured at N = 10^6 Plummer (1.47e10
+// pairs, leaves of 23 particles on average): 10.2 ms, 1.44e12 pairs/s, against
 // 12.9 ms for two sinks per lane with strided phases (26 slots per pair: lanes
 // idle in uneven groups, a load per two pairs); the short lists of the sink-scale
 // estimate at N = 10^5: 75 us against 214 us.  Loading the next step's source
-// ahead costs registers and moves and is slower (11.0 ms): four wavefronts per
+// ahead costs registers and moves and is slower (by 0.7 ms): four wavefronts per
 // SIMD cover the load.  The lists are flattened once per leaf by the plan:
-// flattening them in each wavefront took 11.5 ms.
+// flattening them in each wavefront took 1.2 ms more.
 //
 // The order in which a sink's sources are added depends only on its leaf's
 // lists (lane = position in the list modulo 64, slices of NEAR_TASK sources,

@@ -59,8 +59,8 @@ constexpr uint32_t slice_length(int64_t j0, int64_t j1) {
 // bytes each; at most one leaf's entries more, which are fewer than its sources),
 // so that offsets inside a part fit 32 bits and the list's memory is bounded:
 // part k holds the leaves whose entries begin in [k NEAR_ENTRIES, (k + 1)
-// NEAR_ENTRIES).  10^6 bodies in leaves of 80 have 1.1e7 entries; in leaves of
-// one body up to 4.6e8.
+// NEAR_ENTRIES).  10^6 bodies in leaves of 80 have 4e6 entries, in leaves of one
+// body 1.7e8 to 2.2e8 (2^31 would come at 10^7 bodies).
 constexpr int64_t NEAR_ENTRIES = int64_t(1) << 27;
 constexpr int near_parts(int64_t entries) {
     return (int)std::max<int64_t>(1, (entries + NEAR_ENTRIES - 1) / NEAR_ENTRIES);
